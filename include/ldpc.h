@@ -175,11 +175,14 @@ ldpc_status ldpc_decode(const ldpc_graph* g, const float* llr, int32_t gamma, in
  * on one compute unit, its check-to-variable messages in registers and its
  * posterior sums in LDS (a (3,6) code up to n = 18,432; codes whose base
  * has 3 rows of weight <= 9 or 4 rows of weight <= 8, no empty base column,
- * p <= 3072, two n-float arrays within the device's LDS per workgroup), 0
+ * p <= 3072, two n-float arrays within the device's LDS per workgroup; and
+ * codes of a full base, p >= 64, with 3 rows of weight 9 (p <= 3072) or 18
+ * (p <= 1536) or 4 rows of weight 24 (p <= 1024)), 0
  * when it runs the message-package decoder (edge messages in the workspace,
- * one launch per half-iteration).  Both compute Algorithm 1 with the FP32
- * check rule in the (tanh, 1 - tanh) pair form; the on-chip decoder carries
- * the pairs unnormalised (no reciprocal per input) and forms each
+ * one launch per half-iteration).  Both compute Algorithm 1; the package
+ * decoder's FP32 check rule combines (tanh, 1 - tanh) pairs, the on-chip
+ * decoder's the two parities' probabilities up to a common factor (no
+ * reciprocal per input), and the on-chip decoder forms each
  * variable-to-check message as clip(L - alpha) from the posterior sum
  * instead of summing the other edges, so the two agree within FP32
  * rounding, not bit for bit.  Setting

@@ -1,7 +1,7 @@
 """Build step for the HIP library: compiles csrc/ into libldpc_hip.so (gfx950).
 
 Each source is compiled to its own object in parallel (the device code of the
-two .hip files dominates the build time), then the objects are linked."""
+the .hip files dominates the build time), then the objects are linked."""
 from __future__ import annotations
 
 import os
@@ -14,7 +14,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libldpc_hip.so")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("graph.cpp", "decode.hip", "plan.hip", "onchip.hip")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("graph.cpp", "decode.hip", "plan.hip", "onchip.hip", "onchip_wide.hip")]
 ARCH = os.environ.get("LDPC_OFFLOAD_ARCH", "gfx950")
 
 

@@ -27,4 +27,10 @@ bool onchip_selected(const ldpc_graph* g);
 int onchip_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
                   uint8_t* bits, int32_t* iters, uint8_t* converged, hipStream_t st, const float* nms_w = nullptr);
 
+// The same for the kernel of onchip_wide.hip: regular bases of 3 rows of
+// weight 9 or 18 or 4 rows of weight 24, one posterior sum per variable.
+bool onchip_wide_fits(const ldpc_graph* g);
+int onchip_wide_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
+                       uint8_t* bits, int32_t* iters, uint8_t* converged, hipStream_t st, const float* nms_w);
+
 }  // namespace ldpc

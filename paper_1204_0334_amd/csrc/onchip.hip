@@ -113,41 +113,6 @@ __device__ __forceinline__ float* lds_ptr(float2* L, uint32_t byte) {
 // LLRs are scaled by log2(e) once when read and the posteriors unscaled when
 // written.
 
-// Learned min-sum rule (the package decoder's RULE 1) in base-2 units:
-// alpha_k = w_k s_k max(m_k - b_k, 0), m_k the smallest |beta| of the row's
-// other edges (|beta| <= 30 log2 e already), s_k the product of their signs
-// (negative iff beta < 0); w[2k], w[2k+1] = (scale, offset) of slot k's
-// block, the offset in natural units (scaled here).
-template <int DC>
-__device__ __forceinline__ void nms2_row(const float (&in)[DC], int d, const float* __restrict__ w,
-                                         float (&out)[DC]) {
-    float min1 = __builtin_inff(), min2 = __builtin_inff();
-    int idx1 = -1;
-    uint32_t parity = 0;
-#pragma unroll
-    for (int k = 0; k < DC; ++k) {
-        if (k < d) {
-            const float m = fabsf(in[k]);
-            if (m < min1) {
-                min2 = min1;
-                min1 = m;
-                idx1 = k;
-            } else if (m < min2) {
-                min2 = m;
-            }
-            parity ^= (uint32_t)(in[k] < 0.0f);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < DC; ++k) {
-        if (k < d) {
-            const float m = k == idx1 ? min2 : min1;
-            const float a = w[2 * k] * fmaxf(m - w[2 * k + 1] * kLog2eF, 0.0f);
-            out[k] = (parity ^ (uint32_t)(in[k] < 0.0f)) ? -a : a;
-        }
-    }
-}
-
 // Eq. 3 for one row in base-2 units (check2.h's check2_row) with each
 // input's pair left unnormalised: (u, w, s) = (1 - e, 2e, 1 + e), e =
 // 2^-|x|, is (t, q, 1) times 1 + e, so no reciprocal is taken per input.
@@ -474,8 +439,8 @@ constexpr Variant variant() {
 // (base rows, rows per thread and base row, row-weight capacity, regular
 // base); each compiles without spilled vector registers but the general
 // 3 x 9 variant with two rows per thread (4 values, 12 with early stopping;
-// 54 alphas per thread at most: rows of weight 18 would spill and stay with
-// the package decoder)
+// 54 alphas per thread at most).  Heavier rows and longer codes go to the
+// kernel of onchip_wide.hip.
 const Variant kVariants[] = {
     variant<3, 1, 6, true>(),  variant<3, 2, 6, true>(),  variant<3, 3, 6, true>(),
     variant<3, 1, 9, true>(),  variant<3, 2, 9, true>(),
@@ -539,7 +504,7 @@ bool choose(const ldpc_graph* g, int rule, Choice& c) {
 
 bool onchip_fits(const ldpc_graph* g) {
     Choice c;
-    return choose(g, 0, c);
+    return choose(g, 0, c) || onchip_wide_fits(g);
 }
 
 bool onchip_selected(const ldpc_graph* g) {
@@ -551,7 +516,8 @@ bool onchip_selected(const ldpc_graph* g) {
 int onchip_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
                   uint8_t* bits, int32_t* iters, uint8_t* converged, hipStream_t st, const float* nms_w) {
     Choice c;
-    if (!choose(g, nms_w ? 1 : 0, c)) return 0;
+    if (!choose(g, nms_w ? 1 : 0, c))
+        return onchip_wide_decode(g, llr, gamma, max_iters, early, post, bits, iters, converged, st, nms_w);
     const QCDesc& D = g->qc;
     OnchipArgs A{};
     A.llr = llr;

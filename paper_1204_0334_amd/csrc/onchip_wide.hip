@@ -1,0 +1,379 @@
+// Block decoder with a whole frame on one compute unit (gfx950), for codes
+// whose posterior sums are too large, or whose check rows are too heavy, for
+// the kernel of onchip.hip: the rate-5/6 4 x 24 codes up to n = 24,576, for
+// instance.  As there, one workgroup decodes one frame, thread i keeps the
+// check-to-variable messages of check rows (j, i + q*TB) of every base row in
+// registers for the whole decode, and beta = clip(L - alpha) is formed from
+// the posterior sums in LDS.  What differs:
+//
+//   * One sum per variable instead of two.  An iteration first updates all
+//     check rows from the sums (every thread, all base rows, no barrier in
+//     between), then, base row by base row with a barrier after each, adds
+//     the new messages into the sums.  n floats of LDS (two arrays of n would
+//     not fit), at J + 2 barriers per iteration instead of J.
+//   * Addresses without a wrap.  The rows of a wavefront are consecutive, so
+//     the variables an edge slot meets are consecutive in a base column up to
+//     one wrap.  Every column is stored with 64 further cells behind its p
+//     sums, so a wavefront's 64 variables are one run of cells from a base
+//     that the scalar unit computes: one vector operation per edge.  While
+//     sums are accumulated, a further cell takes the part of its variable's
+//     sum that arrives across the wrap; a last short step adds the two parts
+//     and writes the total to both.
+//   * Row updates in place and in blocks: a row's inputs replace its old
+//     messages, and the sweeps of Eq. 3 keep suffix pairs of one block of
+//     slots at a time (check2e_row), so that the 96 messages of four rows of
+//     weight 24 and their update fit the 128 registers a thread has with four
+//     wavefronts on a SIMD.
+//
+// The decode is bound by the vector ALUs: about 25 plain instructions and 3
+// transcendentals per edge and iteration.  4 x 24 code, p = 1024, 1024
+// frames, 30 iterations: 2.53 ms (98,304 edges per frame: 1.19 10^12 edge
+// updates per second), 12.15 ms with the message-package decoder, which
+// streams every message through HBM twice an iteration.  Tried on the way
+// there: (u, w, s) triples instead of pairs, two rows per thread, 512 threads
+// and run bases formed by the scalar unit 3.9 ms.
+#include <hip/hip_runtime.h>
+
+#include <cstdlib>
+#include <cstring>
+
+#include "check2.h"
+#include "device.h"
+#include "internal.h"
+#include "onchip.h"
+
+namespace ldpc {
+
+constexpr int kOwRows = 4;     // base rows an instantiation may have
+constexpr int kOwSlots = 24;   // edge slots per row an instantiation may have
+constexpr int kOwPad = 64;     // further cells behind each column
+constexpr int kOwMinP = 64;    // a further cell repeats a cell of its own column
+
+// Edge slot k of base row j (index j * kOwSlots + k): row (j, s) meets
+// variable (l, (s + a) mod p) of its base column l.  Byte offsets.
+struct WideEdge {
+    uint32_t sh4;     // 4 a
+    uint32_t cb4;     // 4 l (p + kOwPad): the column's first cell
+    uint32_t gb4;     // 4 l p: the column's first channel LLR
+    uint32_t first;   // 1: the lowest nonzero block of its base column
+};
+
+struct WideArgs {
+    WideEdge e[kOwRows * kOwSlots];
+    const float* llr;                 // [gamma][n]
+    float* post;                      // [gamma][n]
+    uint8_t* bits;                    // [gamma][n]
+    int32_t* iters;                   // [gamma] or NULL
+    uint8_t* conv;                    // [gamma] or NULL
+    const float* nms_w;               // learned min-sum (RULE 1): [iters][blocks][2]
+    int32_t n, p, L, max_iters, nb;
+    int32_t deg[kOwRows];             // nonzero blocks of base row j
+    int32_t rb0[kOwRows];             // first block of base row j
+};
+
+__device__ __forceinline__ float* ow_cell(float* L, uint32_t byte) {
+    return reinterpret_cast<float*>(reinterpret_cast<char*>(L) + byte);
+}
+
+// One frame per workgroup.  NJ base rows, NQ rows per thread and base row, DC
+// slots per row, REG: every base row has DC nonzero blocks; RULE 0:
+// sum-product, 1: learned min-sum; NB: blocks of check2e_row; MAXT: threads
+// the register budget is for; EARLY: with early stopping.
+template <int NJ, int NQ, int DC, bool REG, int RULE, int NB, int MAXT, bool EARLY>
+__global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
+    // dynamic LDS: L columns of p + kOwPad sums, then two flag words
+    extern __shared__ float cells[];
+    const int p = A.p, nl = A.L;
+    const int stride = p + kOwPad;
+    uint32_t* flag = reinterpret_cast<uint32_t*>(cells + (size_t)nl * stride);
+    const int tid = threadIdx.x;
+    const int TB = blockDim.x;
+    const size_t f0 = (size_t)blockIdx.x * A.n;
+    const char* __restrict__ mu = reinterpret_cast<const char*>(A.llr + f0);
+    const uint32_t p4 = 4u * (uint32_t)p, lane4 = 4u * (uint32_t)(tid & 63);
+    // L of "iteration 0" is mu, so that iteration 1 reads beta = clip(mu - 0)
+    for (int l = 0; l < nl; ++l)
+        for (int t = tid; t < stride; t += TB)
+            cells[l * stride + t] = A.llr[f0 + (size_t)l * p + (t < p ? t : t - p)] * kLog2eF + 0.0f;
+    if (tid < 2) flag[tid] = 0u;
+    float al[NJ][NQ][DC];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int k = 0; k < DC; ++k) al[j][q][k] = 0.0f;
+    __syncthreads();
+
+    // First cell of edge slot k of this wavefront's rows (j, q): a run of 64
+    // cells serves all lanes.  Lane i of run[v] holds the first cell of edge
+    // 64 v + i, edges numbered (j * NQ + q) * DC + k.
+    constexpr int kEdges = NJ * NQ * DC, kRuns = (kEdges + 63) / 64;
+    uint32_t run[kRuns];
+#pragma unroll
+    for (int v = 0; v < kRuns; ++v) {
+        const int i = min(v * 64 + (tid & 63), kEdges - 1);
+        const int jq = i / DC;
+        const WideEdge& e = A.e[(jq / NQ) * kOwSlots + i - jq * DC];
+        const uint32_t t = 4u * (uint32_t)((tid & ~63) + (jq % NQ) * TB) + e.sh4;
+        run[v] = e.cb4 + min(t, t - p4);
+    }
+    const uint32_t tid4 = 4u * (uint32_t)tid;
+
+    int it = 1, stop = 0;
+    for (; it <= A.max_iters; ++it) {
+        // opaque, so that the runs' first cells are read from the lanes where
+        // they are used and not held in scalar registers (there are too few)
+#pragma unroll
+        for (int v = 0; v < kRuns; ++v) asm volatile("" : "+v"(run[v]));
+        auto first_cell = [&](int j, int q, int k) -> uint32_t {
+            const int i = (j * NQ + q) * DC + k;
+            return (uint32_t)__builtin_amdgcn_readlane((int)run[i >> 6], i & 63);
+        };
+
+        // check rows: new messages from the sums of the previous iteration
+        uint64_t viol = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int d = REG ? DC : A.deg[j];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                if (tid4 + 4u * (uint32_t)(q * TB) < p4) {
+                    float (&x)[DC] = al[j][q];
+                    uint32_t sx = 0;
+#pragma unroll
+                    for (int k = 0; k < DC; ++k) {
+                        if (REG || k < d) {
+                            const float L = *ow_cell(cells, first_cell(j, q, k) + lane4);
+                            // the row's parity in bit 31 (a sum is never -0: it starts from mu + 0)
+                            if (EARLY) sx ^= __float_as_uint(L);
+                            x[k] = clip2(L - x[k]);
+                        } else {
+                            x[k] = 0.0f;
+                        }
+                    }
+                    if (EARLY) viol |= __ballot((int32_t)sx < 0);
+                    if constexpr (RULE == 0)
+                        check2e_row<DC, NB>(x, d);
+                    else
+                        nms2_row<DC>(x, d, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
+                }
+            }
+        }
+        // the syndrome read here is that of iteration it - 1
+        if (EARLY && viol != 0ull && (tid & 63) == 0) flag[it & 1] = 1u;
+        __syncthreads();
+        if (EARLY && it >= 2 && flag[it & 1] == 0u) {
+            stop = it - 1;
+            break;
+        }
+        if (EARLY && tid == 0) flag[(it + 1) & 1] = 0u;
+
+        // sums, base row by base row (within one, no two threads meet the
+        // same variable, and no two lanes the same cell)
+        for (int i = tid; i < nl * kOwPad; i += TB) cells[(i / kOwPad) * stride + p + i % kOwPad] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int d = REG ? DC : A.deg[j];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                if (tid4 + 4u * (uint32_t)(q * TB) < p4) {
+                    constexpr int B = DC % 8 == 0 ? 8 : DC % 6 == 0 ? 6 : 9;
+#pragma unroll
+                    for (int k0 = 0; k0 < DC; k0 += B) {
+                        // all reads of a group before its writes: the compiler cannot
+                        // know that the cells differ
+                        float v[B];
+                        uint32_t at[B];
+#pragma unroll
+                        for (int i = 0; i < B; ++i) {
+                            const int k = k0 + i, jk = j * kOwSlots + k;
+                            if (!(REG || k < d)) continue;
+                            at[i] = first_cell(j, q, k) + lane4;
+                            if (REG ? j == 0 : A.e[jk].first != 0u) {
+                                // the sum starts from mu, in the variable's own cell
+                                uint32_t t = at[i] - A.e[jk].cb4;
+                                t = min(t, t - p4);
+                                at[i] = A.e[jk].cb4 + t;
+                                v[i] = *reinterpret_cast<const float*>(mu + (A.e[jk].gb4 + t)) * kLog2eF + 0.0f;
+                            } else {
+                                v[i] = *ow_cell(cells, at[i]);
+                            }
+                        }
+#pragma unroll
+                        for (int i = 0; i < B; ++i)
+                            if (REG || k0 + i < d) *ow_cell(cells, at[i]) = v[i] + al[j][q][k0 + i];
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        // the parts of a sum on either side of the wrap
+        for (int i = tid; i < nl * kOwPad; i += TB) {
+            float* c = cells + (i / kOwPad) * stride + i % kOwPad;
+            const float L = c[0] + c[p];
+            c[0] = L;
+            c[p] = L;
+        }
+        __syncthreads();
+    }
+
+    int iters_out, conv_out;
+    if (stop) {
+        iters_out = stop;
+        conv_out = 1;
+    } else {
+        // syndrome of the last iteration, in the flag word cleared in it
+        const uint32_t w4 = __builtin_amdgcn_readfirstlane(4u * (uint32_t)(tid & ~63));
+        const int fw = EARLY ? (A.max_iters + 1) & 1 : 0;
+        uint64_t viol = 0;
+        for (int j = 0; j < NJ; ++j) {
+            const int d = REG ? DC : A.deg[j];
+            for (int q = 0; q < NQ; ++q) {
+                const uint32_t s4 = w4 + 4u * (uint32_t)(q * TB);
+                if (s4 + lane4 < p4) {
+                    uint32_t sx = 0;
+                    for (int k = 0; k < d; ++k) {
+                        const WideEdge& e = A.e[j * kOwSlots + k];
+                        const uint32_t t = s4 + e.sh4;
+                        sx ^= __float_as_uint(*ow_cell(cells, e.cb4 + min(t, t - p4) + lane4));
+                    }
+                    viol |= __ballot((int32_t)sx < 0);
+                }
+            }
+        }
+        if (viol != 0ull && (tid & 63) == 0) flag[fw] = 1u;
+        __syncthreads();
+        iters_out = A.max_iters;
+        conv_out = flag[fw] == 0u ? 1 : 0;
+    }
+    for (int l = 0; l < nl; ++l)
+        for (int t = tid; t < p; t += TB) {
+            const float L = cells[l * stride + t];
+            const size_t v = f0 + (size_t)l * p + t;
+            A.post[v] = unscale2(L, A.llr[v]);
+            A.bits[v] = (uint8_t)(L < 0.0f);
+        }
+    if (tid == 0) {
+        if (A.iters) A.iters[blockIdx.x] = iters_out;
+        if (A.conv) A.conv[blockIdx.x] = (uint8_t)conv_out;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+
+namespace {
+
+struct WideVariant {
+    int nj, nq, dc;
+    bool reg;
+    int rule, maxt;
+    const void* fn;         // without early stopping
+    const void* fn_early;   // with early stopping
+};
+
+template <int NJ, int NQ, int DC, bool REG, int RULE, int NB, int MAXT>
+constexpr WideVariant wide() {
+    return WideVariant{NJ, NQ, DC, REG, RULE, MAXT,
+                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, REG, RULE, NB, MAXT, false>),
+                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, REG, RULE, NB, MAXT, true>)};
+}
+
+const WideVariant kWide[] = {
+    wide<4, 1, 24, true, 0, 3, 1024>(),
+    wide<3, 1, 18, true, 0, 2, 1024>(), wide<3, 2, 18, true, 0, 2, 768>(),
+    wide<3, 3, 9, true, 0, 1, 1024>(),
+    wide<4, 1, 24, true, 1, 2, 1024>(),
+    wide<3, 1, 18, true, 1, 2, 1024>(), wide<3, 2, 18, true, 1, 2, 768>(),
+    wide<3, 3, 9, true, 1, 1, 1024>(),
+};
+
+// Which codes: regular bases with a base row that fills a wavefront at least
+// (kOwMinP), whose rows, threads and LDS an instantiation covers.  There is no
+// smallest batch: at 20 iterations a single frame takes 0.64-0.78 of the
+// package decoder's time (4 x 24, p = 1024: 410 us against 526; 3 x 18, p =
+// 1365: 355 against 482), 256 frames 0.24-0.3 (423 us against 1649).
+struct WideChoice {
+    const WideVariant* v;
+    int tb;
+    size_t lds;
+};
+
+bool choose_wide(const ldpc_graph* g, int rule, WideChoice& c) {
+    if (!g || g->kind != LDPC_GRAPH_QC) return false;
+    const QCDesc& D = g->qc;
+    if (D.J > kOwRows || D.dc_max > kOwSlots || D.p < kOwMinP) return false;
+    for (int l = 0; l < D.L; ++l)
+        if (D.cstart[l + 1] == D.cstart[l]) return false;   // a base column without edges
+    bool reg = D.rstart[1] - D.rstart[0] == D.L;
+    for (int j = 0; j < D.J; ++j) reg = reg && (D.rstart[j + 1] - D.rstart[j] == D.dc_max);
+    int dev = 0, limit = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t lds = ((size_t)D.L * (D.p + kOwPad) + 2) * sizeof(float);
+    if (lds > (size_t)limit) return false;
+    for (const WideVariant& v : kWide) {
+        if (v.rule != rule || v.nj != D.J || v.dc != D.dc_max || !reg) continue;
+        const int per = (D.p + v.nq - 1) / v.nq;
+        const int tb = (per + 63) / 64 * 64;
+        if (tb > v.maxt) continue;
+        c.v = &v;
+        c.tb = tb;
+        c.lds = lds;
+        return true;
+    }
+    return false;
+}
+
+}  // namespace
+
+bool onchip_wide_fits(const ldpc_graph* g) {
+    WideChoice c;
+    return choose_wide(g, 0, c);
+}
+
+int onchip_wide_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
+                       uint8_t* bits, int32_t* iters, uint8_t* converged, hipStream_t st, const float* nms_w) {
+    WideChoice c;
+    if (!choose_wide(g, nms_w ? 1 : 0, c)) return 0;
+    const QCDesc& D = g->qc;
+    WideArgs A{};
+    A.llr = llr;
+    A.post = post;
+    A.bits = bits;
+    A.iters = iters;
+    A.conv = converged;
+    A.nms_w = nms_w;
+    A.n = D.n;
+    A.p = D.p;
+    A.L = D.L;
+    A.max_iters = max_iters;
+    A.nb = D.nb;
+    for (int j = 0; j < D.J; ++j) {
+        A.deg[j] = D.rstart[j + 1] - D.rstart[j];
+        A.rb0[j] = D.rstart[j];
+        for (int k = 0; k < A.deg[j]; ++k) {
+            const int b = D.rstart[j] + k, l = D.ecol[b];
+            WideEdge& e = A.e[j * kOwSlots + k];
+            e.sh4 = 4u * (uint32_t)D.eshift[b];
+            e.cb4 = 4u * (uint32_t)(l * (D.p + kOwPad));
+            e.gb4 = 4u * (uint32_t)(l * D.p);
+            e.first = D.cedge[D.cstart[l]] == b ? 1u : 0u;   // edge blocks of a column ascend by base row
+        }
+    }
+    const void* fn = early ? c.v->fn_early : c.v->fn;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    timing::Scope ts(23, st);
+    void* args[] = {&A};
+    return hipLaunchKernel(fn, dim3((unsigned)gamma), dim3((unsigned)c.tb), args, c.lds, st) == hipSuccess ? 1 : -1;
+}
+
+}  // namespace ldpc
