@@ -104,33 +104,21 @@ def window_algorithmic_bytes(info, W: int, gamma: int):
 
 
 # Issue slots of the FP32 vector ALUs (a transcendental -- exp2, log2,
-# reciprocal -- issues at a quarter of the rate, so it counts 4) for the
-# check rules the decoders run, Eq. 3 in base-2 units.  Convolutional-code
-# decoders, (t, q) form: a row of weight d takes, over its edges, the input
-# pairs 4d (1 + e, e * r, q = 2 e r, t = 1 - q), the sign product d - 1, the
-# suffix sweep 2 (d - 2), the prefix sweep with the exclusive complements
-# 3 (d - 2), the output pairs 2d (1 + P, times 1/Q), the output signs 2d:
-# 14d - 11 plain operations, and 4d transcendentals (2^-|x| and 1/(1 + e) of
-# each input, 1/Q and log2 of each output): 30d - 11 slots.  On-chip block
-# decoder, the same pairs unnormalised, (u, w, s) = (1 - e, 2e, 1 + e): the
-# input triples 3d, the sign product d - 1, the suffix sweep 4 (d - 2) - 1
-# (U, W, S; the last S is not needed), the prefix sweep with the exclusive
-# triples 6 (d - 2), the outputs 2d (2U + W, times 1/W), the output signs 2d:
-# 18d - 22 plain operations, and 3d transcendentals (2^-|x| of each input,
-# 1/W and log2 of each output): 30d - 22 slots.  Variable side per edge: the
-# on-chip block decoder forms L = mu + sum alpha and beta = clip(L - alpha)
-# (3: the addition, the subtraction, the clip); the window decoder sums the
-# other edges by prefix and suffix (4: two partial sums, mu + sum, the clip).
+# reciprocal -- issues at a quarter of the rate, so it counts 4) for the check
+# rule the on-chip block decoders and the convolutional-code decoders run,
+# Eq. 3 in base-2 units on (even, odd) probability pairs: a row of weight d
+# takes, over its edges, collecting the signs d, the suffix and the prefix
+# sweep 2 (d - 2) each (two multiply-adds a step), the exclusive pairs 4d - 10
+# (none for the first and the last slot, two for the second), the ratios d and
+# the output signs 2d: 12d - 18 plain operations, and 3d transcendentals
+# (2^-|x| of each input, the reciprocal and log2 of each output): 24d - 18
+# slots.  Variable side per edge: L = mu + sum alpha and beta = clip(L -
+# alpha) (3: the addition, the subtraction, the clip).
 def check_row_slots(d: int) -> int:
-    return 30 * d - 11
+    return 24 * d - 18
 
 
-def onchip_check_row_slots(d: int) -> int:
-    return 30 * d - 22
-
-
-VN_EDGE_SLOTS = 4
-ONCHIP_VN_EDGE_SLOTS = 3
+VN_EDGE_SLOTS = 3
 # FP32 vector issue rate: 256 CUs x 128 FP32 lanes x 2.4 GHz = 78.6 T lane
 # operations/s (MI355X's 157.3 TFLOP/s FP32 vector figure counts an FMA as
 # two).  The kernels use no packed-FP32 instructions; plain VOP2/VOP3 FP32
@@ -157,6 +145,16 @@ def window_algorithmic_ops(info, W: int, K: int, gamma: int):
         dfull = (ms + 1) * info["Lb"]
         total += K * (check_row_slots(dfull) * e_cn / dfull + VN_EDGE_SLOTS * e_vn)
     return total * gamma
+
+
+def pipeline_algorithmic_ops(info, I: int, gamma: int):
+    """ALU issue slots (lane operations) of one pipelined decode: I check and
+    variable updates of every edge of the chain."""
+    c, ms, L = info["c"], info["ms"], info["positions"]
+    per_pair = info["Jb"] * info["Lb"] * info["p"]
+    edges = sum(per_pair for t in range(info["layers"]) for d in range(ms + 1) if 0 <= t - d < L)
+    dfull = (ms + 1) * info["Lb"]
+    return I * gamma * (check_row_slots(dfull) / dfull + VN_EDGE_SLOTS) * edges
 
 
 def pipeline_algorithmic_bytes(info, I: int, gamma: int):
@@ -268,6 +266,18 @@ def bench_window(args, pipeline: bool = False):
                     "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_ops_per_launch": ops,
                     "note": "FP32 vector issue slots (transcendentals count 4) against the FP32 vector "
                             "issue rate (256 CUs x 128 lanes x 2.4 GHz); messages stay in LDS"}
+    elif pipeline and not per_kernel["pipeline_variable_node"][0]:
+        # each stream on one compute unit, several processors per sweep: the
+        # bound is the ALUs
+        launches, ms = per_kernel["pipeline_check_node"]
+        decode_s = ms / args.steps * 1e-3
+        ops = pipeline_algorithmic_ops(g.info, I, gamma)
+        achieved = ops / decode_s / 1e12
+        roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": round(ALU_PEAK_TOPS, 2), "unit": "Top/s",
+                    "frac": round(achieved / ALU_PEAK_TOPS, 4), "traffic": None, "kernel": "sweep_kernel",
+                    "avg_launch_us": round(ms / launches * 1e3, 2), "algorithmic_ops_per_decode": ops,
+                    "note": "FP32 vector issue slots (transcendentals count 4) against the FP32 vector "
+                            "issue rate (256 CUs x 128 lanes x 2.4 GHz); messages cross memory once per sweep"}
     elif pipeline:
         # the ring of 68 frames x 512 streams (about 74 MB) stays in the
         # L2 / Infinity Cache, so algorithmic bytes overstate what crosses the
@@ -630,7 +640,7 @@ def bench_plan(args):
     if oc and per_kernel["onchip_decode"][0]:
         # fixed work: every iteration of every frame of the on-chip codes,
         # over their launches' summed time (they run beside the phase launches)
-        slots = sum(iters * gammas[i] * (onchip_row_slots(shifts[i], specs[i]["p"]) + ONCHIP_VN_EDGE_SLOTS * E[i])
+        slots = sum(iters * gammas[i] * (onchip_row_slots(shifts[i], specs[i]["p"]) + VN_EDGE_SLOTS * E[i])
                     for i in oc)
         t_s = per_kernel["onchip_decode"][1] * 1e-3 / args.steps
         onchip = {"bound": "alu", "codes": [i for i in oc], "achieved": round(slots / t_s / 1e12, 2),
@@ -876,10 +886,10 @@ def gamma_control(g, shifts, llr_dev, iters, gamma, steps=5):
 
 def onchip_row_slots(shifts, p: int) -> int:
     """Check-rule issue slots of one iteration of one frame of the QC code
-    with this shift table: p rows of each base row, onchip_check_row_slots(weight)
+    with this shift table: p rows of each base row, check_row_slots(weight)
     each (the weight: the base row's nonzero blocks)."""
     import numpy as np
-    return sum(p * onchip_check_row_slots(int(d)) for d in (np.asarray(shifts) >= 0).sum(1))
+    return sum(p * check_row_slots(int(d)) for d in (np.asarray(shifts) >= 0).sum(1))
 
 
 def onchip_roofline(per_kernel, shifts, p: int, E: int, iters: int, gamma: int, traffic_path=TRAFFIC_FILE_ONCHIP):
@@ -890,14 +900,14 @@ def onchip_roofline(per_kernel, shifts, p: int, E: int, iters: int, gamma: int, 
     FP32 vector issue rate."""
     launches, ms = per_kernel["onchip_decode"]
     avg_s = ms / launches * 1e-3
-    ops = iters * gamma * (onchip_row_slots(shifts, p) + ONCHIP_VN_EDGE_SLOTS * E)
+    ops = iters * gamma * (onchip_row_slots(shifts, p) + VN_EDGE_SLOTS * E)
     achieved = ops / avg_s / 1e12
     return {"bound": "alu", "achieved": round(achieved, 2), "peak": round(ALU_PEAK_TOPS, 2), "unit": "Top/s",
             "frac": round(achieved / ALU_PEAK_TOPS, 4),
             "traffic": measured_traffic("onchip_decode", traffic_path, ONCHIP_SOURCES) if traffic_path else None,
             "kernel": "onchip_decode",
             "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_ops_per_launch": ops,
-            "note": "FP32 vector issue slots of the check rule (30 d - 22 per row of weight d, transcendentals "
+            "note": "FP32 vector issue slots of the check rule (24 d - 18 per row of weight d, transcendentals "
                     "count 4) and 3 per variable edge, against the FP32 vector issue rate (256 CUs x 128 lanes x "
                     "2.4 GHz); each frame's messages stay in registers and LDS of one compute unit"}
 

@@ -456,6 +456,16 @@ ldpc_status ldpc_decode_window(const ldpc_graph* conv, const float* llr, int32_t
  * only iters * (ms+1) frames, plus 7 it reads in ahead so that one launch
  * brings in 8 entering frames (workspace from
  * ldpc_workspace_size(conv, gamma, iters, 0)).
+ * Execution: codes with one circulant row per layer and full sub-blocks
+ * (T = ms + 1 = 3 with 2 circulant columns per position, or 4 with 6; p as
+ * the LDS allows, at most 512 or 1024) are decoded with a stream on one
+ * compute unit, several processors per sweep of the chain, the messages
+ * between sweeps in the workspace: ldpc_workspace_size is then the larger of
+ * that and the ring.  Where those messages of 256 streams (or all, if fewer)
+ * would take more than 4 GiB, for other codes, with
+ * LDPC_PIPELINE_PATH=launch, and when the workspace passed holds only the
+ * ring, every slot is two launches over all streams.  Both give the same
+ * results bit for bit.
  *   llr, post, bits as for ldpc_decode_window; 1 <= iters <= 64.
  * Errors: EINVAL (QC graph, iters < 1, NULL pointers), EUNSUPPORTED
  * (iters > 64), EWORKSPACE, EHIP.
@@ -502,7 +512,8 @@ const char* ldpc_status_str(ldpc_status s);
  *   last variable-node pass of a decode without early stopping, which writes
  *   the outputs; with early stopping the final transpose),
  *   5 frame status, 6 window ingest, 7 window check-node,
- *   8 window variable-node, 9 pipeline ingest, 10 pipeline check-node,
+ *   8 window variable-node, 9 pipeline ingest, 10 pipeline check-node (a
+ *   sweep, where each stream is decoded on one compute unit),
  *   11 pipeline variable-node, 12 training check-node, 13 training
  *   variable-node, 14 training variable-node backward, 15 training
  *   check-node backward, 16 training loss and gradient reductions,

@@ -48,6 +48,7 @@
 #include "device.h"
 #include "internal.h"
 #include "onchip.h"
+#include "sweep.h"
 
 namespace ldpc {
 
@@ -1090,52 +1091,34 @@ __global__ void __launch_bounds__(kBlock) conv_cn_kernel(const ConvDesc D, const
     if (tile >= P.tiles) return;
     const ConvRow R(D, U, row);
     float* mt = P.msg + (size_t)tile * U.ring * U.eps * Gt + (size_t)lane * FPL;
-    float in[DCMAX][FPL];
-    float t[FPL][DCMAX], q[FPL][DCMAX];
-    uint32_t sgn[FPL];
-#pragma unroll
-    for (int f = 0; f < FPL; ++f) sgn[f] = 0;
+    float io[DCMAX][FPL];
 #pragma unroll
     for (int k = 0; k < DCMAX; ++k) {
         if (R.valid(D, S, k)) {
-            load_frames<FPL>(mt + (size_t)R.pkg(D, S, U, k) * Gt, in[k]);
+            load_frames<FPL>(mt + (size_t)R.pkg(D, S, U, k) * Gt, io[k]);
         } else {
+            // no such edge: the identity of the row's products
 #pragma unroll
-            for (int f = 0; f < FPL; ++f) in[k][f] = 0.0f;
+            for (int f = 0; f < FPL; ++f) io[k][f] = __builtin_inff();
         }
     }
-#pragma unroll
-    for (int k = 0; k < DCMAX; ++k) {
-        const bool ok = R.valid(D, S, k);
-#pragma unroll
-        for (int f = 0; f < FPL; ++f) {
-            if (ok) {
-                tq2_of(in[k][f], t[f][k], q[f][k]);
-                sgn[f] ^= __float_as_uint(in[k][f]) & 0x80000000u;
-            } else {
-                t[f][k] = 1.0f;
-                q[f][k] = 0.0f;
-            }
-        }
-    }
-    float outv[DCMAX][FPL];
 #pragma unroll
     for (int f = 0; f < FPL; ++f) {
-        float mag[DCMAX];
-        boxplus2_fb<DCMAX>(t[f], q[f], mag);
+        float x[DCMAX];
 #pragma unroll
-        for (int k = 0; k < DCMAX; ++k) {
-            const uint32_t sg = sgn[f] ^ (__float_as_uint(in[k][f]) & 0x80000000u);
-            outv[k][f] = __uint_as_float(__float_as_uint(mag[k]) | sg);
-        }
+        for (int k = 0; k < DCMAX; ++k) x[k] = io[k][f];
+        check2e_row<DCMAX, 1>(x, DCMAX);
+#pragma unroll
+        for (int k = 0; k < DCMAX; ++k) io[k][f] = x[k];
     }
 #pragma unroll
     for (int k = 0; k < DCMAX; ++k)
-        if (R.valid(D, S, k) && R.writable(S, k)) store_frames<FPL>(mt + (size_t)R.pkg(D, S, U, k) * Gt, outv[k]);
+        if (R.valid(D, S, k) && R.writable(S, k)) store_frames<FPL>(mt + (size_t)R.pkg(D, S, U, k) * Gt, io[k]);
 }
 
-// One variable column: betas on every existing edge, posterior from the
-// alphas of layers lo..hi.
+// One variable column: the posterior from the channel LLR and the alphas of
+// layers lo..hi in ascending order, betas (the posterior less the own alpha,
+// clipped) on every existing edge.
 template <int DVMAX, int FPL>
 __device__ __forceinline__ void conv_vn_column(const ConvDesc& D, const ConvSlots& S, const ConvUnits& U,
                                                const ConvParams& P, const ConvCol& C, int tile, int lane,
@@ -1155,27 +1138,17 @@ __device__ __forceinline__ void conv_vn_column(const ConvDesc& D, const ConvSlot
             for (int f = 0; f < FPL; ++f) a[k][f] = 0.0f;
         }
     }
-    float b[DVMAX][FPL];
 #pragma unroll
     for (int f = 0; f < FPL; ++f) {
-        float suf[DVMAX];
-        float Ssum = 0.0f;
+        L[f] = mu[f];
 #pragma unroll
-        for (int k = DVMAX - 1; k >= 0; --k) {
-            suf[k] = Ssum;
-            Ssum += a[k][f];
-        }
-        float pre = 0.0f;
+        for (int k = 0; k < DVMAX; ++k) L[f] += a[k][f];
 #pragma unroll
-        for (int k = 0; k < DVMAX; ++k) {
-            b[k][f] = clip2(mu[f] + (pre + suf[k]));
-            pre += a[k][f];
-        }
-        L[f] = mu[f] + pre;
+        for (int k = 0; k < DVMAX; ++k) a[k][f] = clip2(L[f] - a[k][f]);
     }
 #pragma unroll
     for (int k = 0; k < DVMAX; ++k)
-        if (C.valid(D, S, k)) store_frames<FPL>(mt + (size_t)C.pkg(D, S, U, k) * Gt, b[k]);
+        if (C.valid(D, S, k)) store_frames<FPL>(mt + (size_t)C.pkg(D, S, U, k) * Gt, a[k]);
 }
 
 template <int DVMAX, int FPL>
@@ -1199,7 +1172,8 @@ __global__ void __launch_bounds__(kBlock) conv_vn_kernel(const ConvDesc D, const
 // conv_vn_kernel does.
 template <int DVMAX, int FPL>
 __global__ void __launch_bounds__(kOutBlock) conv_vn_out_kernel(const ConvDesc D, const ConvSlots S,
-                                                                const ConvUnits U, const ConvParams P, float* post,
+                                                                const ConvUnits U, const ConvParams P,
+                                                                const float* __restrict__ llr, float* post,
                                                                 uint8_t* bits_out, int out_blocks) {
     constexpr int Gt = 64 * FPL;
     __shared__ float Ls[kOutVars][Gt + 1];
@@ -1240,9 +1214,9 @@ __global__ void __launch_bounds__(kOutBlock) conv_vn_out_kernel(const ConvDesc D
     const int64_t oc = (int64_t)U.pos[U.out_unit] * D.c + c0 + var;
     const int nvalid = min(P.gamma - tile * Gt, Gt);
     for (int fr = threadIdx.x / kOutVars; fr < nvalid; fr += kOutBlock / kOutVars) {
-        const float L = Ls[var][fr] * kLn2F;   // base-2 units to an LLR
+        const float L = Ls[var][fr];
         const size_t o = (size_t)(tile * Gt + fr) * ld + oc;
-        post[o] = clip30(L);
+        post[o] = unscale2(L, llr[o]);
         bits_out[o] = (uint8_t)(L < 0.0f);
     }
 }
@@ -1280,7 +1254,7 @@ __global__ void __launch_bounds__(kIngestBlock) conv_ingest_kernel(const ConvDes
         const int t = t0 + pu;
         const int q = rem / D.p, uu = rem - q * D.p;
         const int slot = t % U.ring;
-        const float mu = tileS[tx][r] * kLog2eF;   // base-2 units
+        const float mu = tileS[tx][r] * kLog2eF + 0.0f;   // base-2 units; never -0
         P.mu[((size_t)tile * U.ring * D.c + (size_t)slot * D.c + rem) * Gt + fl] = mu;
         const float b = clip2(mu);
         const int jc = t % D.T;
@@ -1390,7 +1364,7 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                 const int t = in_lo + pu;
                 const int q = rem / D.p, uu = rem - q * D.p;
                 const int slot = t % R;
-                const float m = x[(int64_t)t * D.c + rem] * kLog2eF;   // base-2 units
+                const float m = x[(int64_t)t * D.c + rem] * kLog2eF + 0.0f;   // base-2 units; never -0
                 mu[slot * D.c + rem] = m;
                 const float b = clip2(m);
                 const int jc = t % D.T;
@@ -1456,52 +1430,27 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                 for (int e = 0; e < DCMAX; ++e) any_missing |= o[e];
                 const bool full = any_missing >= 0;
                 if (full) {
-                    float in[DCMAX], t[DCMAX], q[DCMAX], mag[DCMAX];
-                    uint32_t sgn = 0;
+                    float in[DCMAX];
 #pragma unroll
                     for (int e = 0; e < DCMAX; ++e) in[e] = msg[o[e] + so];
+                    check2e_row<DCMAX, 1>(in, DCMAX);
 #pragma unroll
-                    for (int e = 0; e < DCMAX; ++e) {
-                        tq2_of(in[e], t[e], q[e]);
-                        sgn ^= __float_as_uint(in[e]) & 0x80000000u;
-                    }
-                    boxplus2_fb<DCMAX>(t, q, mag);
-#pragma unroll
-                    for (int e = 0; e < DCMAX; ++e) {
-                        const uint32_t sg = sgn ^ (__float_as_uint(in[e]) & 0x80000000u);
-                        msg[o[e] + so] = __uint_as_float(__float_as_uint(mag[e]) | sg);
-                    }
+                    for (int e = 0; e < DCMAX; ++e) msg[o[e] + so] = in[e];
                     return;
                 }
             }
-            float in[DCMAX], t[DCMAX], q[DCMAX];
+            float in[DCMAX];
             int idx[DCMAX];
-            uint32_t sgn = 0;
 #pragma unroll
             for (int e = 0; e < DCMAX; ++e) {
                 const int o = tb[e];
                 idx[e] = o < 0 ? -1 : o + so;
-                in[e] = o < 0 ? 0.0f : msg[o + so];
+                in[e] = o < 0 ? __builtin_inff() : msg[o + so];   // no edge: the identity of the row's products
             }
+            check2e_row<DCMAX, 1>(in, DCMAX);
 #pragma unroll
-            for (int e = 0; e < DCMAX; ++e) {
-                if (idx[e] >= 0) {
-                    tq2_of(in[e], t[e], q[e]);
-                    sgn ^= __float_as_uint(in[e]) & 0x80000000u;
-                } else {
-                    t[e] = 1.0f;
-                    q[e] = 0.0f;
-                }
-            }
-            float mag[DCMAX];
-            boxplus2_fb<DCMAX>(t, q, mag);
-#pragma unroll
-            for (int e = 0; e < DCMAX; ++e) {
-                if (idx[e] >= 0 && u >= cdd[e]) {     // position s + u - dd is not frozen
-                    const uint32_t sg = sgn ^ (__float_as_uint(in[e]) & 0x80000000u);
-                    msg[idx[e]] = __uint_as_float(__float_as_uint(mag[e]) | sg);
-                }
-            }
+            for (int e = 0; e < DCMAX; ++e)
+                if (idx[e] >= 0 && u >= cdd[e]) msg[idx[e]] = in[e];   // position s + u - dd is not frozen
         };
         // variable column (unit u = position s + u, circulant column q,
         // offset uu; rem = q * p + uu); the table holds the edge's ring
@@ -1531,24 +1480,14 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                 if (full) {
 #pragma unroll
                     for (int e = 0; e < DVMAX; ++e) a[e] = msg[idx[e]];
-                    float suf[DVMAX];
-                    float Ssum = 0.0f;
+                    float L = m;
 #pragma unroll
-                    for (int e = DVMAX - 1; e >= 0; --e) {
-                        suf[e] = Ssum;
-                        Ssum += a[e];
-                    }
-                    float pre = 0.0f;
+                    for (int e = 0; e < DVMAX; ++e) L += a[e];
 #pragma unroll
-                    for (int e = 0; e < DVMAX; ++e) {
-                        const float b = clip2(m + (pre + suf[e]));
-                        pre += a[e];
-                        msg[idx[e]] = b;
-                    }
+                    for (int e = 0; e < DVMAX; ++e) msg[idx[e]] = clip2(L - a[e]);
                     if (out && u == 0) {
-                        const float L = (m + pre) * kLn2F;
                         const size_t o = frame_off + (size_t)s * D.c + rem;
-                        post[o] = clip30(L);
+                        post[o] = unscale2(L, llr[o]);
                         bits_out[o] = (uint8_t)(L < 0.0f);
                     }
                     return;
@@ -1562,24 +1501,15 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                 // only messages from window layers (s + u + dd <= lay_hi) are summed
                 a[e] = (o != kNoEdge && u + vdd[e] <= span) ? msg[i] : 0.0f;
             }
-            float suf[DVMAX];
-            float Ssum = 0.0f;
+            float L = m;
 #pragma unroll
-            for (int e = DVMAX - 1; e >= 0; --e) {
-                suf[e] = Ssum;
-                Ssum += a[e];
-            }
-            float pre = 0.0f;
+            for (int e = 0; e < DVMAX; ++e) L += a[e];
 #pragma unroll
-            for (int e = 0; e < DVMAX; ++e) {
-                const float b = clip2(m + (pre + suf[e]));
-                pre += a[e];
-                if (idx[e] >= 0) msg[idx[e]] = b;
-            }
+            for (int e = 0; e < DVMAX; ++e)
+                if (idx[e] >= 0) msg[idx[e]] = clip2(L - a[e]);
             if (out && u == 0) {
-                const float L = (m + pre) * kLn2F;
                 const size_t o = frame_off + (size_t)s * D.c + rem;
-                post[o] = clip30(L);
+                post[o] = unscale2(L, llr[o]);
                 bits_out[o] = (uint8_t)(L < 0.0f);
             }
         };
@@ -1638,25 +1568,17 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                         float a[DVMAX];
 #pragma unroll
                         for (int e = 0; e < DVMAX; ++e) a[e] = vix[j][e] >= 0 ? msg[vix[j][e]] : 0.0f;
-                        float suf[DVMAX];
-                        float Ssum = 0.0f;
+                        float L = m;
 #pragma unroll
-                        for (int e = DVMAX - 1; e >= 0; --e) {
-                            suf[e] = Ssum;
-                            Ssum += a[e];
-                        }
-                        float pre_sum = 0.0f;
+                        for (int e = 0; e < DVMAX; ++e) L += a[e];
 #pragma unroll
                         for (int e = 0; e < DVMAX; ++e) {
-                            const float b = clip2(m + (pre_sum + suf[e]));
-                            pre_sum += a[e];
                             const int v = vix[j][e];
-                            if (v != -1) msg[v >= 0 ? v : -2 - v] = b;
+                            if (v != -1) msg[v >= 0 ? v : -2 - v] = clip2(L - a[e]);
                         }
                         if (k == K && cu0 + j * cstep == 0) {
-                            const float L = (m + pre_sum) * kLn2F;
                             const size_t o = frame_off + (size_t)s * D.c + crem0;
-                            post[o] = clip30(L);
+                            post[o] = unscale2(L, llr[o]);
                             bits_out[o] = (uint8_t)(L < 0.0f);
                         }
                     }
@@ -2249,7 +2171,7 @@ struct ConvRun {
             const int64_t plain_waves = (int64_t)(Pv.rows - D.c) * tl.tiles;
             const unsigned grid = (unsigned)(out_blocks + (plain_waves + kOutBlock / 64 - 1) / (kOutBlock / 64));
             LDPC_DV_SWITCH(dvc, (conv_vn_out_kernel<DV, FPL>
-                                 <<<grid, kOutBlock, 0, st>>>(D, S, U, Pv, post, bits, out_blocks)));
+                                 <<<grid, kOutBlock, 0, st>>>(D, S, U, Pv, llr, post, bits, out_blocks)));
         } else {
             LDPC_DV_SWITCH(dvc, (conv_vn_kernel<DV, FPL>
                                  <<<grid_for_waves((int64_t)Pv.rows * tl.tiles), kBlock, 0, st>>>(D, S, U, Pv)));
@@ -2395,6 +2317,14 @@ static bool window_lds(const ldpc_graph* g, const float* llr, int gamma, int W, 
     return done;
 }
 
+// Whether ldpc_decode_pipeline runs the sweeps of sweep.hip
+// (LDPC_PIPELINE_PATH=launch keeps every code on the ring).
+static bool pipeline_swept(const ldpc_graph* g, int gamma, int iters, SweepPlan& plan) {
+    const char* env = std::getenv("LDPC_PIPELINE_PATH");
+    if (env && std::strcmp(env, "launch") == 0) return false;
+    return sweep_plan(g, gamma, iters, plan);
+}
+
 }  // namespace ldpc
 
 using namespace ldpc;
@@ -2412,6 +2342,8 @@ ldpc_status ldpc_workspace_size(const ldpc_graph* g, int32_t gamma, int32_t max_
     } else if (window == 0) {
         if (max_iters > kMaxUnits) return LDPC_EUNSUPPORTED;
         *bytes = conv_layout(g, tl, pipeline_ring(g, max_iters)).total;
+        SweepPlan plan;
+        if (pipeline_swept(g, gamma, max_iters, plan)) *bytes = std::max(*bytes, plan.bytes);
     } else {
         if (window < g->ms + 1) return LDPC_EINVAL;
         if (window > kMaxUnits) return LDPC_EUNSUPPORTED;
@@ -2649,6 +2581,13 @@ ldpc_status ldpc_decode_pipeline(const ldpc_graph* g, const float* llr, int32_t 
     if (!workspace || workspace_bytes < lay.total) return LDPC_EWORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return LDPC_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    // a workspace that holds the ring only (a caller's own size) gets the ring
+    SweepPlan plan;
+    if (pipeline_swept(g, gamma, iters, plan) && plan.bytes <= workspace_bytes) {
+        (void)hipGetLastError();
+        return sweep_decode(g, plan, llr, gamma, iters, post, bits, workspace, st) &&
+                       hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
+    }
     ConvRun r = make_conv_run(g, llr, gamma, post, bits, reinterpret_cast<char*>(workspace), lay, tl, st);
     (void)hipGetLastError();
     switch (tl.fpl) {
