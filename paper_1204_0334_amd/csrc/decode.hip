@@ -49,6 +49,7 @@
 #include "internal.h"
 #include "onchip.h"
 #include "sweep.h"
+#include "window.h"
 
 namespace ldpc {
 
@@ -2258,10 +2259,10 @@ static void run_pipeline(ConvRun& r, int I) {
 
 // The window decoder with one workgroup per stream and its ring in LDS
 // (window_lds_kernel), when the ring fits the device's LDS per workgroup and
-// the row / column weights have an instantiation; false if the caller must
-// use the launch-per-phase form (nothing enqueued then).
+// the row / column weights have an instantiation; 0 if the caller must
+// use the launch-per-phase form (nothing enqueued then); -1 if a launch failed.
 template <int DC, int DV>
-static bool launch_window_lds(const ldpc_graph* g, const float* llr, int gamma, int W, int K, float* post,
+static int launch_window_lds(const ldpc_graph* g, const float* llr, int gamma, int W, int K, float* post,
                               uint8_t* bits, int R, size_t bytes, hipStream_t st) {
     // bytes: the ring; the edge tables are added here
     bytes += window_lds_tables<DC, DV>(W, g->Jb, g->Lb) * sizeof(int);
@@ -2269,18 +2270,20 @@ static bool launch_window_lds(const ldpc_graph* g, const float* llr, int gamma, 
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return 0;
     }
-    if (bytes + LDPC_MAX_BLOCKS * sizeof(int) > (size_t)limit) return false;
+    if (bytes + LDPC_MAX_BLOCKS * sizeof(int) > (size_t)limit) return 0;
+    // codes it covers keep their messages in registers, others in the ring
+    if (const int r = window_decode(g, llr, gamma, W, K, post, bits, st); r != 0) return r;
     // row and column indices of a window stay below 2^22 (div_small)
     const int wl = std::min(W, g->positions + g->ms);
-    if ((int64_t)wl * std::max(g->Jb, g->Lb) * g->p >= ((int64_t)1 << 22)) return false;
+    if ((int64_t)wl * std::max(g->Jb, g->Lb) * g->p >= ((int64_t)1 << 22)) return 0;
     const bool fix = kWinBlock % (g->Jb * g->p) == 0 && kWinBlock % (g->Lb * g->p) == 0;
     const void* fn = fix ? reinterpret_cast<const void*>(&window_lds_kernel<DC, DV, true>)
                          : reinterpret_cast<const void*>(&window_lds_kernel<DC, DV, false>);
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return 0;
     }
     timing::Scope ts(21, st);
     if (fix)
@@ -2289,20 +2292,20 @@ static bool launch_window_lds(const ldpc_graph* g, const float* llr, int gamma, 
     else
         window_lds_kernel<DC, DV, false><<<(unsigned)gamma, kWinBlock, bytes, st>>>(g->cv, conv_slots(g), R, W, K,
                                                                                     llr, post, bits);
-    return true;
+    return 1;
 }
 
-static bool window_lds(const ldpc_graph* g, const float* llr, int gamma, int W, int K, float* post, uint8_t* bits,
+static int window_lds(const ldpc_graph* g, const float* llr, int gamma, int W, int K, float* post, uint8_t* bits,
                        hipStream_t st) {
     const char* env = std::getenv("LDPC_WINDOW_PATH");
-    if (env && std::strcmp(env, "launch") == 0) return false;
+    if (env && std::strcmp(env, "launch") == 0) return 0;
     const int R = window_ring(g, W);
     const size_t eps = (size_t)(g->ms + 1) * g->Jb * g->Lb * g->p;
     const size_t c = (size_t)g->Lb * g->p;
     const size_t bytes = (size_t)R * (eps + c) * sizeof(float);
     const int dcc = dc_class((g->ms + 1) * g->Lb), dvc = dv_class((g->ms + 1) * g->Jb);
-    if (dcc > 8 || dvc > 4) return false;
-    bool done = false;
+    if (dcc > 8 || dvc > 4) return 0;
+    int done = 0;
     switch (dcc) {
         case 4: LDPC_DV_SWITCH(dvc, if constexpr (DV <= 4) {
                     done = launch_window_lds<4, DV>(g, llr, gamma, W, K, post, bits, R, bytes, st);
@@ -2321,7 +2324,7 @@ static bool window_lds(const ldpc_graph* g, const float* llr, int gamma, int W, 
 // (LDPC_PIPELINE_PATH=launch keeps every code on the ring).
 static bool pipeline_swept(const ldpc_graph* g, int gamma, int iters, SweepPlan& plan) {
     const char* env = std::getenv("LDPC_PIPELINE_PATH");
-    if (env && std::strcmp(env, "launch") == 0) return false;
+    if (env && std::strcmp(env, "launch") == 0) return 0;
     return sweep_plan(g, gamma, iters, plan);
 }
 
@@ -2559,7 +2562,8 @@ ldpc_status ldpc_decode_window(const ldpc_graph* g, const float* llr, int32_t ga
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return LDPC_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     (void)hipGetLastError();
-    if (window_lds(g, llr, gamma, W, iters_per_window, post, bits, st))
+    if (const int r = window_lds(g, llr, gamma, W, iters_per_window, post, bits, st); r < 0) return LDPC_EHIP;
+    else if (r > 0)
         return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
     ConvRun r = make_conv_run(g, llr, gamma, post, bits, reinterpret_cast<char*>(workspace), lay, tl, st);
     switch (tl.fpl) {

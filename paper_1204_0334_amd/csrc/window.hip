@@ -1,0 +1,305 @@
+// Sliding-window decoder with a stream on one compute unit and its messages
+// in registers (gfx950): the codes unwrapped from 3 x 6 bases (period 3, two
+// circulant columns per position, one circulant row per layer).
+//
+// window_lds_kernel of decode.hip, which takes the other codes, keeps every
+// edge message of the window in LDS and passes over them twice per iteration
+// (check rows, then variables).  Here a thread owns a check row of up to NW
+// layers of the window and keeps their check-to-variable messages alpha in
+// registers; LDS holds the posterior sums L of the window's W positions, those
+// of the previous iteration and those being formed.  A variable-to-check
+// message is clip(L - alpha).  Per iteration: every row is updated from the
+// previous sums and starts its own position's new sums (mu + alpha, mu in
+// registers); after a barrier the layers add their messages to the positions
+// one back, after another to those two back, so that the sums are formed in
+// order of the layers (each is met once per step) as in the other forms, with
+// which the results agree bit for bit; a third barrier ends the iteration.
+//
+// A position that leaves the window is frozen: where a later layer meets it,
+// the row's register holds the message beta it last sent in place of alpha
+// (+infinity, the identity of the row's products, where the chain has no such
+// position).
+//
+// The layers are dealt to G groups of threads by their number modulo G, so a
+// layer stays with its thread while the window slides; in a group's registers
+// layers move down by one when its oldest leaves.
+//
+// Bound by the vector ALUs and the latency of a row's chain between two
+// barriers.  p = 512, 128 positions, 512 streams, W = 6, 10 iterations: 7.75
+// ms (1.55 10^12 edge updates per second); 13.0 ms with the messages in LDS
+// and the same check rule, 14.8 ms before that.
+#include <hip/hip_runtime.h>
+
+#include "check2.h"
+#include "device.h"
+#include "internal.h"
+#include "window.h"
+
+namespace ldpc {
+
+constexpr int kWdPeriod = 3, kWdCols = 2, kWdSlots = kWdPeriod * kWdCols;
+
+struct WindowArgs {
+    const float* llr;     // [gamma][positions * c]
+    float* post;
+    uint8_t* bits;
+    int32_t positions, layers, p, W, K;
+    int32_t groups, per;  // groups of threads, threads per group
+    // edge slot k of a layer of class m (index 6 m + k): 4 times the shift
+    // towards position layer - (2 - k / 2), column k % 2
+    uint32_t sh4[kWdPeriod * kWdSlots];
+};
+
+__device__ __forceinline__ float* wd_at(float* base, uint32_t byte) {
+    return reinterpret_cast<float*>(reinterpret_cast<char*>(base) + byte);
+}
+
+template <int NW, int MAXT, int WPE>
+__global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
+    constexpr int T = kWdPeriod, LB = kWdCols, DC = kWdSlots, MS = T - 1;
+    extern __shared__ float sums[];   // [2][W][LB][p]
+    const int p = A.p, P = A.positions, W = A.W;
+    const uint32_t p4 = 4u * (uint32_t)p, c4 = LB * p4, other = (uint32_t)W * c4;
+    const int g = __builtin_amdgcn_readfirstlane((int)threadIdx.x / A.per);
+    const uint32_t s4 = 4u * (threadIdx.x - (uint32_t)(g * A.per));
+    const bool own = s4 < p4;
+    const size_t frame = (size_t)blockIdx.x * P * LB * p;
+    const float* __restrict__ mu = A.llr + frame;
+
+    float al[NW][DC];            // alpha, or the beta of a frozen (+inf: missing) position
+    uint32_t offs[NW][DC / 2];   // offsets of the edges' variables in their positions, two to a register
+    float m0[NW][LB];            // channel LLRs that the newest position's sums start from
+    auto off = [&](int j, int k) -> uint32_t { return k % 2 ? offs[j][k / 2] >> 16 : offs[j][k / 2] & 0xffffu; };
+    auto open_layer = [&](int j, int tau) {
+        const int cls = tau % T;
+#pragma unroll
+        for (int k = 0; k < DC; ++k) {
+            const uint32_t w = s4 + A.sh4[cls * DC + k];
+            const uint32_t o = (uint32_t)(k % LB) * p4 + min(w, w - p4);
+            if (k % 2 == 0)
+                offs[j][k / 2] = o;
+            else
+                offs[j][k / 2] |= o << 16;
+            const int pos = tau - (MS - k / LB);
+            al[j][k] = (uint32_t)pos < (uint32_t)P ? 0.0f : __builtin_inff();
+        }
+        if (tau < P) {
+#pragma unroll
+            for (int q = 0; q < LB; ++q)
+                m0[j][q] = mu[(size_t)tau * (LB * p) + (off(j, MS * LB + q) >> 2)] * kLog2eF + 0.0f;
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+#pragma unroll
+        for (int k = 0; k < DC; ++k) al[j][k] = 0.0f;
+#pragma unroll
+        for (int k = 0; k < DC / 2; ++k) offs[j][k] = 0u;
+#pragma unroll
+        for (int q = 0; q < LB; ++q) m0[j][q] = 0.0f;
+        if (own) open_layer(j, g + j * A.groups);
+    }
+    for (int i = threadIdx.x; i < min(W, P) * LB * p; i += blockDim.x) sums[i] = mu[i] * kLog2eF + 0.0f;
+    __syncthreads();
+
+    uint32_t cur = 0;    // LDS offset of the current sums
+    int sW = 0;          // s mod W
+    int w0 = g;          // the group's oldest layer is s + w0
+    for (int s = 0; s < P; ++s) {
+        // ring offset of position s + w, -MS <= w < W
+        auto slot = [&](int w) -> uint32_t {
+            int r = sW + w;
+            r = r < 0 ? r + W : r;
+            return (uint32_t)(r >= W ? r - W : r) * c4;
+        };
+        auto live = [&](int w) { return w < W && s + w < A.layers; };                // layer s + w is in the window
+        auto active = [&](int w, int dd) { return w >= dd && s + w - dd < P; };      // and meets position s + w - dd
+        for (int it = 0; it < A.K; ++it) {
+            const uint32_t old = cur, fresh = other - cur;
+            if (own) {
+#pragma unroll
+                for (int j = 0; j < NW; ++j) {
+                    const int w = w0 + j * A.groups;
+                    if (!live(w)) continue;
+                    float x[DC];
+                    if (w >= MS && s + w < P) {
+#pragma unroll
+                        for (int dd = MS; dd >= 0; --dd) {
+                            const uint32_t base = old + slot(w - dd);
+#pragma unroll
+                            for (int q = 0; q < LB; ++q) {
+                                const int k = (MS - dd) * LB + q;
+                                x[k] = *wd_at(sums, base + off(j, k));
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < DC; ++k) al[j][k] = clip2(x[k] - al[j][k]);
+                        check2e_row<DC, 1>(al[j], DC);
+                    } else {
+#pragma unroll
+                        for (int dd = MS; dd >= 0; --dd) {
+#pragma unroll
+                            for (int q = 0; q < LB; ++q) {
+                                const int k = (MS - dd) * LB + q;
+                                x[k] = active(w, dd) ? clip2(*wd_at(sums, old + slot(w - dd) + off(j, k)) - al[j][k])
+                                                     : al[j][k];
+                            }
+                        }
+                        check2e_row<DC, 1>(x, DC);
+#pragma unroll
+                        for (int k = 0; k < DC; ++k)
+                            if (active(w, MS - k / LB)) al[j][k] = x[k];
+                    }
+                    if (s + w < P) {
+                        const uint32_t base = fresh + slot(w);
+#pragma unroll
+                        for (int q = 0; q < LB; ++q)
+                            *wd_at(sums, base + off(j, MS * LB + q)) = m0[j][q] + al[j][MS * LB + q];
+                    }
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int dd = 1; dd <= MS; ++dd) {
+                if (own) {
+                    float v[NW][LB];
+#pragma unroll
+                    for (int j = 0; j < NW; ++j) {
+                        const int w = w0 + j * A.groups;
+                        if (!live(w) || !active(w, dd)) continue;
+#pragma unroll
+                        for (int q = 0; q < LB; ++q)
+                            v[j][q] = *wd_at(sums, fresh + slot(w - dd) + off(j, (MS - dd) * LB + q));
+                    }
+#pragma unroll
+                    for (int j = 0; j < NW; ++j) {
+                        const int w = w0 + j * A.groups;
+                        if (!live(w) || !active(w, dd)) continue;
+#pragma unroll
+                        for (int q = 0; q < LB; ++q) {
+                            const int k = (MS - dd) * LB + q;
+                            *wd_at(sums, fresh + slot(w - dd) + off(j, k)) = v[j][q] + al[j][k];
+                        }
+                    }
+                }
+                __syncthreads();
+            }
+            cur = fresh;
+        }
+        // position s is decided and freezes: the layers that meet it from now on keep the beta it last sent
+        {
+            const uint32_t base = cur + slot(0);
+            const size_t v0 = (size_t)s * (LB * p);
+            for (int i = threadIdx.x; i < LB * p; i += blockDim.x) {
+                const float L = *wd_at(sums, base + 4u * (uint32_t)i);
+                A.post[frame + v0 + i] = unscale2(L, mu[v0 + i]);
+                A.bits[frame + v0 + i] = (uint8_t)(L < 0.0f);
+            }
+            if (own) {
+#pragma unroll
+                for (int j = 0; j < NW; ++j) {
+                    const int w = w0 + j * A.groups;
+                    if (!live(w)) continue;
+#pragma unroll
+                    for (int dd = 1; dd <= MS; ++dd) {
+                        if (w != dd) continue;
+#pragma unroll
+                        for (int q = 0; q < LB; ++q) {
+                            const int k = (MS - dd) * LB + q;
+                            al[j][k] = clip2(*wd_at(sums, base + off(j, k)) - al[j][k]);
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        // position s + W enters with its channel LLRs; layer s leaves, layer s + W enters
+        if (s + W < P) {
+            const uint32_t base = cur + slot(0);
+            const size_t v0 = (size_t)(s + W) * (LB * p);
+            for (int i = threadIdx.x; i < LB * p; i += blockDim.x)
+                *wd_at(sums, base + 4u * (uint32_t)i) = mu[v0 + i] * kLog2eF + 0.0f;
+        }
+        if (w0 == 0) {
+            w0 = A.groups - 1;
+#pragma unroll
+            for (int j = 0; j + 1 < NW; ++j) {
+#pragma unroll
+                for (int k = 0; k < DC; ++k) al[j][k] = al[j + 1][k];
+#pragma unroll
+                for (int k = 0; k < DC / 2; ++k) offs[j][k] = offs[j + 1][k];
+#pragma unroll
+                for (int q = 0; q < LB; ++q) m0[j][q] = m0[j + 1][q];
+            }
+            if (own) open_layer(NW - 1, s + NW * A.groups);
+        } else {
+            --w0;
+        }
+        sW = sW + 1 == W ? 0 : sW + 1;
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+
+int window_decode(const ldpc_graph* g, const float* llr, int gamma, int W, int K, float* post, uint8_t* bits,
+                  hipStream_t st) {
+    if (g->Jb != 1 || g->T != kWdPeriod || g->ms + 1 != g->T || g->Lb != kWdCols) return 0;
+    for (int v : g->sf)
+        if (v < 0) return 0;
+    const int per = (g->p + 63) / 64 * 64;
+    // Layers per thread: the fewest that 1024 threads can hold the window with
+    // (rows of one thread are updated one after the other).  W = 6, 10
+    // iterations: p = 52, 128 streams, 1, 2, 3 or 6 layers: 153, 231, 315, 592
+    // us; p = 512, 256 streams, 3 or 6: 4.52 and 5.80 ms.
+    int nw = 0;
+    for (int n : {6, 3, 2, 1})
+        if ((W + n - 1) / n * per <= 1024) nw = n;
+    if (nw == 0) return 0;
+    const int groups = (W + nw - 1) / nw;
+    const size_t lds = 2 * (size_t)W * kWdCols * g->p * sizeof(float);
+    int dev = 0, limit = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    if (lds > (size_t)limit) return 0;
+    WindowArgs A{};
+    A.llr = llr;
+    A.post = post;
+    A.bits = bits;
+    A.positions = g->positions;
+    A.layers = g->layers;
+    A.p = g->p;
+    A.W = W;
+    A.K = K;
+    A.groups = groups;
+    A.per = per;
+    for (int m = 0; m < kWdPeriod; ++m)
+        for (int k = 0; k < kWdSlots; ++k)
+            A.sh4[m * kWdSlots + k] =
+                4u * (uint32_t)g->sf[(m * kWdPeriod + (g->ms - k / kWdCols)) * kWdCols + k % kWdCols];
+    // With more streams than compute units, 64 registers, so that two
+    // workgroups of 1024 threads share one (p = 512, 512 streams: 7.75 ms
+    // against 9.05; 256 streams: 4.60 against 4.52).
+    const bool two = gamma > 256;
+    const void* fn = nw == 1 ? reinterpret_cast<const void*>(&window_kernel<1, 1024, 8>)
+                     : nw == 2 ? (two ? reinterpret_cast<const void*>(&window_kernel<2, 1024, 8>)
+                                      : reinterpret_cast<const void*>(&window_kernel<2, 1024, 4>))
+                     : nw == 3 ? (two ? reinterpret_cast<const void*>(&window_kernel<3, 1024, 8>)
+                                      : reinterpret_cast<const void*>(&window_kernel<3, 1024, 4>))
+                               : reinterpret_cast<const void*>(&window_kernel<6, 1024, 4>);
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    timing::Scope ts(21, st);
+    void* args[] = {&A};
+    return hipLaunchKernel(fn, dim3((unsigned)gamma), dim3((unsigned)(groups * per)), args, lds, st) == hipSuccess ? 1
+                                                                                                                   : -1;
+}
+
+}  // namespace ldpc
