@@ -217,36 +217,47 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
     const int TB = blockDim.x;
     const size_t f0 = (size_t)blockIdx.x * n;
     const float* __restrict__ mu = A.llr + f0;
+    const uint32_t p8 = 8u * (uint32_t)p, TB8 = 8u * (uint32_t)TB;
+    float mu0[NQ][DC];
     // L of "iteration 0" is mu, so that iteration 1 reads beta = clip(mu - 0)
     if constexpr (oc_mu_in_regs(REG, DC)) {
-        // rotated columns (pair l p + u holds variable l p + (u + a_0l) mod p)
-        for (int l = 0; l < DC; ++l) {
-            const int rot = A.rot8[l] >> 3;
-            for (int u = tid; u < p; u += TB) {
-                int t = u + rot;
-                t = t >= p ? t - p : t;
-                Lpair[l * p + u].x = mu[l * p + t] * kLog2eF + 0.0f;
+        // rotated columns (pair l p + u holds variable l p + (u + a_0l) mod p):
+        // the pairs a thread fills are those its rows of base row 0 meet (slot
+        // l of a full base row 0 is column l's)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+#pragma unroll
+            for (int l = 0; l < DC; ++l) {
+                mu0[q][l] = 0.0f;
+                if (s8 < p8)
+                    mu0[q][l] = *reinterpret_cast<const float*>(
+                                    reinterpret_cast<const char*>(mu) +
+                                    ((A.cb8[l] + oc_wrap8(s8 + A.rot8[l], p8)) >> 1)) * kLog2eF + 0.0f;
             }
         }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+#pragma unroll
+            for (int l = 0; l < DC; ++l)
+                if (s8 < p8) *lds_ptr(Lpair, A.cb8[l] + s8) = mu0[q][l];
+        }
     } else {
-        for (int v = tid; v < n; v += TB) Lpair[v].x = mu[v] * kLog2eF + 0.0f;
-    }
-    if (tid < 3) flag[tid] = 0u;
-    const uint32_t p8 = 8u * (uint32_t)p, TB8 = 8u * (uint32_t)TB;
-    float al[NJ][NQ][DC];
-    float mu0[NQ][DC];
+        if constexpr (REG) {   // a full base has DC columns: their loads go out together
+            for (int u = tid; u < p; u += TB) {
+                float m[DC];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+                for (int l = 0; l < DC; ++l) m[l] = mu[l * p + u];
 #pragma unroll
-        for (int k = 0; k < DC; ++k) {
-            mu0[q][k] = 0.0f;
-            if (oc_mu_in_regs(REG, DC) && s8 < p8)
-                mu0[q][k] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(mu) +
-                                                            ((A.cb8[k] + oc_wrap8(s8 + A.rot8[k], p8)) >> 1)) *
-                            kLog2eF + 0.0f;
+                for (int l = 0; l < DC; ++l) Lpair[l * p + u].x = m[l] * kLog2eF + 0.0f;
+            }
+        } else {
+            for (int v = tid; v < n; v += TB) Lpair[v].x = mu[v] * kLog2eF + 0.0f;
         }
     }
+    if (tid < 3) flag[tid] = 0u;
+    float al[NJ][NQ][DC];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -328,22 +339,42 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
         iters_out = last;
         conv_out = flag[fw] == 0u ? 1 : 0;
     }
-    auto put = [&](int v, int pair) {
-        const float x = Lf[2 * pair + comp];
-        A.post[f0 + v] = unscale2(x, mu[v]);
-        A.bits[f0 + v] = (uint8_t)(x < 0.0f);
-    };
     if constexpr (oc_mu_in_regs(REG, DC)) {
-        for (int l = 0; l < DC; ++l) {
-            const int rot = A.rot8[l] >> 3;
-            for (int u = tid; u < p; u += TB) {
-                int t = u + rot;
-                t = t >= p ? t - p : t;
-                put(l * p + t, l * p + u);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+            if (s8 >= p8) continue;
+            uint32_t v[DC];
+            float m[DC];
+#pragma unroll
+            for (int l = 0; l < DC; ++l) {
+                v[l] = (A.cb8[l] + oc_wrap8(s8 + A.rot8[l], p8)) >> 3;
+                m[l] = mu[v[l]];
+            }
+#pragma unroll
+            for (int l = 0; l < DC; ++l) {
+                const float x = lds_at(Lpair, A.cb8[l] + s8 + 4u * (uint32_t)comp);
+                A.post[f0 + v[l]] = unscale2(x, m[l]);
+                A.bits[f0 + v[l]] = (uint8_t)(x < 0.0f);
             }
         }
     } else {
-        for (int v = tid; v < n; v += TB) put(v, v);
+        auto put = [&](int v, float m) {
+            const float x = Lf[2 * v + comp];
+            A.post[f0 + v] = unscale2(x, m);
+            A.bits[f0 + v] = (uint8_t)(x < 0.0f);
+        };
+        if constexpr (REG) {
+            for (int u = tid; u < p; u += TB) {
+                float m[DC];
+#pragma unroll
+                for (int l = 0; l < DC; ++l) m[l] = mu[l * p + u];
+#pragma unroll
+                for (int l = 0; l < DC; ++l) put(l * p + u, m[l]);
+            }
+        } else {
+            for (int v = tid; v < n; v += TB) put(v, mu[v]);
+        }
     }
     if (tid == 0) {
         if (A.iters) A.iters[blockIdx.x] = iters_out;

@@ -50,12 +50,11 @@ constexpr int kOwPad = 64;     // further cells behind each column
 constexpr int kOwMinP = 64;    // a further cell repeats a cell of its own column
 
 // Edge slot k of base row j (index j * kOwSlots + k): row (j, s) meets
-// variable (l, (s + a) mod p) of its base column l.  Byte offsets.
+// variable (k, (s + a) mod p) of base column k.  Byte offsets.
 struct WideEdge {
     uint32_t sh4;     // 4 a
-    uint32_t cb4;     // 4 l (p + kOwPad): the column's first cell
-    uint32_t gb4;     // 4 l p: the column's first channel LLR
-    uint32_t first;   // 1: the lowest nonzero block of its base column
+    uint32_t cb4;     // 4 k (p + kOwPad): the column's first cell
+    uint32_t gb4;     // 4 k p: the column's first channel LLR
 };
 
 struct WideArgs {
@@ -67,7 +66,6 @@ struct WideArgs {
     uint8_t* conv;                    // [gamma] or NULL
     const float* nms_w;               // learned min-sum (RULE 1): [iters][blocks][2]
     int32_t n, p, L, max_iters, nb;
-    int32_t deg[kOwRows];             // nonzero blocks of base row j
     int32_t rb0[kOwRows];             // first block of base row j
 };
 
@@ -76,10 +74,10 @@ __device__ __forceinline__ float* ow_cell(float* L, uint32_t byte) {
 }
 
 // One frame per workgroup.  NJ base rows, NQ rows per thread and base row, DC
-// slots per row, REG: every base row has DC nonzero blocks; RULE 0:
+// slots per row (the base is full: DC columns, DC blocks in every row); RULE 0:
 // sum-product, 1: learned min-sum; NB: blocks of check2e_row; MAXT: threads
 // the register budget is for; EARLY: with early stopping.
-template <int NJ, int NQ, int DC, bool REG, int RULE, int NB, int MAXT, bool EARLY>
+template <int NJ, int NQ, int DC, int RULE, int NB, int MAXT, bool EARLY>
 __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
     // dynamic LDS: L columns of p + kOwPad sums, then two flag words
     extern __shared__ float cells[];
@@ -92,9 +90,19 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
     const char* __restrict__ mu = reinterpret_cast<const char*>(A.llr + f0);
     const uint32_t p4 = 4u * (uint32_t)p, lane4 = 4u * (uint32_t)(tid & 63);
     // L of "iteration 0" is mu, so that iteration 1 reads beta = clip(mu - 0)
-    for (int l = 0; l < nl; ++l)
-        for (int t = tid; t < stride; t += TB)
-            cells[l * stride + t] = A.llr[f0 + (size_t)l * p + (t < p ? t : t - p)] * kLog2eF + 0.0f;
+    // (a full base has DC columns; a group of columns' loads go out together)
+    constexpr int G = DC % 8 == 0 ? 8 : 9;
+    for (int t = tid; t < stride; t += TB) {
+        const float* at = A.llr + f0 + (t < p ? t : t - p);
+#pragma unroll 1
+        for (int l0 = 0; l0 < DC; l0 += G) {
+            float m[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) m[i] = at[(size_t)(l0 + i) * p];
+#pragma unroll
+            for (int i = 0; i < G; ++i) cells[(l0 + i) * stride + t] = m[i] * kLog2eF + 0.0f;
+        }
+    }
     if (tid < 2) flag[tid] = 0u;
     float al[NJ][NQ][DC];
 #pragma unroll
@@ -135,7 +143,6 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
         uint64_t viol = 0;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int d = REG ? DC : A.deg[j];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 if (tid4 + 4u * (uint32_t)(q * TB) < p4) {
@@ -143,20 +150,16 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
                     uint32_t sx = 0;
 #pragma unroll
                     for (int k = 0; k < DC; ++k) {
-                        if (REG || k < d) {
-                            const float L = *ow_cell(cells, first_cell(j, q, k) + lane4);
-                            // the row's parity in bit 31 (a sum is never -0: it starts from mu + 0)
-                            if (EARLY) sx ^= __float_as_uint(L);
-                            x[k] = clip2(L - x[k]);
-                        } else {
-                            x[k] = 0.0f;
-                        }
+                        const float L = *ow_cell(cells, first_cell(j, q, k) + lane4);
+                        // the row's parity in bit 31 (a sum is never -0: it starts from mu + 0)
+                        if (EARLY) sx ^= __float_as_uint(L);
+                        x[k] = clip2(L - x[k]);
                     }
                     if (EARLY) viol |= __ballot((int32_t)sx < 0);
                     if constexpr (RULE == 0)
-                        check2e_row<DC, NB>(x, d);
+                        check2e_row<DC, NB>(x, DC);
                     else
-                        nms2_row<DC>(x, d, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
+                        nms2_row<DC>(x, DC, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
                 }
             }
         }
@@ -174,7 +177,6 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
         for (int i = tid; i < nl * kOwPad; i += TB) cells[(i / kOwPad) * stride + p + i % kOwPad] = 0.0f;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int d = REG ? DC : A.deg[j];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 if (tid4 + 4u * (uint32_t)(q * TB) < p4) {
@@ -188,9 +190,8 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
 #pragma unroll
                         for (int i = 0; i < B; ++i) {
                             const int k = k0 + i, jk = j * kOwSlots + k;
-                            if (!(REG || k < d)) continue;
                             at[i] = first_cell(j, q, k) + lane4;
-                            if (REG ? j == 0 : A.e[jk].first != 0u) {
+                            if (j == 0) {
                                 // the sum starts from mu, in the variable's own cell
                                 uint32_t t = at[i] - A.e[jk].cb4;
                                 t = min(t, t - p4);
@@ -202,7 +203,7 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
                         }
 #pragma unroll
                         for (int i = 0; i < B; ++i)
-                            if (REG || k0 + i < d) *ow_cell(cells, at[i]) = v[i] + al[j][q][k0 + i];
+                            *ow_cell(cells, at[i]) = v[i] + al[j][q][k0 + i];
                     }
                 }
             }
@@ -228,12 +229,11 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
         const int fw = EARLY ? (A.max_iters + 1) & 1 : 0;
         uint64_t viol = 0;
         for (int j = 0; j < NJ; ++j) {
-            const int d = REG ? DC : A.deg[j];
             for (int q = 0; q < NQ; ++q) {
                 const uint32_t s4 = w4 + 4u * (uint32_t)(q * TB);
                 if (s4 + lane4 < p4) {
                     uint32_t sx = 0;
-                    for (int k = 0; k < d; ++k) {
+                    for (int k = 0; k < DC; ++k) {
                         const WideEdge& e = A.e[j * kOwSlots + k];
                         const uint32_t t = s4 + e.sh4;
                         sx ^= __float_as_uint(*ow_cell(cells, e.cb4 + min(t, t - p4) + lane4));
@@ -247,12 +247,19 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
         iters_out = A.max_iters;
         conv_out = flag[fw] == 0u ? 1 : 0;
     }
-    for (int l = 0; l < nl; ++l)
-        for (int t = tid; t < p; t += TB) {
-            const float L = cells[l * stride + t];
-            const size_t v = f0 + (size_t)l * p + t;
-            A.post[v] = unscale2(L, A.llr[v]);
-            A.bits[v] = (uint8_t)(L < 0.0f);
+    for (int t = tid; t < p; t += TB)
+#pragma unroll 1
+        for (int l0 = 0; l0 < DC; l0 += G) {
+            float m[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) m[i] = A.llr[f0 + (size_t)(l0 + i) * p + t];
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const float L = cells[(l0 + i) * stride + t];
+                const size_t v = f0 + (size_t)(l0 + i) * p + t;
+                A.post[v] = unscale2(L, m[i]);
+                A.bits[v] = (uint8_t)(L < 0.0f);
+            }
         }
     if (tid == 0) {
         if (A.iters) A.iters[blockIdx.x] = iters_out;
@@ -267,27 +274,25 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
 namespace {
 
 struct WideVariant {
-    int nj, nq, dc;
-    bool reg;
-    int rule, maxt;
+    int nj, nq, dc, rule, maxt;
     const void* fn;         // without early stopping
     const void* fn_early;   // with early stopping
 };
 
-template <int NJ, int NQ, int DC, bool REG, int RULE, int NB, int MAXT>
+template <int NJ, int NQ, int DC, int RULE, int NB, int MAXT>
 constexpr WideVariant wide() {
-    return WideVariant{NJ, NQ, DC, REG, RULE, MAXT,
-                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, REG, RULE, NB, MAXT, false>),
-                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, REG, RULE, NB, MAXT, true>)};
+    return WideVariant{NJ, NQ, DC, RULE, MAXT,
+                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, RULE, NB, MAXT, false>),
+                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, RULE, NB, MAXT, true>)};
 }
 
 const WideVariant kWide[] = {
-    wide<4, 1, 24, true, 0, 3, 1024>(),
-    wide<3, 1, 18, true, 0, 2, 1024>(), wide<3, 2, 18, true, 0, 2, 768>(),
-    wide<3, 3, 9, true, 0, 1, 1024>(),
-    wide<4, 1, 24, true, 1, 2, 1024>(),
-    wide<3, 1, 18, true, 1, 2, 1024>(), wide<3, 2, 18, true, 1, 2, 768>(),
-    wide<3, 3, 9, true, 1, 1, 1024>(),
+    wide<4, 1, 24, 0, 3, 1024>(),
+    wide<3, 1, 18, 0, 2, 1024>(), wide<3, 2, 18, 0, 2, 768>(),
+    wide<3, 3, 9, 0, 1, 1024>(),
+    wide<4, 1, 24, 1, 2, 1024>(),
+    wide<3, 1, 18, 1, 2, 1024>(), wide<3, 2, 18, 1, 2, 768>(),
+    wide<3, 3, 9, 1, 1, 1024>(),
 };
 
 // Which codes: regular bases with a base row that fills a wavefront at least
@@ -305,10 +310,8 @@ bool choose_wide(const ldpc_graph* g, int rule, WideChoice& c) {
     if (!g || g->kind != LDPC_GRAPH_QC) return false;
     const QCDesc& D = g->qc;
     if (D.J > kOwRows || D.dc_max > kOwSlots || D.p < kOwMinP) return false;
-    for (int l = 0; l < D.L; ++l)
-        if (D.cstart[l + 1] == D.cstart[l]) return false;   // a base column without edges
-    bool reg = D.rstart[1] - D.rstart[0] == D.L;
-    for (int j = 0; j < D.J; ++j) reg = reg && (D.rstart[j + 1] - D.rstart[j] == D.dc_max);
+    for (int j = 0; j < D.J; ++j)
+        if (D.rstart[j + 1] - D.rstart[j] != D.L) return false;   // a zero block
     int dev = 0, limit = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) {
@@ -318,7 +321,7 @@ bool choose_wide(const ldpc_graph* g, int rule, WideChoice& c) {
     const size_t lds = ((size_t)D.L * (D.p + kOwPad) + 2) * sizeof(float);
     if (lds > (size_t)limit) return false;
     for (const WideVariant& v : kWide) {
-        if (v.rule != rule || v.nj != D.J || v.dc != D.dc_max || !reg) continue;
+        if (v.rule != rule || v.nj != D.J || v.dc != D.dc_max) continue;
         const int per = (D.p + v.nq - 1) / v.nq;
         const int tb = (per + 63) / 64 * 64;
         if (tb > v.maxt) continue;
@@ -355,15 +358,13 @@ int onchip_wide_decode(const ldpc_graph* g, const float* llr, int gamma, int max
     A.max_iters = max_iters;
     A.nb = D.nb;
     for (int j = 0; j < D.J; ++j) {
-        A.deg[j] = D.rstart[j + 1] - D.rstart[j];
         A.rb0[j] = D.rstart[j];
-        for (int k = 0; k < A.deg[j]; ++k) {
+        for (int k = 0; k < D.dc_max; ++k) {
             const int b = D.rstart[j] + k, l = D.ecol[b];
             WideEdge& e = A.e[j * kOwSlots + k];
             e.sh4 = 4u * (uint32_t)D.eshift[b];
             e.cb4 = 4u * (uint32_t)(l * (D.p + kOwPad));
             e.gb4 = 4u * (uint32_t)(l * D.p);
-            e.first = D.cedge[D.cstart[l]] == b ? 1u : 0u;   // edge blocks of a column ascend by base row
         }
     }
     const void* fn = early ? c.v->fn_early : c.v->fn;
