@@ -49,6 +49,7 @@
 #include "internal.h"
 #include "onchip.h"
 #include "sweep.h"
+#include "train.h"
 #include "window.h"
 
 namespace ldpc {
@@ -2332,6 +2333,20 @@ static bool pipeline_swept(const ldpc_graph* g, int gamma, int iters, SweepPlan&
 
 using namespace ldpc;
 
+// Whether a training step runs with each frame on one compute unit (train.hip):
+// the code is covered and the step's workspace fits what the message packages
+// take, whatever the checkpoint interval, so that neither the workspace nor
+// the gradient depends on it.
+static bool trained_onchip(const ldpc_graph* g, const Tiling& tl, int gamma, int T) {
+    const size_t need = train_onchip_bytes(g, gamma, T);
+    if (need == 0) return false;
+    // the smallest total lies near k = sqrt(T / 2)
+    const int most = std::min(T, 64);
+    for (int k = 1; k <= most; ++k)
+        if (train_layout(g, tl, T, k).total < need) return false;
+    return true;
+}
+
 extern "C" {
 
 ldpc_status ldpc_workspace_size(const ldpc_graph* g, int32_t gamma, int32_t max_iters, int32_t window,
@@ -2515,8 +2530,10 @@ ldpc_status ldpc_nms_train_forward(const ldpc_graph* g, const float* llr, int32_
     if (!workspace || workspace_bytes < lay.total) return LDPC_EWORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return LDPC_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    TrainRun r = make_train_run(g, gamma, iters, ckpt_every, weights, reinterpret_cast<char*>(workspace), tl, st);
     (void)hipGetLastError();
+    if (trained_onchip(g, tl, gamma, iters))
+        return train_onchip_forward(g, llr, gamma, iters, weights, loss, workspace, st) ? LDPC_OK : LDPC_EHIP;
+    TrainRun r = make_train_run(g, gamma, iters, ckpt_every, weights, reinterpret_cast<char*>(workspace), tl, st);
     switch (tl.fpl) {
         case 4: train_forward<4>(r, llr, loss); break;
         case 2: train_forward<2>(r, llr, loss); break;
@@ -2539,8 +2556,10 @@ ldpc_status ldpc_nms_train_backward(const ldpc_graph* g, int32_t gamma, int32_t 
     if (!workspace || workspace_bytes < lay.total) return LDPC_EWORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255) return LDPC_EINVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    TrainRun r = make_train_run(g, gamma, iters, ckpt_every, weights, reinterpret_cast<char*>(workspace), tl, st);
     (void)hipGetLastError();
+    if (trained_onchip(g, tl, gamma, iters))
+        return train_onchip_backward(g, gamma, iters, weights, dloss, grad, workspace, st) ? LDPC_OK : LDPC_EHIP;
+    TrainRun r = make_train_run(g, gamma, iters, ckpt_every, weights, reinterpret_cast<char*>(workspace), tl, st);
     switch (tl.fpl) {
         case 4: train_backward<4>(r, dloss, grad); break;
         case 2: train_backward<2>(r, dloss, grad); break;
