@@ -178,7 +178,12 @@ __device__ __forceinline__ void nms2_row(const float (&in)[DC], int d, const flo
         if (k < d) {
             const float m = fabsf(in[k]) == min1 ? min2 : min1;
             const float v = fmaxf(m - w[2 * k + 1] * kLog2eF, 0.0f);
-            out[k] = w[2 * k] * __builtin_copysignf(v, __uint_as_float(sgn << (32 - DC + k)));
+            // rounded before it is added to a sum: the sums are the same whether a
+            // message comes from a register or from another compute unit
+            {
+#pragma clang fp contract(off)
+                out[k] = w[2 * k] * __builtin_copysignf(v, __uint_as_float(sgn << (32 - DC + k)));
+            }
         }
     }
 }

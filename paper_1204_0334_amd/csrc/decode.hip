@@ -48,6 +48,7 @@
 #include "device.h"
 #include "internal.h"
 #include "onchip.h"
+#include "spread.h"
 #include "sweep.h"
 #include "train.h"
 #include "window.h"
@@ -2392,9 +2393,13 @@ static ldpc_status decode_block(const ldpc_graph* g, const float* llr, int32_t g
     (void)hipGetLastError();
     // decodes of codes that fit one compute unit run on chip (onchip.hip),
     // sum-product and learned min-sum alike; LDPC_BLOCK_PATH=packages keeps
-    // them on this decoder
+    // them on this decoder, =onchip each frame on one unit
     if (!packages_forced()) {
-        const int r = onchip_decode(g, llr, gamma, max_iters, early_stop ? 1 : 0, post, bits, iters, converged, st,
+        // a frame on several compute units where few frames leave them idle
+        int r = spread_decode(g, llr, gamma, max_iters, early_stop ? 1 : 0, post, bits, iters, converged, ws,
+                              lay.total, st, nms_w);
+        if (r == 0)
+            r = onchip_decode(g, llr, gamma, max_iters, early_stop ? 1 : 0, post, bits, iters, converged, st,
                                     nms_w);
         if (r != 0) return r > 0 && hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
     }

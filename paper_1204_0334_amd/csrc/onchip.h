@@ -19,6 +19,9 @@ bool onchip_fits(const ldpc_graph* g);
 // variable LDPC_BLOCK_PATH is not "packages" (the rule ldpc_decode applies).
 bool onchip_selected(const ldpc_graph* g);
 
+// Whether that is the kernel with a pair of sums per variable (onchip.hip).
+bool onchip_pairs(const ldpc_graph* g);
+
 // Enqueues the whole decode (arguments as ldpc_decode; outputs written
 // directly in the caller's layout; nms_w: NULL for sum-product, else the
 // learned min-sum weights of ldpc_nms_decode).  Returns 1 once launched, 0

@@ -476,6 +476,11 @@ bool onchip_fits(const ldpc_graph* g) {
     return choose(g, 0, c) || onchip_wide_fits(g);
 }
 
+bool onchip_pairs(const ldpc_graph* g) {
+    Choice c;
+    return choose(g, 0, c);
+}
+
 bool onchip_selected(const ldpc_graph* g) {
     const char* path = std::getenv("LDPC_BLOCK_PATH");
     if (path && std::strcmp(path, "packages") == 0) return false;

@@ -1,0 +1,22 @@
+// Block decoder with a frame on several compute units (spread.hip), for
+// batches that would leave most of the chip idle.  Called by ldpc_decode
+// before the one-unit decoder of onchip.hip, whose results it returns bit for
+// bit.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+#include <stdint.h>
+
+#include "internal.h"
+
+namespace ldpc {
+
+// Enqueues the whole decode (arguments as ldpc_decode, nms_w as
+// ldpc_nms_decode's weights or NULL) in the workspace of ws_bytes.  Returns 1
+// once launched, 0 (having enqueued nothing) when the rule does not choose
+// it, -1 when a launch failed.
+int spread_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
+                  uint8_t* bits, int32_t* iters, uint8_t* converged, void* ws, size_t ws_bytes, hipStream_t st,
+                  const float* nms_w);
+
+}  // namespace ldpc

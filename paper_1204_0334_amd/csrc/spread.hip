@@ -1,0 +1,367 @@
+// Block decoder with a frame spread over several compute units (gfx950), for
+// full bases of 3 rows of weight 6 or 9.
+//
+// On one compute unit (onchip.hip) an iteration of a long code is bound by
+// that unit's vector ALUs: 8 us for 3 x 6, p = 3060, with 255 of 256 units
+// idle when there is one frame.  Here C workgroups share a frame: member c
+// owns the check rows (j, s), c TB <= s < (c + 1) TB, one offset s per thread
+// with the rows of all three base rows, and keeps their messages alpha and
+// channel LLRs in registers.  Per edge a thread reads the alphas of the other
+// two rows of the edge's variable, forms L = ((mu + a0) + a1) + a2 as the
+// one-unit decoder's sums are formed, and beta = clip(L - own alpha): every
+// row forms its variables' sums itself, so there is one exchange per
+// iteration, no sum is shared, and the results are the one-unit decoder's bit
+// for bit.
+//
+// The exchange needs no barrier.  An alpha travels as one 64-bit word (value,
+// iteration) through device-coherent stores and loads, and a reader repeats
+// its loads until the words carry the iteration it wants; nothing relies on
+// the order in which two words become visible.  Two words per edge (iteration
+// & 1) are enough: the thread at the other end of a variable writes its alpha
+// of iteration i + 2 only after it has read the reader's alpha of i + 1 on
+// the same variable, which the reader wrote after it had read the alpha of
+// iteration i.  The words are cleared first, in a launch of their own.
+//
+// Early stopping: a member publishes whether one of its rows is violated, in
+// a word of the same form, and every member reads all of them an iteration
+// later, beside the alphas, when L of the iteration they judge is still at
+// hand.
+//
+// Every wait ends: workgroups take their places in the order in which they
+// start, so at most one frame of a launch has a member that has not started,
+// and at most C - 1 workgroups wait for it.  A device runs at most 32 queues
+// at a time and holds two of these workgroups per compute unit, so with C <=
+// kSpMembers = 16 at most 480 of its 512 places are taken by such workgroups
+// and the missing ones find room.  The number of tries is bounded all the
+// same; a thread that exhausts it marks its outputs as NaN.
+//
+// 3 x 6, p = 3060, 20 iterations: 1 frame 96 us for 168 on one unit, 16 frames
+// 139 for 169.  An iteration of one frame takes 4.5 us, of which 3.3 are the
+// exchange (with one wavefront per member the rows take 0.8).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+
+#include "check2.h"
+#include "device.h"
+#include "internal.h"
+#include "onchip.h"
+#include "spread.h"
+
+namespace ldpc {
+
+constexpr int kSpRows = 3, kSpSlots = 9, kSpMembers = 16, kSpThreads = 256;
+
+struct SpreadArgs {
+    const float* llr;      // [gamma][n]
+    float* post;           // [gamma][n]
+    uint8_t* bits;         // [gamma][n]
+    int32_t* iters;        // [gamma] or NULL
+    uint8_t* conv;         // [gamma] or NULL
+    const float* nms_w;    // learned min-sum (RULE 1): [iters][blocks][2]
+    uint64_t* box;         // [gamma][2][E]: alpha of edge (j DC + k) p + s, slot iteration & 1
+    uint64_t* verdict;     // [gamma][2][kSpMembers]
+    uint32_t* ticket;      // workgroups that have started
+    int32_t n, p, max_iters, members, nb;
+    int32_t rb0[kSpRows];                      // first block of base row j
+    uint32_t sh4[kSpRows * kSpSlots];          // 4 times the shift of edge slot k of base row j
+    // 8 times the offset from row (j, s) to the row of base row (j + 1) % 3
+    // (first) and (j + 2) % 3 (second) that meets the variable of its slot k
+    uint32_t to1[kSpRows * kSpSlots], to2[kSpRows * kSpSlots];
+};
+
+// words in device memory
+typedef __attribute__((address_space(1))) uint64_t sp_word;
+typedef __attribute__((address_space(1))) char sp_byte;
+
+__device__ __forceinline__ uint64_t sp_load(sp_word* base, uint32_t byte) {
+    return __hip_atomic_load((sp_word*)((sp_byte*)base + byte), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void sp_store(sp_word* base, uint32_t byte, uint32_t value, uint32_t tag) {
+    __hip_atomic_store((sp_word*)((sp_byte*)base + byte), (uint64_t)value | (uint64_t)tag << 32, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// DC: row weight; RULE 0: sum-product, 1: learned min-sum; EARLY: with early
+// stopping.  Two workgroups fit a compute unit (256 registers).
+template <int DC, int RULE, bool EARLY>
+__global__ void __launch_bounds__(kSpThreads) spread_kernel(const SpreadArgs A) {
+    __shared__ uint32_t place, bad[2], go;
+    const int tid = threadIdx.x, TB = blockDim.x, p = A.p;
+    if (tid == 0) {
+        place = __hip_atomic_fetch_add(A.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bad[0] = bad[1] = 0u;
+    }
+    __syncthreads();
+    const uint32_t me = __builtin_amdgcn_readfirstlane(place);
+    const uint32_t frame = me / (uint32_t)A.members, member = me - frame * (uint32_t)A.members;
+    const size_t f0 = (size_t)frame * A.n;
+    const float* __restrict__ llr = A.llr + f0;
+    const uint32_t p4 = 4u * (uint32_t)p, p8 = 8u * (uint32_t)p;
+    const uint32_t s = member * (uint32_t)TB + (uint32_t)tid;
+    const bool active = s < (uint32_t)p;
+    const uint32_t s4 = 4u * s, s8 = 8u * s;
+    const size_t E = (size_t)kSpRows * DC * p;
+    sp_word* const box = (sp_word*)A.box + (size_t)frame * 2 * E;
+    sp_word* const verdict = (sp_word*)A.verdict + (size_t)frame * 2 * kSpMembers;
+    uint32_t tries = 1u << 22;
+
+    auto channel = [&](int j, int k) -> uint32_t {   // byte of the LLR that slot k of row (j, s) meets
+        const uint32_t t = s4 + A.sh4[j * kSpSlots + k];
+        return (uint32_t)k * p4 + min(t, t - p4);
+    };
+    auto raw = [&](int j, int k) -> float {
+        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(llr) + channel(j, k));
+    };
+    float mu[kSpRows][DC], al[kSpRows][DC], Lkeep[DC];
+#pragma unroll
+    for (int j = 0; j < kSpRows; ++j)
+#pragma unroll
+        for (int k = 0; k < DC; ++k) {
+            mu[j][k] = active ? raw(j, k) : 0.0f;
+            al[j][k] = 0.0f;
+        }
+#pragma unroll
+    for (int k = 0; k < DC; ++k) Lkeep[k] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kSpRows; ++j)
+#pragma unroll
+        for (int k = 0; k < DC; ++k) mu[j][k] = mu[j][k] * kLog2eF + 0.0f;
+
+    // whether a member's rows are violated, from the words of iteration it
+    auto judged = [&](uint32_t it) -> bool {
+        bool v = false;
+        if (tid < A.members) {
+            uint64_t w = sp_load(verdict, 8u * ((it & 1u) * kSpMembers + (uint32_t)tid));
+            while ((uint32_t)(w >> 32) != it && tries > 0u) {
+                --tries;
+                w = sp_load(verdict, 8u * ((it & 1u) * kSpMembers + (uint32_t)tid));
+            }
+            v = (uint32_t)w != 0u;
+        }
+        return __ballot(v) != 0ull;
+    };
+
+    int stop = 0;
+    for (int it = 1;; ++it) {
+        const bool fin = it > A.max_iters;
+        const uint32_t want = (uint32_t)(it - 1);
+        sp_word* from = box + (want & 1u) * E;
+        sp_word* to = box + ((uint32_t)it & 1u) * E;
+        // alphas of the other rows of the thread's variables, iteration it - 1
+        uint64_t w1[kSpRows][DC], w2[kSpRows][DC];
+        auto fetch = [&]() -> bool {
+            // opaque: the words' offsets are worked out again at every try, not held
+            uint32_t at = s8;
+            asm volatile("" : "+v"(at));
+            bool ok = true;
+#pragma unroll
+            for (int j = 0; j < kSpRows; ++j) {
+                const int j1 = (j + 1) % kSpRows, j2 = (j + 2) % kSpRows;
+#pragma unroll
+                for (int k = 0; k < DC; ++k) {
+                    const uint32_t t1 = at + A.to1[j * kSpSlots + k], t2 = at + A.to2[j * kSpSlots + k];
+                    w1[j][k] = sp_load(from, (uint32_t)(j1 * DC + k) * p8 + min(t1, t1 - p8));
+                    w2[j][k] = sp_load(from, (uint32_t)(j2 * DC + k) * p8 + min(t2, t2 - p8));
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kSpRows; ++j)
+#pragma unroll
+                for (int k = 0; k < DC; ++k)
+                    ok = ok && (uint32_t)(w1[j][k] >> 32) == want && (uint32_t)(w2[j][k] >> 32) == want;
+            return ok;
+        };
+        if (it > 1 && active)
+            while (!fetch() && tries > 0u) --tries;
+        if (EARLY && it >= 3) {
+            if (tid < 64) {
+                const bool any = judged(want);
+                if (tid == 0) go = any ? 1u : 0u;
+            }
+            __syncthreads();
+            if (go == 0u) {   // the syndrome of iteration it - 2 is zero: Lkeep holds its sums
+                stop = it - 2;
+                break;
+            }
+        }
+        uint64_t viol = 0;
+        if (active) {
+#pragma unroll
+            for (int j = 0; j < kSpRows; ++j) {
+                float x[DC];
+                uint32_t sx = 0;
+#pragma unroll
+                for (int k = 0; k < DC; ++k) {
+                    float L = mu[j][k];
+                    if (it > 1) {
+                        const float u = __uint_as_float((uint32_t)w1[j][k]), v = __uint_as_float((uint32_t)w2[j][k]);
+                        const float a0 = j == 0 ? al[j][k] : j == 1 ? v : u;
+                        const float a1 = j == 0 ? u : j == 1 ? al[j][k] : v;
+                        const float a2 = j == 0 ? v : j == 1 ? u : al[j][k];
+                        L = ((L + a0) + a1) + a2;
+                    }
+                    if (j == 0) Lkeep[k] = L;
+                    sx ^= __float_as_uint(L);   // the row's parity in bit 31 (a sum is never -0)
+                    x[k] = clip2(L - al[j][k]);
+                }
+                viol |= __ballot((int32_t)sx < 0);
+                if (!fin) {
+                    uint32_t at = s8;
+                    asm volatile("" : "+v"(at));
+                    if constexpr (RULE == 0)
+                        check2e_row<DC, 1>(x, DC);
+                    else
+                        nms2_row<DC>(x, DC, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
+#pragma unroll
+                    for (int k = 0; k < DC; ++k) {
+                        al[j][k] = x[k];
+                        sp_store(to, (uint32_t)(j * DC + k) * p8 + at, __float_as_uint(x[k]), (uint32_t)it);
+                    }
+                }
+            }
+        }
+        if ((EARLY && it >= 2) || fin) {
+            if (viol != 0ull && (tid & 63) == 0) bad[it & 1] = 1u;
+            __syncthreads();
+            if (tid == 0) {
+                sp_store(verdict, 8u * (((uint32_t)it & 1u) * kSpMembers + member), bad[it & 1], (uint32_t)it);
+                bad[(it + 1) & 1] = 0u;
+            }
+        }
+        if (fin) break;
+    }
+
+    if (active) {
+#pragma unroll
+        for (int k = 0; k < DC; ++k) {
+            const float x = tries > 0u ? Lkeep[k] : __builtin_nanf("");
+            const size_t v = f0 + (channel(0, k) >> 2);
+            A.post[v] = unscale2(x, raw(0, k));
+            A.bits[v] = (uint8_t)(x < 0.0f);
+        }
+    }
+    if (member == 0 && tid < 64) {
+        const bool any = stop ? false : judged((uint32_t)A.max_iters + 1u);
+        if (tid == 0) {
+            if (A.iters) A.iters[frame] = stop ? stop : A.max_iters;
+            if (A.conv) A.conv[frame] = any || tries == 0u ? 0 : 1;
+        }
+    }
+}
+
+// Clears the words (count 16-byte pieces).
+__global__ void __launch_bounds__(256) spread_clear_kernel(uint4* words, size_t count) {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256)
+        words[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+
+namespace {
+
+struct SpreadVariant {
+    int dc, rule;
+    const void *fn, *fn_early;
+};
+
+template <int DC, int RULE>
+constexpr SpreadVariant spread() {
+    return SpreadVariant{DC, RULE, reinterpret_cast<const void*>(&spread_kernel<DC, RULE, false>),
+                         reinterpret_cast<const void*>(&spread_kernel<DC, RULE, true>)};
+}
+
+const SpreadVariant kSpread[] = {spread<6, 0>(), spread<9, 0>(), spread<6, 1>(), spread<9, 1>()};
+
+// Below this an iteration on one compute unit takes no longer than the
+// exchange.  20 iterations, one unit / spread: 3 x 6, p = 1000 61 / 87 us for
+// 8 frames, p = 1600 95 / 87 for 1 and 96 / 100 for 16, p = 2000 114 / 89 and
+// 115 / 109; 3 x 9, p = 1600 148 / 132 and 150 / 149, p = 2048 182 / 133 and
+// 183 / 158.
+constexpr int kSpLeastP = 1800;
+
+struct SpreadChoice {
+    const SpreadVariant* v;
+    int members, tb;
+    size_t ticket, verdict, total;   // bytes: the boxes come first
+};
+
+// Codes that the one-unit decoder keeps two sums per variable for (its order
+// of additions is the one followed here) and batches that leave kSpMembers
+// compute units to a frame: with 25 frames on 10 units each the exchange's
+// traffic makes it slower (p = 2000 133 us for 115).
+bool choose_spread(const ldpc_graph* g, int rule, int gamma, SpreadChoice& c) {
+    const QCDesc& D = g->qc;
+    if (g->kind != LDPC_GRAPH_QC || D.J != kSpRows || D.p < kSpLeastP) return false;
+    for (int j = 0; j < D.J; ++j)
+        if (D.rstart[j + 1] - D.rstart[j] != D.L) return false;   // a zero block
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (gamma > cus / kSpMembers || 2 * cus <= 32 * (kSpMembers - 1)) return false;
+    c.tb = ((D.p + kSpMembers - 1) / kSpMembers + 63) / 64 * 64;
+    if (c.tb > kSpThreads) return false;
+    c.members = (D.p + c.tb - 1) / c.tb;
+    c.v = nullptr;
+    for (const SpreadVariant& v : kSpread)
+        if (v.dc == D.L && v.rule == rule) c.v = &v;
+    c.verdict = (size_t)gamma * 2 * D.E * sizeof(uint64_t);
+    c.ticket = c.verdict + (size_t)gamma * 2 * kSpMembers * sizeof(uint64_t);
+    c.total = c.ticket + 16;
+    return c.v != nullptr;
+}
+
+}  // namespace
+
+int spread_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
+                  uint8_t* bits, int32_t* iters, uint8_t* converged, void* ws, size_t ws_bytes, hipStream_t st,
+                  const float* nms_w) {
+    const char* path = std::getenv("LDPC_BLOCK_PATH");
+    if (path && std::strcmp(path, "onchip") == 0) return 0;
+    SpreadChoice c;
+    if (!onchip_pairs(g) || !choose_spread(g, nms_w ? 1 : 0, gamma, c) || c.total > ws_bytes) return 0;
+    const QCDesc& D = g->qc;
+    char* base = reinterpret_cast<char*>(ws);
+    SpreadArgs A{};
+    A.llr = llr;
+    A.post = post;
+    A.bits = bits;
+    A.iters = iters;
+    A.conv = converged;
+    A.nms_w = nms_w;
+    A.box = reinterpret_cast<uint64_t*>(base);
+    A.verdict = reinterpret_cast<uint64_t*>(base + c.verdict);
+    A.ticket = reinterpret_cast<uint32_t*>(base + c.ticket);
+    A.n = D.n;
+    A.p = D.p;
+    A.max_iters = max_iters;
+    A.members = c.members;
+    A.nb = D.nb;
+    for (int j = 0; j < kSpRows; ++j) {
+        A.rb0[j] = D.rstart[j];
+        for (int k = 0; k < D.L; ++k) {
+            const int a = D.eshift[D.rstart[j] + k];
+            const int a1 = D.eshift[D.rstart[(j + 1) % kSpRows] + k], a2 = D.eshift[D.rstart[(j + 2) % kSpRows] + k];
+            A.sh4[j * kSpSlots + k] = 4u * (uint32_t)a;
+            A.to1[j * kSpSlots + k] = 8u * (uint32_t)((a - a1 + D.p) % D.p);
+            A.to2[j * kSpSlots + k] = 8u * (uint32_t)((a - a2 + D.p) % D.p);
+        }
+    }
+    timing::Scope ts(23, st);
+    const size_t words = c.total / 16;
+    spread_clear_kernel<<<(unsigned)std::min<size_t>((words + 255) / 256, 2048), 256, 0, st>>>(
+        reinterpret_cast<uint4*>(base), words);
+    if (hipGetLastError() != hipSuccess) return -1;
+    void* args[] = {&A};
+    return hipLaunchKernel(early ? c.v->fn_early : c.v->fn, dim3((unsigned)(gamma * c.members)), dim3((unsigned)c.tb),
+                           args, 0, st) == hipSuccess ? 1 : -1;
+}
+
+}  // namespace ldpc
