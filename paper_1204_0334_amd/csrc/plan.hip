@@ -1377,7 +1377,12 @@ void build_table(ldpc_plan* P, const PlanBuffers& B, char* ws) {
         T.io0 = io;
         T.red0 = red;
         T.red_chunks = (int)(((int64_t)T.cn_wpt * T.fpl + kPlanRedWords - 1) / kPlanRedWords);
-        if (P->onchip[c]) continue;   // no work in the phase launches: an empty range in each
+        if (P->onchip[c]) {
+            // no work in the phase launches, not even in what fills up their
+            // last block
+            T.cn0 = T.vn0 = T.syn0 = T.st0 = T.io0 = T.red0 = INT64_MAX;
+            continue;
+        }
         cn += (int64_t)T.tiles * T.cn_wpt;
         vn += (int64_t)T.tiles * T.vn_wpt;
         syn += ((int64_t)T.tiles * g->m + 63) / 64 * 64;

@@ -1,0 +1,29 @@
+"""A plan whose last codes run on chip after codes of the phase launches: the
+threads that fill up a phase launch's last block leave their results alone."""
+import pytest
+import torch
+
+from paper_1204_0334_amd import ldpc
+
+from test_gpu_plan import assert_same, make_case, single_code
+
+pytestmark = pytest.mark.gpu
+
+PACKAGES = dict(J=3, L=18, p=36, gamma=33, ebn0_db=3.5)
+ONCHIP = dict(J=3, L=6, p=81, gamma=100, ebn0_db=2.0)
+
+
+@pytest.mark.parametrize("specs", [[PACKAGES, ONCHIP], [ONCHIP, PACKAGES, ONCHIP], [PACKAGES, ONCHIP, PACKAGES]])
+@pytest.mark.parametrize("early", [True, False])
+def test_on_chip_codes_after_phase_codes(specs, early, monkeypatch):
+    monkeypatch.delenv("LDPC_BLOCK_PATH", raising=False)
+    graphs, llrs = make_case(specs, 9000)
+    plan = ldpc.Plan(graphs, [c["gamma"] for c in specs], 20, early_stop=early)
+    ws, outs = plan.workspace(), plan.outputs()
+    refs = single_code(graphs, llrs, 20, early)
+    for _ in range(5):
+        for o in outs:
+            for t in o:
+                t.zero_()
+        plan.decode(llrs, outs=outs, ws=ws)
+        assert_same(outs, refs, "on-chip codes after phase codes")
