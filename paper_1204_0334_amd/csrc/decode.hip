@@ -39,6 +39,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -1632,38 +1633,69 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
 // Thread = (frame f, block b of 4 bits): the counter (b, f mod 2^32, tag,
 // f >> 32) gives four uniforms u = (w + 0.5) 2^-32 and two Box-Muller pairs
 // r0 (cos, sin)(2 pi u1), r1 (cos, sin)(2 pi u3), r = sqrt(-2 ln u), in FP64.
-__global__ void awgn_llr_kernel(float* __restrict__ llr, int64_t n, int gamma, uint64_t seed, int64_t frame0,
-                                uint32_t tag, double sigma2) {
-    const int64_t nblk = (n + 3) / 4;
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= nblk * gamma) return;
-    const int64_t g = id / nblk, b = id - g * nblk;
-    const uint64_t f = (uint64_t)(frame0 + g);
-    uint32_t c[4] = {(uint32_t)b, (uint32_t)f, tag, (uint32_t)(f >> 32)};
-    philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
-    const double inv = 1.0 / 4294967296.0;
-    const double two_pi = 6.283185307179586476925286766559;
-    const double u0 = ((double)c[0] + 0.5) * inv, u1 = ((double)c[1] + 0.5) * inv;
-    const double u2 = ((double)c[2] + 0.5) * inv, u3 = ((double)c[3] + 0.5) * inv;
-    const double r0 = sqrt(-2.0 * log(u0)), r1 = sqrt(-2.0 * log(u2));
-    const double v[4] = {r0 * cos(two_pi * u1), r0 * sin(two_pi * u1), r1 * cos(two_pi * u3), r1 * sin(two_pi * u3)};
-    const double sigma = sqrt(sigma2);
+// Bound by the FP64 arithmetic: sine and cosine together, of an angle in half
+// turns (no reduction by pi), one division per launch and a grid row per frame
+// (no division of the index).  AWGNFIG
+__global__ void __launch_bounds__(256) awgn_llr_kernel(float* __restrict__ llr, int64_t n, int gamma, uint64_t seed,
+                                                       int64_t frame0, uint32_t tag, double sigma, double scale) {
+    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (b >= (n + 3) / 4) return;
+    for (int64_t g = blockIdx.y; g < gamma; g += gridDim.y) {
+        const uint64_t f = (uint64_t)(frame0 + g);
+        uint32_t c[4] = {(uint32_t)b, (uint32_t)f, tag, (uint32_t)(f >> 32)};
+        philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
+        const double inv = 1.0 / 4294967296.0;
+        double v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int64_t i = 4 * b + q;
-        if (i < n) llr[g * n + i] = (float)(2.0 * (1.0 + sigma * v[q]) / sigma2);
+        for (int h = 0; h < 2; ++h) {
+            const double r = sqrt(-2.0 * log(((double)c[2 * h] + 0.5) * inv));
+            double sn, cs;
+            sincospi(((double)c[2 * h + 1] + 0.5) * (2.0 * inv), &sn, &cs);
+            v[2 * h] = r * cs;
+            v[2 * h + 1] = r * sn;
+        }
+        float* out = llr + g * n + 4 * b;
+        float4 x;
+        x.x = (float)((1.0 + sigma * v[0]) * scale);
+        x.y = (float)((1.0 + sigma * v[1]) * scale);
+        x.z = (float)((1.0 + sigma * v[2]) * scale);
+        x.w = (float)((1.0 + sigma * v[3]) * scale);
+        if (4 * b + 4 <= n && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+            *reinterpret_cast<float4*>(out) = x;
+        } else {
+            const float y[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (4 * b + q < n) out[q] = y[q];
+        }
     }
+}
+
+// nonzero bytes of a word
+__device__ __forceinline__ unsigned int nonzero_bytes(uint32_t w) {
+    return __builtin_popcount((((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u);
 }
 
 // Bit errors against the all-zero codeword: per frame (one block per frame)
 // and accumulated into totals[0] (bit errors) and totals[1] (frame errors).
+// 16 bytes per load between the row's first and last 16-byte boundary
+// (COUNTFIG).
 __global__ void __launch_bounds__(256) count_errors_kernel(const uint8_t* __restrict__ bits, int64_t n,
                                                            int32_t* frame_errors, unsigned long long* totals) {
     __shared__ unsigned int part[4];
     const int g = blockIdx.x;
     const uint8_t* row = bits + (size_t)g * n;
     unsigned int cnt = 0;
-    for (int64_t i = threadIdx.x; i < n; i += 256) cnt += row[i] != 0;
+    const int64_t head = min((int64_t)((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15), n);
+    const int64_t words = (n - head) / 16;
+    const uint4* mid = reinterpret_cast<const uint4*>(row + head);
+    for (int64_t i = threadIdx.x; i < words; i += 256) {
+        const uint4 w = mid[i];
+        cnt += nonzero_bytes(w.x) + nonzero_bytes(w.y) + nonzero_bytes(w.z) + nonzero_bytes(w.w);
+    }
+    const int64_t tail = head + 16 * words;
+    if ((int64_t)threadIdx.x < head) cnt += row[threadIdx.x] != 0;
+    if ((int64_t)threadIdx.x < n - tail) cnt += row[tail + threadIdx.x] != 0;
     for (int off = 32; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = cnt;
     __syncthreads();
@@ -2631,9 +2663,9 @@ ldpc_status ldpc_awgn_llr(int64_t n, int32_t gamma, double sigma2, uint64_t seed
     if (!llr || n < 1 || gamma < 1 || !(sigma2 > 0.0) || frame0 < 0) return LDPC_EINVAL;
     if (n > ((int64_t)1 << 31) || (int64_t)gamma * n > ((int64_t)1 << 40)) return LDPC_EUNSUPPORTED;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    const int64_t threads = (n + 3) / 4 * gamma;
+    const dim3 grid((unsigned)(((n + 3) / 4 + 255) / 256), (unsigned)std::min(gamma, 65535));
     (void)hipGetLastError();
-    awgn_llr_kernel<<<(unsigned)((threads + 255) / 256), 256, 0, st>>>(llr, n, gamma, seed, frame0, 0x4E5Au, sigma2);
+    awgn_llr_kernel<<<grid, 256, 0, st>>>(llr, n, gamma, seed, frame0, 0x4E5Au, std::sqrt(sigma2), 2.0 / sigma2);
     return hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
 }
 
