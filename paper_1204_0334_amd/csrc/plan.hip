@@ -38,6 +38,7 @@
 #include "device.h"
 #include "internal.h"
 #include "onchip.h"
+#include "spread.h"
 
 namespace ldpc {
 
@@ -1254,11 +1255,16 @@ int default_layout(const ldpc_graph* g, int gamma) {
 
 }  // namespace
 
+// Streams that the on-chip codes of a plan are dealt to: with the caller's, one
+// for each of a process's four hardware queues.
+constexpr int kSides = 3;
+
 struct ldpc_plan {
     int ncodes = 0, max_iters = 0, early = 0;
     std::vector<const ldpc_graph*> graphs;
     std::vector<int> gammas, layouts;
     std::vector<size_t> region_off;       // byte offset of each code's region in the workspace
+    std::vector<size_t> region_bytes;
     size_t table_bytes = 0, ws_bytes = 0;
     std::vector<PlanCode> table;          // host copy of the device table
     // launch geometry
@@ -1276,10 +1282,12 @@ struct ldpc_plan {
     PersistArgs pa{};
     // codes decoded by the on-chip block decoder (onchip.hip) instead of the
     // phase launches: decided when the table is built (phase launches only,
-    // as ldpc_decode decides), launched on a stream forked from the caller's
-    std::vector<uint8_t> onchip;
-    hipStream_t side = nullptr;
-    hipEvent_t fork_ev = nullptr, join_ev = nullptr;
+    // as ldpc_decode decides), launched on `sides` streams forked from the
+    // caller's (branch[c]: code c's)
+    std::vector<uint8_t> onchip, branch;
+    int sides = 0;
+    hipStream_t side[kSides] = {};
+    hipEvent_t fork_ev = nullptr, join_ev[kSides] = {};
     // graph
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -1321,13 +1329,54 @@ int persist_items_per_ticket() {
 std::vector<uint8_t> onchip_choice(const ldpc_plan* P) {
     std::vector<uint8_t> v(P->ncodes, 0);
     if (!P->persistent)
-        for (int c = 0; c < P->ncodes; ++c) v[c] = onchip_selected(P->graphs[c]) ? 1 : 0;
+        for (int c = 0; c < P->ncodes; ++c) v[c] = onchip_selected(P->graphs[c]) || spread_bytes(P->graphs[c], P->gammas[c]) ? 1 : 0;
     return v;
+}
+
+// Deals the on-chip codes to streams, longest first to the least loaded.  A
+// code takes about 12 us and 0.2 ns per edge, iteration and round of 256
+// frames (about six iterations with early stopping), spread over several
+// units 20 us and 8 per iteration; another stream is used for every 60 us,
+// since it costs an event wait at either end.  Five codes of 27 <= p <= 2700,
+// 32 to 1024 frames, with early stopping: 236 us one after the other, 133 us
+// on three streams; two of them, 20 iterations: 488 and 318.  Beside phase
+// launches (3.6 us each at least) there are no more streams than let the
+// on-chip codes end with them: the phases take longer the more compute units
+// those hold at a time (7 codes, 5 of them on chip, phases of 300 us: 389 us
+// with one stream, 448 with three).
+void deal_onchip(ldpc_plan* P) {
+    P->branch.assign(P->ncodes, 0);
+    std::vector<int> order;
+    std::vector<double> cost(P->ncodes, 0.0);
+    double total = 0.0;
+    const int iters = P->early ? std::min(P->max_iters, 6) : P->max_iters;
+    double phases = 0.0;
+    for (int c = 0; c < P->ncodes; ++c) {
+        const ldpc_graph* g = P->graphs[c];
+        if (!P->onchip[c]) {
+            phases = std::max(phases, 3.6 * (2 * P->max_iters + 5)) + 1e-5 * g->E * P->gammas[c] * iters;
+            continue;
+        }
+        cost[c] = spread_bytes(g, P->gammas[c]) ? 20.0 + 8.0 * iters
+                                                : 12.0 + 0.2e-3 * g->E * iters * ((P->gammas[c] + 255) / 256);
+        total += cost[c];
+        order.push_back(c);
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+    const int most = phases > 0.0 ? std::min(kSides, (int)(total / phases) + 1) : kSides;
+    P->sides = order.empty() ? 0 : std::max(1, std::min({most, (int)order.size(), (int)(total / 60.0)}));
+    double load[kSides] = {};
+    for (int c : order) {
+        const int b = (int)(std::min_element(load, load + P->sides) - load);
+        P->branch[c] = (uint8_t)b;
+        load[b] += cost[c];
+    }
 }
 
 void build_table(ldpc_plan* P, const PlanBuffers& B, char* ws) {
     P->table.assign(P->ncodes, PlanCode{});
     P->onchip = onchip_choice(P);
+    deal_onchip(P);
     int64_t cn = 0, vn = 0, syn = 0, st = 0, io = 0, red = 0;
     for (int c = 0; c < P->ncodes; ++c) {
         const ldpc_graph* g = P->graphs[c];
@@ -1449,16 +1498,14 @@ bool same_buffers(const ldpc_plan* P, const PlanBuffers& B, const void* ws) {
 ldpc_status upload_table(ldpc_plan* P, const PlanBuffers& B, char* ws, hipStream_t st) {
     if (same_buffers(P, B, ws)) return LDPC_OK;
     build_table(P, B, ws);
-    bool any = false;
-    for (uint8_t o : P->onchip) any = any || o;
-    if (any && !P->side) {
+    for (int i = 0; i < P->sides; ++i) {
         // default priority, like every stream of the library
-        if (hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking) != hipSuccess) {
-            P->side = nullptr;
+        if (!P->side[i] && hipStreamCreateWithFlags(&P->side[i], hipStreamNonBlocking) != hipSuccess) {
+            P->side[i] = nullptr;
             return LDPC_EHIP;
         }
-        if (hipEventCreateWithFlags(&P->fork_ev, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&P->join_ev, hipEventDisableTiming) != hipSuccess)
+        if ((!P->fork_ev && hipEventCreateWithFlags(&P->fork_ev, hipEventDisableTiming) != hipSuccess) ||
+            (!P->join_ev[i] && hipEventCreateWithFlags(&P->join_ev[i], hipEventDisableTiming) != hipSuccess))
             return LDPC_EHIP;
     }
     // the table, then the persistent launch's counters (zero)
@@ -1491,23 +1538,25 @@ bool enqueue(ldpc_plan* P, char* ws, hipStream_t st) {
         return true;
     }
     bool ok = true;
-    // codes on chip: one launch each on the side stream, forked from st and
-    // joined back at the end (under capture, a parallel branch of the graph)
-    bool any_onchip = false;
-    for (uint8_t o : P->onchip) any_onchip = any_onchip || o;
-    if (any_onchip) {
-        (void)hipEventRecord(P->fork_ev, st);
-        (void)hipStreamWaitEvent(P->side, P->fork_ev, 0);
+    // codes on chip: one launch each on the side streams, forked from st and
+    // joined back at the end (under capture, parallel branches of the graph)
+    if (P->sides > 0) (void)hipEventRecord(P->fork_ev, st);
+    for (int i = 0; i < P->sides; ++i) {
+        (void)hipStreamWaitEvent(P->side[i], P->fork_ev, 0);
         for (int c = 0; c < nc; ++c) {
-            if (!P->onchip[c]) continue;
+            if (!P->onchip[c] || P->branch[c] != i) continue;
             const PlanCode& H = P->table[c];
-            ok = ok && onchip_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out,
-                                     H.iters, H.converged, P->side) > 0;
+            int r = spread_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
+                                  H.converged, H.region, P->region_bytes[c], P->side[i], nullptr);
+            if (r == 0)
+                r = onchip_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
+                                  H.converged, P->side[i]);
+            ok = ok && r > 0;
         }
-        (void)hipEventRecord(P->join_ev, P->side);
+        (void)hipEventRecord(P->join_ev[i], P->side[i]);
     }
     if (P->cn_waves > 0) enqueue_phases(P, T, st);
-    if (any_onchip) (void)hipStreamWaitEvent(st, P->join_ev, 0);
+    for (int i = 0; i < P->sides; ++i) (void)hipStreamWaitEvent(st, P->join_ev[i], 0);
     return ok;
 }
 
@@ -1591,7 +1640,9 @@ ldpc_status ldpc_plan_create(const ldpc_graph* const* graphs, const int32_t* gam
         size_t most = 0;
         for (int l = 0; l < kLayoutValues; ++l)
             if (layout_allowed(graphs[c], l)) most = std::max(most, code_region(graphs[c], gammas[c], l, max_iters).total);
+        most = std::max(most, spread_bytes(graphs[c], gammas[c]));
         P->region_off.push_back(off);
+        P->region_bytes.push_back(most);
         off = align256(off + most);
     }
     P->ws_bytes = off;
@@ -1603,9 +1654,11 @@ void ldpc_plan_destroy(ldpc_plan* P) {
     if (!P) return;
     drop_graph(P);
     if (P->cap_stream) (void)hipStreamDestroy(P->cap_stream);
-    if (P->side) (void)hipStreamDestroy(P->side);
+    for (int i = 0; i < kSides; ++i) {
+        if (P->side[i]) (void)hipStreamDestroy(P->side[i]);
+        if (P->join_ev[i]) (void)hipEventDestroy(P->join_ev[i]);
+    }
     if (P->fork_ev) (void)hipEventDestroy(P->fork_ev);
-    if (P->join_ev) (void)hipEventDestroy(P->join_ev);
     delete P;
 }
 

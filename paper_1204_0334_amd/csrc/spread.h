@@ -1,7 +1,7 @@
 // Block decoder with a frame on several compute units (spread.hip), for
-// batches that would leave most of the chip idle.  Called by ldpc_decode
-// before the one-unit decoder of onchip.hip, whose results it returns bit for
-// bit.
+// batches that would leave most of the chip idle.  Called by ldpc_decode and
+// the plans before the one-unit decoder of onchip.hip, whose results it
+// returns bit for bit, and in place of the message packages for longer codes.
 #pragma once
 
 #include <hip/hip_runtime_api.h>
@@ -10,6 +10,11 @@
 #include "internal.h"
 
 namespace ldpc {
+
+// Workspace of a batch of gamma frames on the current device, 0 when the rule
+// does not choose this decoder (or the environment variable LDPC_BLOCK_PATH is
+// "packages" or "onchip").
+size_t spread_bytes(const ldpc_graph* g, int gamma);
 
 // Enqueues the whole decode (arguments as ldpc_decode, nms_w as
 // ldpc_nms_decode's weights or NULL) in the workspace of ws_bytes.  Returns 1

@@ -1,9 +1,10 @@
 // Block decoder with a frame spread over several compute units (gfx950), for
-// full bases of 3 rows of weight 6 or 9.
+// full bases of 3 rows of weight 6, 9 or 18.
 //
 // On one compute unit (onchip.hip) an iteration of a long code is bound by
 // that unit's vector ALUs: 8 us for 3 x 6, p = 3060, with 255 of 256 units
-// idle when there is one frame.  Here C workgroups share a frame: member c
+// idle when there is one frame; longer codes do not fit one unit, and their
+// message packages take two launches per iteration.  Here C workgroups share a frame: member c
 // owns the check rows (j, s), c TB <= s < (c + 1) TB, one offset s per thread
 // with the rows of all three base rows, and keeps their messages alpha and
 // channel LLRs in registers.  Per edge a thread reads the alphas of the other
@@ -20,7 +21,8 @@
 // & 1) are enough: the thread at the other end of a variable writes its alpha
 // of iteration i + 2 only after it has read the reader's alpha of i + 1 on
 // the same variable, which the reader wrote after it had read the alpha of
-// iteration i.  The words are cleared first, in a launch of their own.
+// iteration i.  The words are cleared first, in a launch of their own: to
+// alphas 0 of iteration 0.
 //
 // Early stopping: a member publishes whether one of its rows is violated, in
 // a word of the same form, and every member reads all of them an iteration
@@ -38,6 +40,9 @@
 // 3 x 6, p = 3060, 20 iterations: 1 frame 96 us for 168 on one unit, 16 frames
 // 139 for 169.  An iteration of one frame takes 4.5 us, of which 3.3 are the
 // exchange (with one wavefront per member the rows take 0.8).
+// Codes too long for one unit, 20 iterations, spread / message packages: 3 x 6,
+// p = 3600, 1 frame 84 / 434 us, 16 frames 126 / 425; 3 x 18, p = 3600, 8
+// frames 239 / 940; stopping after 4 iterations 91 / 473 and 114 / 640.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,7 +57,7 @@
 
 namespace ldpc {
 
-constexpr int kSpRows = 3, kSpSlots = 9, kSpMembers = 16, kSpThreads = 256;
+constexpr int kSpRows = 3, kSpSlots = 18, kSpMembers = 16, kSpThreads = 256;
 
 struct SpreadArgs {
     const float* llr;      // [gamma][n]
@@ -85,9 +90,11 @@ __device__ __forceinline__ void sp_store(sp_word* base, uint32_t byte, uint32_t 
 }
 
 // DC: row weight; RULE 0: sum-product, 1: learned min-sum; EARLY: with early
-// stopping.  Two workgroups fit a compute unit (256 registers).
+// stopping.  Two workgroups fit a compute unit (256 registers).  The words of
+// all three rows are in flight together, of heavy rows those of one row.
 template <int DC, int RULE, bool EARLY>
-__global__ void __launch_bounds__(kSpThreads) spread_kernel(const SpreadArgs A) {
+__global__ void __launch_bounds__(kSpThreads) __attribute__((amdgpu_waves_per_eu(2)))
+spread_kernel(const SpreadArgs A) {
     __shared__ uint32_t place, bad[2], go;
     const int tid = threadIdx.x, TB = blockDim.x, p = A.p;
     if (tid == 0) {
@@ -115,20 +122,24 @@ __global__ void __launch_bounds__(kSpThreads) spread_kernel(const SpreadArgs A) 
     auto raw = [&](int j, int k) -> float {
         return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(llr) + channel(j, k));
     };
-    float mu[kSpRows][DC], al[kSpRows][DC], Lkeep[DC];
+    // of heavy rows the channel LLRs are read again where they are used
+    constexpr bool kMuInRegs = DC <= 9;
+    float mu[kMuInRegs ? kSpRows : 1][DC], al[kSpRows][DC], Lkeep[DC];
 #pragma unroll
     for (int j = 0; j < kSpRows; ++j)
 #pragma unroll
         for (int k = 0; k < DC; ++k) {
-            mu[j][k] = active ? raw(j, k) : 0.0f;
+            if (kMuInRegs) mu[kMuInRegs ? j : 0][k] = active ? raw(j, k) : 0.0f;
             al[j][k] = 0.0f;
         }
 #pragma unroll
     for (int k = 0; k < DC; ++k) Lkeep[k] = 0.0f;
+    if (kMuInRegs) {
 #pragma unroll
-    for (int j = 0; j < kSpRows; ++j)
+        for (int j = 0; j < kSpRows; ++j)
 #pragma unroll
-        for (int k = 0; k < DC; ++k) mu[j][k] = mu[j][k] * kLog2eF + 0.0f;
+            for (int k = 0; k < DC; ++k) mu[kMuInRegs ? j : 0][k] = mu[kMuInRegs ? j : 0][k] * kLog2eF + 0.0f;
+    }
 
     // whether a member's rows are violated, from the words of iteration it
     auto judged = [&](uint32_t it) -> bool {
@@ -150,32 +161,34 @@ __global__ void __launch_bounds__(kSpThreads) spread_kernel(const SpreadArgs A) 
         const uint32_t want = (uint32_t)(it - 1);
         sp_word* from = box + (want & 1u) * E;
         sp_word* to = box + ((uint32_t)it & 1u) * E;
-        // alphas of the other rows of the thread's variables, iteration it - 1
-        uint64_t w1[kSpRows][DC], w2[kSpRows][DC];
-        auto fetch = [&]() -> bool {
+        // alphas of the other rows of the variables of rows (j, s), j0 <= j <
+        // j0 + NW, iteration it - 1
+        constexpr int NW = DC <= 9 ? kSpRows : 1;
+        uint64_t w1[NW][DC], w2[NW][DC];
+        auto fetch = [&](int j0) -> bool {
             // opaque: the words' offsets are worked out again at every try, not held
             uint32_t at = s8;
             asm volatile("" : "+v"(at));
             bool ok = true;
 #pragma unroll
-            for (int j = 0; j < kSpRows; ++j) {
-                const int j1 = (j + 1) % kSpRows, j2 = (j + 2) % kSpRows;
+            for (int i = 0; i < NW; ++i) {
+                const int j = j0 + i, j1 = (j + 1) % kSpRows, j2 = (j + 2) % kSpRows;
 #pragma unroll
                 for (int k = 0; k < DC; ++k) {
                     const uint32_t t1 = at + A.to1[j * kSpSlots + k], t2 = at + A.to2[j * kSpSlots + k];
-                    w1[j][k] = sp_load(from, (uint32_t)(j1 * DC + k) * p8 + min(t1, t1 - p8));
-                    w2[j][k] = sp_load(from, (uint32_t)(j2 * DC + k) * p8 + min(t2, t2 - p8));
+                    w1[i][k] = sp_load(from, (uint32_t)(j1 * DC + k) * p8 + min(t1, t1 - p8));
+                    w2[i][k] = sp_load(from, (uint32_t)(j2 * DC + k) * p8 + min(t2, t2 - p8));
                 }
             }
 #pragma unroll
-            for (int j = 0; j < kSpRows; ++j)
+            for (int i = 0; i < NW; ++i)
 #pragma unroll
                 for (int k = 0; k < DC; ++k)
-                    ok = ok && (uint32_t)(w1[j][k] >> 32) == want && (uint32_t)(w2[j][k] >> 32) == want;
+                    ok = ok && (uint32_t)(w1[i][k] >> 32) == want && (uint32_t)(w2[i][k] >> 32) == want;
             return ok;
         };
-        if (it > 1 && active)
-            while (!fetch() && tries > 0u) --tries;
+        if (NW == kSpRows && active)
+            while (__ballot(!fetch(0)) != 0ull && tries > 0u) --tries;
         if (EARLY && it >= 3) {
             if (tid < 64) {
                 const bool any = judged(want);
@@ -191,18 +204,30 @@ __global__ void __launch_bounds__(kSpThreads) spread_kernel(const SpreadArgs A) 
         if (active) {
 #pragma unroll
             for (int j = 0; j < kSpRows; ++j) {
+                float (&m)[DC] = mu[kMuInRegs ? j : 0];
+                if (!kMuInRegs) {
+                    uint32_t at = s4;
+                    asm volatile("" : "+v"(at));
+#pragma unroll
+                    for (int k = 0; k < DC; ++k) {
+                        const uint32_t t = at + A.sh4[j * kSpSlots + k];
+                        m[k] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(llr) +
+                                                               ((uint32_t)k * p4 + min(t, t - p4))) * kLog2eF + 0.0f;
+                    }
+                }
+                if (NW == 1)
+                    while (__ballot(!fetch(j)) != 0ull && tries > 0u) --tries;
+                constexpr bool all = NW == kSpRows;
                 float x[DC];
                 uint32_t sx = 0;
 #pragma unroll
                 for (int k = 0; k < DC; ++k) {
-                    float L = mu[j][k];
-                    if (it > 1) {
-                        const float u = __uint_as_float((uint32_t)w1[j][k]), v = __uint_as_float((uint32_t)w2[j][k]);
-                        const float a0 = j == 0 ? al[j][k] : j == 1 ? v : u;
-                        const float a1 = j == 0 ? u : j == 1 ? al[j][k] : v;
-                        const float a2 = j == 0 ? v : j == 1 ? u : al[j][k];
-                        L = ((L + a0) + a1) + a2;
-                    }
+                    const float u = __uint_as_float((uint32_t)w1[all ? j : 0][k]);
+                    const float v = __uint_as_float((uint32_t)w2[all ? j : 0][k]);
+                    const float a0 = j == 0 ? al[j][k] : j == 1 ? v : u;
+                    const float a1 = j == 0 ? u : j == 1 ? al[j][k] : v;
+                    const float a2 = j == 0 ? v : j == 1 ? u : al[j][k];
+                    const float L = ((m[k] + a0) + a1) + a2;
                     if (j == 0) Lkeep[k] = L;
                     sx ^= __float_as_uint(L);   // the row's parity in bit 31 (a sum is never -0)
                     x[k] = clip2(L - al[j][k]);
@@ -212,7 +237,7 @@ __global__ void __launch_bounds__(kSpThreads) spread_kernel(const SpreadArgs A) 
                     uint32_t at = s8;
                     asm volatile("" : "+v"(at));
                     if constexpr (RULE == 0)
-                        check2e_row<DC, 1>(x, DC);
+                        check2e_row<DC, DC <= 9 ? 1 : 2>(x, DC);
                     else
                         nms2_row<DC>(x, DC, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
 #pragma unroll
@@ -275,14 +300,16 @@ constexpr SpreadVariant spread() {
                          reinterpret_cast<const void*>(&spread_kernel<DC, RULE, true>)};
 }
 
-const SpreadVariant kSpread[] = {spread<6, 0>(), spread<9, 0>(), spread<6, 1>(), spread<9, 1>()};
+const SpreadVariant kSpread[] = {spread<6, 0>(), spread<9, 0>(), spread<18, 0>(),
+                                 spread<6, 1>(), spread<9, 1>(), spread<18, 1>()};
 
 // Below this an iteration on one compute unit takes no longer than the
 // exchange.  20 iterations, one unit / spread: 3 x 6, p = 1000 61 / 87 us for
 // 8 frames, p = 1600 95 / 87 for 1 and 96 / 100 for 16, p = 2000 114 / 89 and
 // 115 / 109; 3 x 9, p = 1600 148 / 132 and 150 / 149, p = 2048 182 / 133 and
-// 183 / 158.
-constexpr int kSpLeastP = 1800;
+// 183 / 158.  Codes that no one-unit kernel takes (p = 1537 and more; the others
+// have p < 64) are faster here at every length.
+constexpr int kSpLeastP = 1800, kSpLeastLongP = 1024;
 
 struct SpreadChoice {
     const SpreadVariant* v;
@@ -291,12 +318,16 @@ struct SpreadChoice {
 };
 
 // Codes that the one-unit decoder keeps two sums per variable for (its order
-// of additions is the one followed here) and batches that leave kSpMembers
-// compute units to a frame: with 25 frames on 10 units each the exchange's
-// traffic makes it slower (p = 2000 133 us for 115).
+// of additions is the one followed here) and codes that no one-unit kernel
+// takes; batches that leave kSpMembers compute units to a frame: with 25
+// frames on 10 units each the exchange's traffic makes it slower (p = 2000 133
+// us for 115).
 bool choose_spread(const ldpc_graph* g, int rule, int gamma, SpreadChoice& c) {
     const QCDesc& D = g->qc;
-    if (g->kind != LDPC_GRAPH_QC || D.J != kSpRows || D.p < kSpLeastP) return false;
+    if (g->kind != LDPC_GRAPH_QC || D.J != kSpRows || gamma < 1) return false;
+    const char* path = std::getenv("LDPC_BLOCK_PATH");
+    if (path && (std::strcmp(path, "onchip") == 0 || std::strcmp(path, "packages") == 0)) return false;
+    if (onchip_fits(g) ? !onchip_pairs(g) || D.p < kSpLeastP : D.p < kSpLeastLongP) return false;
     for (int j = 0; j < D.J; ++j)
         if (D.rstart[j + 1] - D.rstart[j] != D.L) return false;   // a zero block
     int dev = 0, cus = 0;
@@ -320,13 +351,16 @@ bool choose_spread(const ldpc_graph* g, int rule, int gamma, SpreadChoice& c) {
 
 }  // namespace
 
+size_t spread_bytes(const ldpc_graph* g, int gamma) {
+    SpreadChoice c;
+    return choose_spread(g, 0, gamma, c) ? c.total : 0;
+}
+
 int spread_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
                   uint8_t* bits, int32_t* iters, uint8_t* converged, void* ws, size_t ws_bytes, hipStream_t st,
                   const float* nms_w) {
-    const char* path = std::getenv("LDPC_BLOCK_PATH");
-    if (path && std::strcmp(path, "onchip") == 0) return 0;
     SpreadChoice c;
-    if (!onchip_pairs(g) || !choose_spread(g, nms_w ? 1 : 0, gamma, c) || c.total > ws_bytes) return 0;
+    if (!choose_spread(g, nms_w ? 1 : 0, gamma, c) || c.total > ws_bytes) return 0;
     const QCDesc& D = g->qc;
     char* base = reinterpret_cast<char*>(ws);
     SpreadArgs A{};

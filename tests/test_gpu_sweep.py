@@ -80,7 +80,7 @@ def test_rate_five_sixths_against_the_reference(p, positions, I, gamma):
 
 
 def test_a_workspace_of_the_ring_alone_still_decodes():
-    # 40 positions and 4 processors: the sweeps need more than the ring
+    # 40 positions and 8 processors: the sweeps need more than the ring
     p, positions, I, gamma = 48, 40, 8, 200
     g = ldpc.Graph.ldpccc_from_qc(shifts(3, 6, p), p, positions, True)
     x = ldpc.awgn_llr(g.n, gamma, 0.5, 5, 0, device=DEV)
