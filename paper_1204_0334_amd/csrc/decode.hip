@@ -49,6 +49,7 @@
 #include "device.h"
 #include "internal.h"
 #include "onchip.h"
+#include "small.h"
 #include "spread.h"
 #include "sweep.h"
 #include "train.h"
@@ -2433,6 +2434,9 @@ static ldpc_status decode_block(const ldpc_graph* g, const float* llr, int32_t g
         if (r == 0)
             r = onchip_decode(g, llr, gamma, max_iters, early_stop ? 1 : 0, post, bits, iters, converged, st,
                                     nms_w);
+        // short codes with a frame's packages in LDS
+        if (r == 0 && !nms_w)
+            r = small_decode(g, llr, gamma, max_iters, early_stop ? 1 : 0, post, bits, iters, converged, st);
         if (r != 0) return r > 0 && hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
     }
     switch (tl.fpl) {

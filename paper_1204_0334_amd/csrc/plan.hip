@@ -38,6 +38,7 @@
 #include "device.h"
 #include "internal.h"
 #include "onchip.h"
+#include "small.h"
 #include "spread.h"
 
 namespace ldpc {
@@ -1329,7 +1330,8 @@ int persist_items_per_ticket() {
 std::vector<uint8_t> onchip_choice(const ldpc_plan* P) {
     std::vector<uint8_t> v(P->ncodes, 0);
     if (!P->persistent)
-        for (int c = 0; c < P->ncodes; ++c) v[c] = onchip_selected(P->graphs[c]) || spread_bytes(P->graphs[c], P->gammas[c]) ? 1 : 0;
+        for (int c = 0; c < P->ncodes; ++c) v[c] = onchip_selected(P->graphs[c]) || small_selected(P->graphs[c], P->gammas[c]) ||
+                           spread_bytes(P->graphs[c], P->gammas[c]) ? 1 : 0;
     return v;
 }
 
@@ -1551,6 +1553,9 @@ bool enqueue(ldpc_plan* P, char* ws, hipStream_t st) {
             if (r == 0)
                 r = onchip_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
                                   H.converged, P->side[i]);
+            if (r == 0)
+                r = small_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
+                                 H.converged, P->side[i]);
             ok = ok && r > 0;
         }
         (void)hipEventRecord(P->join_ev[i], P->side[i]);
