@@ -504,6 +504,11 @@ def bench_train(args):
                         "workspace_gb_ckpt4": round(ws.numel() * ws.element_size() / 1e9, 2)}
         del ws_all
     algo = train_algorithmic_bytes(n, E, gamma, T)
+    if not per_kernel["train_variable_node_backward"][0]:
+        # a frame on one compute unit: one launch each way, which pass the row
+        # words (3 per row) and the posteriors of every iteration
+        kept = 4 * T * gamma * (3 * g.info["m"] + n)
+        algo = {"train_check_node": kept + 4 * gamma * n, "train_check_node_backward": kept}
     dom = max(algo, key=lambda c: per_kernel[c][1])
     launches, ms = per_kernel[dom]
     avg_s = ms / launches * 1e-3
@@ -587,14 +592,20 @@ def bench_plan(args):
     per.decode(llrs, outs=pouts, ws=pws)
     per.check(pws)
     # same layouts, same device functions: bit for bit the phase launches'
-    # outputs for the codes both run in the message-package kernels (the
-    # phase launches decode the codes that fit a compute unit on chip, the
-    # persistent launch does not; after its own autotuning the persistent plan
-    # may also pick other layouts, and a split layout agrees only to FP32
-    # rounding)
+    # outputs when those decode every code (LDPC_BLOCK_PATH=packages; after its
+    # own autotuning the persistent plan may also pick other layouts, and a
+    # split layout agrees only to FP32 rounding)
+    os.environ["LDPC_BLOCK_PATH"] = "packages"
+    phases = ldpc.Plan(graphs, gammas, iters, early_stop=True)
+    for c in range(len(graphs)):
+        phases.set_layout(c, plan.layout(c))
+    fws, fouts = phases.workspace(dev), phases.outputs(dev)
+    phases.decode(llrs, outs=fouts, ws=fws)
     torch.cuda.synchronize()
-    pkg = [c for c, g in enumerate(graphs) if ldpc.decode_path(g) != "onchip"]
-    same = all(torch.equal(a, b) for c in pkg for a, b in zip(outs[c], pouts[c]))
+    os.environ.pop("LDPC_BLOCK_PATH", None)
+    pkg = list(range(len(graphs)))
+    same = all(torch.equal(a, b) for c in pkg for a, b in zip(fouts[c], pouts[c]))
+    del phases, fws, fouts
     per.capture(llrs, pouts, pws)
     per_same_ms = timed(per.replay, args.steps, args.warmup)
     per_tuned_ms = per.autotune(llrs, pouts, pws, trials=3)
@@ -608,42 +619,46 @@ def bench_plan(args):
     souts = [ldpc.decode(g, x, iters, True, ws=w) for g, x, w in zip(graphs, llrs, wss)]
     seq_ms = timed(lambda: [ldpc.decode(g, x, iters, True, out=o, ws=w)
                             for g, x, o, w in zip(graphs, llrs, souts, wss)], args.steps, args.warmup)
-    # fixed work (no early stop), same layouts: per-kernel times for the roofline
-    fixed = ldpc.Plan(graphs, gammas, iters, early_stop=False)
-    for c in range(len(graphs)):
-        fixed.set_layout(c, plan.layout(c))
-    fws = fixed.workspace(dev)
-    fouts = fixed.outputs(dev)
-    fixed.decode(llrs, outs=fouts, ws=fws)
-    torch.cuda.synchronize()
-    ldpc.timing_read()
-    ldpc.timing_enable(True)
-    for _ in range(args.steps):
+    # fixed work (no early stop): per-kernel times for the rooflines, of the
+    # decode as it runs and with every code in the phase launches
+    def fixed_work():
+        fixed = ldpc.Plan(graphs, gammas, iters, early_stop=False)
+        for c in range(len(graphs)):
+            fixed.set_layout(c, plan.layout(c))
+        fws = fixed.workspace(dev)
+        fouts = fixed.outputs(dev)
         fixed.decode(llrs, outs=fouts, ws=fws)
-    torch.cuda.synchronize()
-    ldpc.timing_enable(False)
-    per_kernel = ldpc.timing_read()
-    # the phase launches carry only the codes that do not run on chip
-    paths = [ldpc.decode_path(g) for g in graphs]
-    pk = [i for i, q in enumerate(paths) if q == "packages"]
+        torch.cuda.synchronize()
+        ldpc.timing_read()
+        ldpc.timing_enable(True)
+        for _ in range(args.steps):
+            fixed.decode(llrs, outs=fouts, ws=fws)
+        torch.cuda.synchronize()
+        ldpc.timing_enable(False)
+        return ldpc.timing_read()
+
+    per_kernel = fixed_work()
+    os.environ["LDPC_BLOCK_PATH"] = "packages"
+    phase_kernel = fixed_work()
+    os.environ.pop("LDPC_BLOCK_PATH", None)
+    pk = list(range(len(graphs)))
     E = [g.info["E"] for g in graphs]
     ns = [g.n for g in graphs]
     algo = {"plan_check_node": sum(8 * E[i] * gammas[i] for i in pk),
             "plan_variable_node": sum(((iters - 1) * (8 * E[i] + 4 * ns[i]) + 4 * E[i] + 8 * ns[i] + ns[i] / 8)
                                       * gammas[i] / iters for i in pk)}
-    dom = max(algo, key=lambda k: per_kernel[k][1])
-    launches, kms = per_kernel[dom]
+    dom = max(algo, key=lambda k: phase_kernel[k][1])
+    launches, kms = phase_kernel[dom]
     avg_s = kms / launches * 1e-3
     achieved = algo[dom] / avg_s / 1e9
     onchip = None
-    oc = [i for i, q in enumerate(paths) if q == "onchip"]
-    if oc and per_kernel["onchip_decode"][0]:
-        # fixed work: every iteration of every frame of the on-chip codes,
-        # over their launches' summed time (they run beside the phase launches)
+    if per_kernel["onchip_decode"][0]:
+        # every iteration of every frame of every code, over their launches'
+        # summed time (they run beside one another)
         slots = sum(iters * gammas[i] * (onchip_row_slots(shifts[i], specs[i]["p"]) + VN_EDGE_SLOTS * E[i])
-                    for i in oc)
+                    for i in pk)
         t_s = per_kernel["onchip_decode"][1] * 1e-3 / args.steps
-        onchip = {"bound": "alu", "codes": [i for i in oc], "achieved": round(slots / t_s / 1e12, 2),
+        onchip = {"bound": "alu", "codes": pk, "achieved": round(slots / t_s / 1e12, 2),
                   "peak": round(ALU_PEAK_TOPS, 2), "unit": "Top/s",
                   "frac": round(slots / t_s / 1e12 / ALU_PEAK_TOPS, 4),
                   "launch_us_per_decode": round(t_s * 1e6, 1)}
@@ -677,7 +692,7 @@ def bench_plan(args):
                        "autotuned_ms": round(per_tuned_ms, 4),
                        "ms_with_phase_launch_layouts": round(per_same_ms, 4),
                        "outputs_equal_phase_launches": bool(same), "codes_compared": pkg,
-                       "how": "one persistent launch per decode (ldpc_plan_set_persistent), HIP graph replay; outputs compared bit for bit with the phase launches in the same layouts, for the codes both decode in the message-package kernels"},
+                       "how": "one persistent launch per decode (ldpc_plan_set_persistent), HIP graph replay; outputs compared bit for bit with the phase launches of all codes (LDPC_BLOCK_PATH=packages) in the same layouts"},
         "sequential": {"ms_per_step": round(seq_ms, 4), "value": round(bits / (seq_ms * 1e-3) / 1e6, 2),
                        "speedup_of_plan": round(seq_ms / ms, 3),
                        "how": "the same frames decoded code by code with ldpc_decode (early stop)"},
@@ -685,8 +700,9 @@ def bench_plan(args):
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": dom,
                      "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_bytes_per_launch": round(algo[dom]),
                      "codes": pk, "onchip": onchip,
-                     "note": "fixed-work pass (no early stop) with the tuned layouts, over the codes of the phase "
-                             "launches; codes that fit a compute unit run the on-chip decoder beside them"},
+                     "note": "fixed-work pass (no early stop) with the tuned layouts and every code in the phase "
+                             "launches (LDPC_BLOCK_PATH=packages); onchip: the decode as it runs, one launch per "
+                             "code"},
         "cpu_baseline": cpu,
         "kernels": {c: {"launches": v[0], "avg_us": round(v[1] / v[0] * 1e3, 2)} for c, v in per_kernel.items()
                     if v[0]},
