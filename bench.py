@@ -42,9 +42,12 @@ TRAFFIC_FILE_ONCHIP_4096 = os.path.join(ROOT, "profiles", "traffic_onchip_qc36_p
 TRAFFIC_BY_GAMMA = {1024: TRAFFIC_FILE, 4096: TRAFFIC_FILE_4096}
 TRAFFIC_ONCHIP_BY_GAMMA = {1024: TRAFFIC_FILE_ONCHIP, 4096: TRAFFIC_FILE_ONCHIP_4096}
 # sources a counter record stays valid for: the package kernels (and the
-# convolutional-code kernels) live in decode.hip, the on-chip decoder in onchip.hip
+# convolutional-code kernels) live in decode.hip, the on-chip decoder in
+# onchip.hip, the one-unit training passes in train.hip
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1204_0334_amd", "csrc", f)
                   for f in ("decode.hip", "check2.h", "device.h", "internal.h")]
+TRAIN_SOURCES = [os.path.join(ROOT, "paper_1204_0334_amd", "csrc", f)
+                 for f in ("train.hip", "device.h", "internal.h")]
 ONCHIP_SOURCES = [os.path.join(ROOT, "paper_1204_0334_amd", "csrc", f)
                   for f in ("onchip.hip", "check2.h", "device.h", "internal.h")]
 
@@ -524,7 +527,8 @@ def bench_train(args):
                    "n": n, "gamma": gamma, "T": T, "ckpt_every": k},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": measured_traffic(dom, os.path.join(ROOT, "profiles", "traffic_nnms_train_p3060.json")),
+                     "traffic": measured_traffic(dom, os.path.join(ROOT, "profiles", "traffic_nnms_train_p3060.json"),
+                                                 TRAIN_SOURCES),
                      "kernel": dom,
                      "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_bytes_per_launch": round(algo[dom])},
         "cpu_baseline": None,
