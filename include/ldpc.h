@@ -178,8 +178,15 @@ ldpc_status ldpc_decode(const ldpc_graph* g, const float* llr, int32_t gamma, in
  * p <= 3072, two n-float arrays within the device's LDS per workgroup; and
  * codes of a full base, p >= 64, with 3 rows of weight 9 (p <= 3072) or 18
  * (p <= 1536) or 4 rows of weight 24 (p <= 1024)), 0
- * when it runs the message-package decoder (edge messages in the workspace,
- * one launch per half-iteration).  Both compute Algorithm 1; the package
+ * when it runs the message-package decoder (one launch per half-iteration,
+ * edge messages in the workspace; for codes of up to 8192 edges, with columns
+ * of weight above 4 for batches of up to 256 frames, one launch per decode
+ * with a frame's packages in LDS, equal bit for bit).  Batches of up to 16
+ * frames of full bases of 3 rows of weight 6, 9 or 18 with 1800 <= p <= 4096
+ * are decoded with a frame on 16 compute units, messages in the workspace:
+ * bit for bit as on one unit where the code has two sums per variable there;
+ * longer codes, of which this function returns 0, in the on-chip decoder's
+ * arithmetic.  Both decoders compute Algorithm 1; the package
  * decoder's FP32 check rule combines (tanh, 1 - tanh) pairs, the on-chip
  * decoder's the two parities' probabilities up to a common factor (no
  * reciprocal per input), and the on-chip decoder forms each
@@ -187,7 +194,8 @@ ldpc_status ldpc_decode(const ldpc_graph* g, const float* llr, int32_t gamma, in
  * instead of summing the other edges, so the two agree within FP32
  * rounding, not bit for bit.  Setting
  * the environment variable LDPC_BLOCK_PATH=packages makes ldpc_decode use
- * the package decoder for every code (read at each call).  The workspace
+ * the launches of the package decoder for every code, =onchip keeps a frame
+ * on one compute unit (read at each call).  The workspace
  * argument of ldpc_decode is validated the same way on both paths.
  * Errors: EINVAL (NULL, convolutional graph).
  */
@@ -270,6 +278,12 @@ ldpc_status ldpc_nms_decode(const ldpc_graph* g, const float* llr, int32_t gamma
  * Errors: EINVAL (NULL pointers, convolutional graph, gamma < 1, iters
  * outside [1, LDPC_MAX_ITERS], ckpt_every outside [1, iters], misaligned
  * buffers), EWORKSPACE, EHIP.
+ * Execution: full bases of 3 rows of weight 6, 9 or 18 whose two arrays of n
+ * floats fit the LDS run with a frame on one compute unit where that takes no
+ * more workspace than any ckpt_every would: the forward pass then keeps, of
+ * every iteration, what the backward pass reads, and nothing is recomputed.
+ * The same weights, losses and gradients' definition; ckpt_every changes
+ * neither the route nor the result.
  */
 ldpc_status ldpc_nms_train_workspace_size(const ldpc_graph* g, int32_t gamma, int32_t iters, int32_t ckpt_every,
                                           size_t* bytes);
@@ -286,10 +300,11 @@ ldpc_status ldpc_nms_train_backward(const ldpc_graph* g, int32_t gamma, int32_t 
  * (Algorithm 1, Eq. 3-6; same arithmetic, so each code's outputs equal
  * ldpc_decode's bit for bit, except in the split layouts below).  Codes that ldpc_decode would decode on chip
  * (ldpc_decode_path; not in persistent mode) run that decoder, one launch
- * per code on a stream forked from the caller's and joined back before the
- * decode ends; for the others, one check-node launch and one variable-node
+ * per code on streams forked from the caller's and joined back before the
+ * decode ends (so do short codes with a frame's packages in LDS and small
+ * batches with a frame on several compute units); for the others, one check-node launch and one variable-node
  * launch per iteration cover all codes.  The whole decode can be captured
- * once into a HIP graph (the on-chip launches as a parallel branch) and
+ * once into a HIP graph (the on-chip launches as parallel branches) and
  * replayed; which codes run on chip is decided when the plan binds its
  * buffers, so a change of LDPC_BLOCK_PATH between calls rebuilds the table
  * and invalidates a captured graph.
@@ -429,10 +444,12 @@ ldpc_status ldpc_plan_check(ldpc_plan* plan, void* workspace, void* stream);
  *   post  device, float [gamma][positions * c]: clip(posterior, +-30)
  *   bits  device, uint8 [gamma][positions * c]
  *   W     window length in positions, ms + 1 <= W <= 64
- * Execution: when one stream's ring (the messages and channel LLRs of the
- * W + ms positions a window holds) fits the device's LDS per workgroup, each
- * stream is decoded from start to end by one workgroup out of LDS (one
- * launch); otherwise every phase is a launch over all streams, with the
+ * Execution: each stream is decoded from start to end by one workgroup (one
+ * launch) when its window is covered: messages in registers and the window's
+ * sums in LDS for codes of a full base with one circulant row per layer and
+ * two columns per position (T = ms + 1 = 3, p <= 512, W = 5 or 6), else a
+ * ring of messages and channel LLRs (the W + ms positions a window holds) in
+ * LDS where it fits; otherwise every phase is a launch over all streams, with the
  * ring in the workspace.  Both give the same results bit for bit; the
  * environment variable LDPC_WINDOW_PATH=launch (or =lds) selects one.  The
  * workspace size is that of the launch-per-phase form in either case.
@@ -514,14 +531,15 @@ const char* ldpc_status_str(ldpc_status s);
  *   5 frame status, 6 window ingest, 7 window check-node,
  *   8 window variable-node, 9 pipeline ingest, 10 pipeline check-node (a
  *   sweep, where each stream is decoded on one compute unit),
- *   11 pipeline variable-node, 12 training check-node, 13 training
+ *   11 pipeline variable-node, 12 training check-node (or the whole forward
+ *   pass, where a frame is on one compute unit), 13 training
  *   variable-node, 14 training variable-node backward, 15 training
- *   check-node backward, 16 training loss and gradient reductions,
+ *   check-node backward (or the whole backward pass), 16 training loss and gradient reductions,
  *   17 plan ingest, 18 plan check-node, 19 plan variable-node, 20 plan
  *   final syndrome, frame status and output, 21 window decoding with the
  *   ring in LDS (one launch per call), 22 plan decode in one persistent
- *   launch, 23 block decode with each frame on one compute unit (one launch
- *   per call).
+ *   launch, 23 block decode with each frame on one compute unit, or on
+ *   several (one launch per call, after one that clears the words).
  * ldpc_kernel_class_name returns a static name for a class index.
  */
 #define LDPC_TIMING_CLASSES 24
