@@ -278,8 +278,8 @@ ldpc_status ldpc_nms_decode(const ldpc_graph* g, const float* llr, int32_t gamma
  * Errors: EINVAL (NULL pointers, convolutional graph, gamma < 1, iters
  * outside [1, LDPC_MAX_ITERS], ckpt_every outside [1, iters], misaligned
  * buffers), EWORKSPACE, EHIP.
- * Execution: full bases of 3 rows of weight 6, 9 or 18 whose two arrays of n
- * floats fit the LDS run with a frame on one compute unit where that takes no
+ * Execution: full bases of 3 rows of weight 6, 9 or 18, or 4 rows of weight 24
+ * with p <= 768, whose two arrays of n floats fit the LDS run with a frame on one compute unit where that takes no
  * more workspace than any ckpt_every would: the forward pass then keeps, of
  * every iteration, what the backward pass reads, and nothing is recomputed.
  * The same weights, losses and gradients' definition; ckpt_every changes

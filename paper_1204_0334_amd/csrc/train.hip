@@ -1,5 +1,5 @@
 // Training step of the learned min-sum decoder with a frame on one compute
-// unit (gfx950), for full bases of 3 rows.
+// unit (gfx950), for full bases of 3 rows, and of 4 rows of weight 24.
 //
 // The message-package form (decode.hip) passes every message through memory
 // eight times an iteration: forward, each iteration's alphas and betas are
@@ -11,7 +11,7 @@
 // What the backward pass needs of a check row is not its betas but which
 // edges hold the two smallest magnitudes, those magnitudes, and the signs
 // (the minimum's gradient reaches no other edge): three words per row and
-// iteration instead of two floats per edge.  With the posteriors, from which
+// iteration (four with rows of weight 24) instead of two floats per edge.  With the posteriors, from which
 // the backward pass forms dloss/dL, that is 60 bytes per iteration and place
 // of a base column of a 3 x 6 code, written once and read once.
 //
@@ -20,7 +20,7 @@
 // added in order of the base rows, L = mu + ((a0 + a1) + a2).  Rows of base
 // rows 1 and 2 publish their alphas, read each other's, base row 0's threads
 // form L and their betas and publish a0 and mu in place, and base rows 1 and 2
-// form theirs: four barriers per iteration.
+// form theirs: four barriers per iteration (4 rows: train_forward4_kernel).
 //
 // Backward: LDS holds, per variable, D = dloss/dL + the sum of the gradients
 // that reached its edges' betas; an edge's dalpha is D less its own.  An
@@ -45,18 +45,22 @@
 
 namespace ldpc {
 
-constexpr int kTrRows = 3, kTrSlots = 18, kTrWaves = 16;
+constexpr int kTrRows = 4, kTrSlots = 24;
+
+// words kept per row: the minima, their edges and the signs (rows of weight
+// above 18: the signs in a word of their own)
+constexpr int tr_words(int dc) { return dc <= 18 ? 3 : 4; }
 
 struct TrainArgs {
     const float* llr;      // [gamma][n] (forward)
     const float* w;        // [T][blocks][2]
     const float* dloss;    // [T] (backward)
-    float* rows;           // [gamma][T][3 words][3][p]: minimum, second minimum, edges and signs
+    float* rows;           // [gamma][T][words][rows][p]: minimum, second minimum, edges and signs
     float* post;           // [gamma][T][n]: posteriors, by place
     float* lpart;          // [T][gamma]: loss sums
-    float* gpart;          // [T][gamma][kTrWaves][blocks][2]
+    float* gpart;          // [T][gamma][waves][blocks][2]
     float inv_count;
-    int32_t n, p, T, gamma;
+    int32_t n, p, T, gamma, waves;
     // Columns are kept rotated by base row 0's shifts (place l p + u holds
     // variable l p + (u + a_0l) mod p), so a row (0, s) meets the places l p +
     // s.  Edge slot k of base row j (index j * kTrSlots + k): 4 times its
@@ -123,9 +127,56 @@ __device__ __forceinline__ float sigmoid_neg(float L) {
     return fmaf(fmaf(-d, r, 1.0f), r, r);
 }
 
+// A check row's forward pass.  flip: bit DC - 1 - k, the sign of the product of
+// the other edges of slot k; par: of all.
+template <int DC>
+struct TrRow {
+    float m1, m2;
+    uint32_t edges, flip, par;   // edges: i1, i2 << 5, unclipped << 10 and << 11
+
+    // x: betas before the clip on entry, alphas on return
+    __device__ __forceinline__ void update(float (&x)[DC], const float* __restrict__ w) {
+        m1 = m2 = __builtin_inff();
+        int i1 = 0, i2 = 0;
+        uint32_t sgn = 0, cut = 0;   // slot k's sign, whether it is clipped: bit DC - 1 - k
+#pragma unroll
+        for (int k = 0; k < DC; ++k) {
+            const float b = x[k] + 0.0f;   // no -0: the sign bit is beta < 0
+            sgn = __builtin_amdgcn_alignbit(sgn, __float_as_uint(b), 31);
+            cut = __builtin_amdgcn_alignbit(cut, __float_as_uint(kClip - fabsf(b)), 31);
+            const float m = fminf(fabsf(b), kClip);
+            const bool lt1 = m < m1, lt2 = m < m2;
+            i2 = lt1 ? i1 : lt2 ? k : i2;
+            i1 = lt1 ? k : i1;
+            m2 = __builtin_amdgcn_fmed3f(m, m1, m2);
+            m1 = fminf(m, m1);
+        }
+        par = (uint32_t)__builtin_popcount(sgn) & 1u;
+        flip = (sgn ^ (0u - par)) & ((1u << DC) - 1u);
+        edges = (uint32_t)i1 | (uint32_t)i2 << 5 | (~(cut >> (DC - 1 - i1)) & 1u) << 10 |
+                (~(cut >> (DC - 1 - i2)) & 1u) << 11;
+#pragma unroll
+        for (int k = 0; k < DC; ++k) {
+            const float v = fmaxf((k == i1 ? m2 : m1) - w[2 * k + 1], 0.0f);
+            x[k] = w[2 * k] * __builtin_copysignf(v, __uint_as_float(flip << (32 - DC + k)));
+        }
+    }
+    __device__ __forceinline__ void store(float* rows, int nj, int j, int p, uint32_t s4) const {
+        *tr_at(rows + (size_t)j * p, s4) = m1;
+        *tr_at(rows + (size_t)(nj + j) * p, s4) = m2;
+        if constexpr (tr_words(DC) == 3) {
+            *tr_at(rows + (size_t)(2 * nj + j) * p, s4) = __uint_as_float(edges | flip << 12 | par << 30);
+        } else {
+            *tr_at(rows + (size_t)(2 * nj + j) * p, s4) = __uint_as_float(edges);
+            *tr_at(rows + (size_t)(3 * nj + j) * p, s4) = __uint_as_float(flip | par << 30);
+        }
+    }
+};
+
 template <int NQ, int DC>
 __global__ void __launch_bounds__(1024) train_forward_kernel(const TrainArgs A) {
-    extern __shared__ float lds[];   // X [n], Y [n], loss sums [kTrWaves]
+    extern __shared__ float lds[];   // X [n], Y [n], loss sums [waves]
+    constexpr int kNJ = 3;
     const int n = A.n, p = A.p, tid = threadIdx.x, TB = blockDim.x;
     float* X = lds;
     float* Y = lds + n;
@@ -145,10 +196,10 @@ __global__ void __launch_bounds__(1024) train_forward_kernel(const TrainArgs A) 
         const uint32_t t = v4 + A.rot4[k] - (uint32_t)k * p4;
         return *tr_at(mu, (uint32_t)k * p4 + min(t, t - p4));
     };
-    float al[kTrRows][NQ][DC];   // beta (before the clip) or alpha of the thread's edges
+    float al[kNJ][NQ][DC];   // beta (before the clip) or alpha of the thread's edges
     float mu0[NQ][DC];           // channel LLRs of base row 0's edges
 #pragma unroll
-    for (int j = 0; j < kTrRows; ++j)
+    for (int j = 0; j < kNJ; ++j)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const uint32_t s4 = 4u * (uint32_t)tid + (uint32_t)q * TB4;
@@ -163,43 +214,18 @@ __global__ void __launch_bounds__(1024) train_forward_kernel(const TrainArgs A) 
     for (int t = 1; t <= A.T; ++t) {
         uint32_t tid4 = 4u * (uint32_t)tid;
         asm volatile("" : "+v"(tid4));   // the edges' variables are worked out again, not held
-        float* rows = A.rows + (f * A.T + (t - 1)) * 9 * (size_t)p;
+        float* rows = A.rows + (f * A.T + (t - 1)) * (3 * kNJ) * (size_t)p;
         // check rows
 #pragma unroll
-        for (int j = 0; j < kTrRows; ++j) {
-            const float* w = A.w + ((size_t)(t - 1) * kTrRows + j) * DC * 2;
+        for (int j = 0; j < kNJ; ++j) {
+            const float* w = A.w + ((size_t)(t - 1) * kNJ + j) * DC * 2;
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 const uint32_t s4 = tid4 + (uint32_t)q * TB4;
                 if (s4 < p4) {
-                    float (&x)[DC] = al[j][q];
-                    float m1 = __builtin_inff(), m2 = __builtin_inff();
-                    int i1 = 0, i2 = 0;
-                    uint32_t sgn = 0, cut = 0;   // slot k's sign, whether it is clipped: bit DC - 1 - k
-#pragma unroll
-                    for (int k = 0; k < DC; ++k) {
-                        const float b = x[k] + 0.0f;   // no -0: the sign bit is beta < 0
-                        sgn = __builtin_amdgcn_alignbit(sgn, __float_as_uint(b), 31);
-                        cut = __builtin_amdgcn_alignbit(cut, __float_as_uint(kClip - fabsf(b)), 31);
-                        const float m = fminf(fabsf(b), kClip);
-                        const bool lt1 = m < m1, lt2 = m < m2;
-                        i2 = lt1 ? i1 : lt2 ? k : i2;
-                        i1 = lt1 ? k : i1;
-                        m2 = __builtin_amdgcn_fmed3f(m, m1, m2);
-                        m1 = fminf(m, m1);
-                    }
-                    const uint32_t par = (uint32_t)__builtin_popcount(sgn) & 1u;
-                    const uint32_t flip = (sgn ^ (0u - par)) & ((1u << DC) - 1u);
-                    const uint32_t word = (uint32_t)i1 | (uint32_t)i2 << 5 | (~(cut >> (DC - 1 - i1)) & 1u) << 10 |
-                                          (~(cut >> (DC - 1 - i2)) & 1u) << 11 | flip << 12 | par << 30;
-                    *tr_at(rows + (0 + j) * (size_t)p, s4) = m1;
-                    *tr_at(rows + (3 + j) * (size_t)p, s4) = m2;
-                    *tr_at(rows + (6 + j) * (size_t)p, s4) = __uint_as_float(word);
-#pragma unroll
-                    for (int k = 0; k < DC; ++k) {
-                        const float v = fmaxf((k == i1 ? m2 : m1) - w[2 * k + 1], 0.0f);
-                        x[k] = w[2 * k] * __builtin_copysignf(v, __uint_as_float(flip << (32 - DC + k)));
-                    }
+                    TrRow<DC> row;
+                    row.update(al[j][q], w);
+                    row.store(rows, kNJ, j, p, s4);
                 }
             }
         }
@@ -267,8 +293,121 @@ __global__ void __launch_bounds__(1024) train_forward_kernel(const TrainArgs A) 
     }
 }
 
-template <int NQ, int DC>
-__global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A) {
+// The same for bases of 4 rows.  One array carries the sums along the base
+// rows, downwards the suffixes and upwards the prefixes that the package form
+// adds (pre + suf), and the other holds the channel LLRs: seven steps per
+// iteration, seven barriers, whose chain bounds it.  4 x 24, 18 iterations, 223
+// frames, loss and gradients: p = 512 2580 us in the package form, 709 here; p
+// = 653 (768 threads, 31 values spilled) 3229 and 1223.
+template <int DC, int MAXT>
+__global__ void __launch_bounds__(MAXT) train_forward4_kernel(const TrainArgs A) {
+    extern __shared__ float lds[];   // X [n], channel LLRs by place [n], loss sums [waves]
+    constexpr int kNJ = 4;
+    const int n = A.n, p = A.p, tid = threadIdx.x, TB = blockDim.x;
+    float* X = lds;
+    float* M = lds + n;
+    float* part = lds + 2 * n;
+    const uint32_t p4 = 4u * (uint32_t)p;
+    const size_t f = blockIdx.x;
+    const float* __restrict__ mu = A.llr + f * n;
+    const bool own = 4u * (uint32_t)tid < p4;
+    auto var4 = [&](uint32_t s4, int j, int k) -> uint32_t {
+        if (j == 0) return (uint32_t)k * p4 + s4;
+        const uint32_t t = s4 + A.sh4[j * kTrSlots + k];
+        return (uint32_t)k * p4 + min(t, t - p4);
+    };
+    float al[kNJ][DC], sf1[DC], sf2[DC];
+    if (own) {
+        const uint32_t s4 = 4u * (uint32_t)tid;
+#pragma unroll
+        for (int k = 0; k < DC; ++k) {
+            const uint32_t t = s4 + A.rot4[k];
+            al[0][k] = *tr_at(mu, (uint32_t)k * p4 + min(t, t - p4));
+        }
+#pragma unroll
+        for (int k = 0; k < DC; ++k) *tr_at(M, (uint32_t)k * p4 + s4) = al[0][k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 1; j < kNJ; ++j)
+#pragma unroll
+        for (int k = 0; k < DC; ++k) al[j][k] = own ? *tr_at(M, var4(4u * (uint32_t)tid, j, k)) : 0.0f;
+
+    for (int t = 1; t <= A.T; ++t) {
+        float* rows = A.rows + (f * A.T + (t - 1)) * (tr_words(DC) * kNJ) * (size_t)p;
+        float* post = A.post + (f * A.T + (t - 1)) * (size_t)n;
+        if (own) {
+#pragma unroll
+            for (int j = 0; j < kNJ; ++j) {
+                TrRow<DC> row;
+                row.update(al[j], A.w + ((size_t)(t - 1) * kNJ + j) * DC * 2);
+                row.store(rows, kNJ, j, p, 4u * (uint32_t)tid);
+            }
+        }
+        // each edge of base row j: its place, worked out again at every step
+        auto each = [&](int j, auto&& act) {
+            uint32_t s4 = 4u * (uint32_t)tid;
+            asm volatile("" : "+v"(s4));
+            if (own) {
+                constexpr int B = 6;   // edges whose reads go out together
+#pragma unroll
+                for (int k0 = 0; k0 < DC; k0 += B) {
+                    uint32_t v[B];
+                    float x[B];
+#pragma unroll
+                    for (int i = 0; i < B; ++i) {
+                        v[i] = var4(s4, j, k0 + i);
+                        x[i] = *tr_at(X, v[i]);
+                    }
+#pragma unroll
+                    for (int i = 0; i < B; ++i) act(k0 + i, v[i], x[i]);
+                }
+            }
+        };
+        if (own) {
+#pragma unroll
+            for (int k = 0; k < DC; ++k) *tr_at(X, var4(4u * (uint32_t)tid, 3, k)) = al[3][k];
+        }
+        __syncthreads();
+        each(2, [&](int k, uint32_t v, float x) { sf2[k] = x; *tr_at(X, v) = x + al[2][k]; });
+        __syncthreads();
+        each(1, [&](int k, uint32_t v, float x) { sf1[k] = x; *tr_at(X, v) = x + al[1][k]; });
+        __syncthreads();
+        each(0, [&](int k, uint32_t v, float x) {
+            *tr_at(X, v) = al[0][k];
+            al[0][k] = *tr_at(M, v) + x;
+        });
+        __syncthreads();
+        each(1, [&](int k, uint32_t v, float x) {
+            *tr_at(X, v) = x + al[1][k];
+            al[1][k] = *tr_at(M, v) + (x + sf1[k]);
+        });
+        __syncthreads();
+        each(2, [&](int k, uint32_t v, float x) {
+            *tr_at(X, v) = x + al[2][k];
+            al[2][k] = *tr_at(M, v) + (x + sf2[k]);
+        });
+        __syncthreads();
+        float lsum = 0.0f;
+        each(3, [&](int k, uint32_t v, float x) {
+            const float m = *tr_at(M, v), L = m + (x + al[3][k]);
+            *tr_at(post, v) = L;
+            lsum += softplus_neg_tr(L);
+            al[3][k] = m + x;
+        });
+        lsum = wave_sum_all(lsum);
+        if ((tid & 63) == 0) part[tid >> 6] = lsum;
+        __syncthreads();
+        if (tid == 0) {
+            float sum = 0.0f;
+            for (int i = 0; i < TB / 64; ++i) sum += part[i];
+            A.lpart[(size_t)(t - 1) * A.gamma + f] = sum;
+        }
+    }
+}
+
+template <int kNJ, int NQ, int DC, int MAXT>
+__global__ void __launch_bounds__(MAXT) train_backward_kernel(const TrainArgs A) {
     extern __shared__ float lds[];   // two arrays of n: D of this iteration, of the one before
     constexpr int NV = (2 * DC + 3) / 4 * 4;   // (dw, db) of a base row's slots, filled up to fours
     const int n = A.n, p = A.p, tid = threadIdx.x, TB = blockDim.x;
@@ -282,17 +421,17 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
         return (uint32_t)k * p4 + min(t, t - p4);
     };
     uint32_t* shifts = reinterpret_cast<uint32_t*>(lds + 2 * n);
-    if (tid < kTrRows * DC) shifts[tid] = A.sh4[tid / DC * kTrSlots + tid % DC];
+    for (int i = tid; i < kNJ * DC; i += TB) shifts[i] = A.sh4[i / DC * kTrSlots + i % DC];
     auto var4_at = [&](uint32_t s4, int j, uint32_t k) -> uint32_t {
         if (j == 0) return k * p4 + s4;
         const uint32_t t = s4 + shifts[j * DC + k];
         return k * p4 + min(t, t - p4);
     };
     // gradients that reached the row's betas (two edges at most) and their slots
-    float g1[kTrRows][NQ], g2[kTrRows][NQ];
-    uint32_t at[kTrRows][NQ];
+    float g1[kNJ][NQ], g2[kNJ][NQ];
+    uint32_t at[kNJ][NQ];
 #pragma unroll
-    for (int j = 0; j < kTrRows; ++j)
+    for (int j = 0; j < kNJ; ++j)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             g1[j][q] = g2[j][q] = 0.0f;
@@ -301,7 +440,8 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
     // what memory holds is read a step ahead: the posteriors of the iteration
     // before the next, the words of the next base row
     float L[NQ][DC], m1[NQ], m2[NQ];
-    uint32_t word[NQ];
+    constexpr int kWords = tr_words(DC);
+    uint32_t word[NQ], signs[NQ];
     auto load_posteriors = [&](int t, uint32_t tid4) {
         const float* post = A.post + (f * A.T + (t - 1)) * (size_t)n;
 #pragma unroll
@@ -312,16 +452,17 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
         }
     };
     auto load_rows = [&](int t, int j, uint32_t tid4) {
-        const float* rows = A.rows + (f * A.T + (t - 1)) * 9 * (size_t)p;
+        const float* rows = A.rows + (f * A.T + (t - 1)) * (kWords * kNJ) * (size_t)p;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const uint32_t s4 = tid4 + (uint32_t)q * TB4;
             m1[q] = m2[q] = 0.0f;
-            word[q] = 0u;
+            word[q] = signs[q] = 0u;
             if (s4 < p4) {
-                m1[q] = *tr_at(rows + (0 + j) * (size_t)p, s4);
-                m2[q] = *tr_at(rows + (3 + j) * (size_t)p, s4);
-                word[q] = __float_as_uint(*tr_at(rows + (6 + j) * (size_t)p, s4));
+                m1[q] = *tr_at(rows + (size_t)j * p, s4);
+                m2[q] = *tr_at(rows + (size_t)(kNJ + j) * p, s4);
+                word[q] = __float_as_uint(*tr_at(rows + (size_t)(2 * kNJ + j) * p, s4));
+                if (kWords == 4) signs[q] = __float_as_uint(*tr_at(rows + (size_t)(3 * kNJ + j) * p, s4));
             }
         }
     };
@@ -353,17 +494,18 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
         }
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kTrRows; ++j) {
-            const float* w = A.w + ((size_t)(t - 1) * kTrRows + j) * DC * 2;
+        for (int j = 0; j < kNJ; ++j) {
+            const float* w = A.w + ((size_t)(t - 1) * kNJ + j) * DC * 2;
             float c1[NQ], c2[NQ];
-            uint32_t cw[NQ];
+            uint32_t cw[NQ], cs[NQ];   // edges; flip in the low bits, par in bit 30 (18)
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 c1[q] = m1[q];
                 c2[q] = m2[q];
                 cw[q] = word[q];
+                cs[q] = kWords == 4 ? signs[q] : word[q] >> 12;
             }
-            if (j + 1 < kTrRows)
+            if (j + 1 < kNJ)
                 load_rows(t, j + 1, tid4);
             else if (t > 1)
                 load_rows(t - 1, 0, tid4);
@@ -374,7 +516,7 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
             for (int q = 0; q < NQ; ++q) {
                 const uint32_t s4 = tid4 + (uint32_t)q * TB4;
                 if (s4 < p4) {
-                    const uint32_t i1 = cw[q] & 31u, i2 = cw[q] >> 5 & 31u, flip = cw[q] >> 12;
+                    const uint32_t i1 = cw[q] & 31u, i2 = cw[q] >> 5 & 31u, flip = cs[q];
                     const uint32_t o1 = at[j][q] & 31u, o2 = at[j][q] >> 5 & 31u;
                     float D[DC];
 #pragma unroll
@@ -396,7 +538,7 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
                     }
                     // the minimum's gradient to the edge that holds it (the second
                     // minimum's for that edge's own output), unless clipped
-                    const uint32_t par = cw[q] >> 30 & 1u;
+                    const uint32_t par = cs[q] >> (kWords == 4 ? 30 : 18) & 1u;
                     const uint32_t n1 = (flip >> (DC - 1 - i1) & 1u) ^ par, n2 = (flip >> (DC - 1 - i2) & 1u) ^ par;
                     float r1 = (cw[q] >> 10 & 1u) && c1[q] != 0.0f ? G1 : 0.0f;
                     float r2 = (cw[q] >> 11 & 1u) && c2[q] != 0.0f ? G2 : 0.0f;
@@ -414,7 +556,7 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
                 }
             }
             wave_sums<NV>(sum);
-            float* part = A.gpart + (((size_t)(t - 1) * A.gamma + f) * kTrWaves + (tid >> 6)) * (kTrRows * DC * 2) +
+            float* part = A.gpart + (((size_t)(t - 1) * A.gamma + f) * A.waves + (tid >> 6)) * (kNJ * DC * 2) +
                           j * DC * 2;
             if ((tid & 63) < 4) {
 #pragma unroll
@@ -428,14 +570,14 @@ __global__ void __launch_bounds__(1024) train_backward_kernel(const TrainArgs A)
 }
 
 // grad[t][b] = sum of the wavefronts' partial sums over the frames, in a fixed
-// order; grid (3 DC, T).
-__global__ void __launch_bounds__(256) train_grad_kernel(const TrainArgs A, int waves, int blocks, float* grad) {
+// order; grid (blocks, T).
+__global__ void __launch_bounds__(256) train_grad_kernel(const TrainArgs A, int blocks, float* grad) {
     __shared__ float sw[256], sb[256];
     const int b = blockIdx.x, t = blockIdx.y;
-    const float2* part = reinterpret_cast<const float2*>(A.gpart) + (size_t)t * A.gamma * kTrWaves * blocks + b;
+    const float2* part = reinterpret_cast<const float2*>(A.gpart) + (size_t)t * A.gamma * A.waves * blocks + b;
     float aw = 0.0f, ab = 0.0f;
-    for (int i = threadIdx.x; i < A.gamma * waves; i += 256) {
-        const float2 v = part[((size_t)(i / waves) * kTrWaves + i % waves) * blocks];
+    for (int i = threadIdx.x; i < A.gamma * A.waves; i += 256) {
+        const float2 v = part[(size_t)i * blocks];
         aw += v.x;
         ab += v.y;
     }
@@ -475,19 +617,25 @@ __global__ void __launch_bounds__(256) train_loss_kernel(const TrainArgs A, floa
 namespace {
 
 struct TrainVariant {
-    int nq, dc;
+    int nj, nq, dc, maxt;
     const void *forward, *backward;
 };
 
 template <int NQ, int DC>
 constexpr TrainVariant train() {
-    return TrainVariant{NQ, DC, reinterpret_cast<const void*>(&train_forward_kernel<NQ, DC>),
-                        reinterpret_cast<const void*>(&train_backward_kernel<NQ, DC>)};
+    return TrainVariant{3, NQ, DC, 1024, reinterpret_cast<const void*>(&train_forward_kernel<NQ, DC>),
+                        reinterpret_cast<const void*>(&train_backward_kernel<3, NQ, DC, 1024>)};
+}
+template <int DC, int MAXT>
+constexpr TrainVariant train4() {
+    return TrainVariant{4, 1, DC, MAXT, reinterpret_cast<const void*>(&train_forward4_kernel<DC, MAXT>),
+                        reinterpret_cast<const void*>(&train_backward_kernel<4, 1, DC, MAXT>)};
 }
 
-// 54 edges per thread at most
-const TrainVariant kTrain[] = {train<1, 6>(), train<2, 6>(), train<3, 6>(), train<1, 9>(), train<2, 9>(),
-                               train<1, 18>()};
+// 54 edges per thread at most; of 4-row bases 96, with fewer threads and more
+// registers for each
+const TrainVariant kTrain[] = {train<1, 6>(), train<2, 6>(), train<3, 6>(), train<1, 9>(),
+                               train<2, 9>(), train<1, 18>(), train4<24, 512>(), train4<24, 768>()};
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -496,7 +644,7 @@ size_t lds_bytes(const QCDesc& D) { return (2 * (size_t)D.n + kTrRows * kTrSlots
 
 const TrainVariant* covered(const ldpc_graph* g) {
     const QCDesc& D = g->qc;
-    if (g->kind != LDPC_GRAPH_QC || D.J != kTrRows) return nullptr;
+    if (g->kind != LDPC_GRAPH_QC) return nullptr;
     for (int j = 0; j < D.J; ++j)
         if (D.rstart[j + 1] - D.rstart[j] != D.L) return nullptr;   // a zero block
     int dev = 0, limit = 0;
@@ -507,7 +655,7 @@ const TrainVariant* covered(const ldpc_graph* g) {
     }
     if (lds_bytes(D) > (size_t)limit) return nullptr;
     for (const TrainVariant& v : kTrain)
-        if (v.dc == D.L && (D.p + v.nq - 1) / v.nq <= 1024) return &v;
+        if (v.nj == D.J && v.dc == D.L && (D.p + v.nq - 1) / v.nq <= v.maxt) return &v;
     return nullptr;
 }
 
@@ -515,21 +663,23 @@ struct TrainSpace {
     size_t rows, post, lpart, gpart, total;
 };
 
-TrainSpace train_space(const QCDesc& D, int gamma, int T) {
+int threads(const TrainVariant& v, const QCDesc& D) { return ((D.p + v.nq - 1) / v.nq + 63) / 64 * 64; }
+
+TrainSpace train_space(const TrainVariant& v, const QCDesc& D, int gamma, int T) {
     TrainSpace S{};
     size_t off = 0;
     auto take = [&](size_t floats) { size_t o = off; off = align256(off + floats * sizeof(float)); return o; };
-    S.rows = take((size_t)gamma * T * 9 * D.p);
+    S.rows = take((size_t)gamma * T * tr_words(v.dc) * D.J * D.p);
     S.post = take((size_t)gamma * T * D.n);
     S.lpart = take((size_t)gamma * T);
-    S.gpart = take((size_t)gamma * T * kTrWaves * D.nb * 2);
+    S.gpart = take((size_t)gamma * T * (threads(v, D) / 64) * D.nb * 2);
     S.total = off;
     return S;
 }
 
-TrainArgs train_args(const ldpc_graph* g, int gamma, int T, const float* w, void* ws) {
+TrainArgs train_args(const TrainVariant& v, const ldpc_graph* g, int gamma, int T, const float* w, void* ws) {
     const QCDesc& D = g->qc;
-    const TrainSpace S = train_space(D, gamma, T);
+    const TrainSpace S = train_space(v, D, gamma, T);
     char* base = reinterpret_cast<char*>(ws);
     TrainArgs A{};
     A.w = w;
@@ -542,14 +692,13 @@ TrainArgs train_args(const ldpc_graph* g, int gamma, int T, const float* w, void
     A.p = D.p;
     A.T = T;
     A.gamma = gamma;
+    A.waves = threads(v, D) / 64;
     for (int j = 0; j < D.J; ++j)
         for (int k = 0; k < D.L; ++k)
             A.sh4[j * kTrSlots + k] = 4u * (uint32_t)((D.eshift[D.rstart[j] + k] - D.eshift[k] + D.p) % D.p);
     for (int k = 0; k < D.L; ++k) A.rot4[k] = 4u * (uint32_t)D.eshift[k];
     return A;
 }
-
-int threads(const TrainVariant& v, const QCDesc& D) { return ((D.p + v.nq - 1) / v.nq + 63) / 64 * 64; }
 
 bool launch(const void* fn, const ldpc_graph* g, const TrainVariant& v, TrainArgs& A, hipStream_t st) {
     const size_t lds = lds_bytes(g->qc);
@@ -561,14 +710,15 @@ bool launch(const void* fn, const ldpc_graph* g, const TrainVariant& v, TrainArg
 }  // namespace
 
 size_t train_onchip_bytes(const ldpc_graph* g, int gamma, int T) {
-    return covered(g) ? train_space(g->qc, gamma, T).total : 0;
+    const TrainVariant* v = covered(g);
+    return v ? train_space(*v, g->qc, gamma, T).total : 0;
 }
 
 bool train_onchip_forward(const ldpc_graph* g, const float* llr, int gamma, int T, const float* w, float* loss,
                           void* ws, hipStream_t st) {
     const TrainVariant* v = covered(g);
     if (!v) return false;
-    TrainArgs A = train_args(g, gamma, T, w, ws);
+    TrainArgs A = train_args(*v, g, gamma, T, w, ws);
     A.llr = llr;
     {
         timing::Scope ts(12, st);
@@ -583,15 +733,14 @@ bool train_onchip_backward(const ldpc_graph* g, int gamma, int T, const float* w
                            void* ws, hipStream_t st) {
     const TrainVariant* v = covered(g);
     if (!v) return false;
-    TrainArgs A = train_args(g, gamma, T, w, ws);
+    TrainArgs A = train_args(*v, g, gamma, T, w, ws);
     A.dloss = dloss;
     {
         timing::Scope ts(15, st);
         if (!launch(v->backward, g, *v, A, st)) return false;
     }
     timing::Scope ts(16, st);
-    train_grad_kernel<<<dim3((unsigned)g->qc.nb, (unsigned)T), 256, 0, st>>>(A, threads(*v, g->qc) / 64, g->qc.nb,
-                                                                             grad);
+    train_grad_kernel<<<dim3((unsigned)g->qc.nb, (unsigned)T), 256, 0, st>>>(A, g->qc.nb, grad);
     return hipGetLastError() == hipSuccess;
 }
 

@@ -1,6 +1,6 @@
 """Loss and gradient of the learned min-sum training step with a frame on one
 compute unit, against the FP64 reference with the tolerances of test_gpu_nnms:
-1, 2 and 3 rows per thread and base row, rows of weight 6, 9 and 18, circulant
+1, 2 and 3 rows per thread and base row, rows of weight 6, 9, 18 and 24, circulant
 sizes below, at and past a wavefront and a workgroup, and weights of either
 sign."""
 import numpy as np
@@ -18,16 +18,18 @@ pytestmark = pytest.mark.gpu
 CASES = [(6, 1, 3, 4), (6, 64, 5, 6), (6, 65, 3, 3), (6, 1024, 2, 3), (6, 1025, 2, 3), (6, 2049, 2, 4), (6, 3072, 2, 3),
          (9, 63, 5, 5), (9, 1024, 2, 3), (9, 1025, 2, 3), (9, 2048, 2, 3), (18, 36, 4, 4), (18, 129, 3, 5),
          (18, 1024, 2, 3)]
+FOUR_ROWS = [(24, 5, 3, 3), (24, 64, 3, 4), (24, 65, 2, 3), (24, 194, 2, 5), (24, 512, 2, 3),
+             (24, 513, 2, 3), (24, 768, 2, 3)]
 
 
-@pytest.mark.parametrize("L,p,gamma,T", CASES)
-def test_loss_and_gradient(L, p, gamma, T):
-    a = np.random.default_rng(L + p).integers(0, p, size=(3, L))
+@pytest.mark.parametrize("J,L,p,gamma,T", [(3,) + c for c in CASES] + [(4,) + c for c in FOUR_ROWS])
+def test_loss_and_gradient(J, L, p, gamma, T):
+    a = np.random.default_rng(L + p).integers(0, p, size=(J, L))
     a[0, 0], a[1, 1], a[2, L - 1] = 0, p - 1, p - 1
-    ebn0 = {6: 1.75, 9: 2.5, 18: 3.75}[L]
-    llr = synth.bpsk_awgn_llr(None, synth.ebn0_to_sigma2(ebn0, 1.0 - 3 / L), 600 + p, gamma=gamma, n=L * p)
+    ebn0 = {6: 1.75, 9: 2.5, 18: 3.75, 24: 3.75}[L]
+    llr = synth.bpsk_awgn_llr(None, synth.ebn0_to_sigma2(ebn0, 1.0 - J / L), 600 + p, gamma=gamma, n=L * p)
     llr[0, :L * p // 2] *= 20.0       # messages beyond the clip
-    w = rand_weights(T, 3 * L, 21)
+    w = rand_weights(T, J * L, 21)
     w[T - 1, 1, 0] = -0.5
     coef = np.linspace(0.5, 1.5, T)
     g = ldpc.Graph.qc(a, p)
@@ -40,4 +42,4 @@ def test_loss_and_gradient(L, p, gamma, T):
     np.testing.assert_allclose(loss, per, rtol=1e-5)
     _, gw, gb = ref_nnms.grad(G, llr.astype(np.float64), x, w[..., 0].astype(np.float64),
                               w[..., 1].astype(np.float64), T, coef=coef)
-    check_grad(grad, gw, gb, f"3x{L} p={p}")
+    check_grad(grad, gw, gb, f"{J}x{L} p={p}")
