@@ -70,7 +70,8 @@ struct OnchipArgs {
     // edge slot k of base row j (index j * kOcSlots + k): row (j, s) meets
     // variable l*p + (s + a) mod p of base column l; held as byte offsets
     // into the LDS posterior pairs (8 bytes per variable): cb8 = 8 l p and
-    // sh8 = 8 a
+    // sh8 = 8 a; with a column's sums in two runs (oc_split), 4 bytes per
+    // variable: cb8 = 8 l P and sh8 = 4 a
     int32_t cb8[kOcRows * kOcSlots];
     int32_t sh8[kOcRows * kOcSlots];
     // regular bases with rows of weight <= 6 (oc_mu_in_regs) store base
@@ -79,6 +80,8 @@ struct OnchipArgs {
     // l p + s (no wrap); rot8[l] = 8 a_0l, 0 otherwise, and sh8 holds the
     // shifts relative to it
     int32_t rot8[kOcSlots];
+    // first LLR of base column l in the caller's frame, as a byte offset: 4 l p
+    int32_t gb4[kOcSlots];
     int32_t deg[kOcRows];   // nonzero blocks of base row j
     uint64_t first;         // bit j * kOcSlots + k: the lowest nonzero block of its base column
     // learned min-sum (RULE 1): weights [iters][blocks][2] (scale, offset in
@@ -117,6 +120,16 @@ __device__ __forceinline__ float* lds_ptr(float2* L, uint32_t byte) {
 // the others read them from the frame's LLRs in L2 when a sum starts.
 constexpr bool oc_mu_in_regs(bool reg, int dc) { return reg && dc <= 6; }
 
+// Regular bases with 54 edges per thread, of which one workgroup fits a compute
+// unit in any case, keep a base column's sums in two runs of P cells, even
+// iterations' and odd ones', P = 1024 NQ: lanes then meet consecutive cells,
+// where one component of a pair is every second one and takes twice the cycles. 20
+// iterations of 3 x 6, p = 3060, 1024 frames 691 -> 666 us, of 3 x 9, p = 1500,
+// 600 frames 444 -> 426.
+constexpr bool oc_split(bool reg, int nq, int dc) { return reg && nq * dc == 18; }
+constexpr uint32_t oc_unit(bool reg, int nq, int dc) { return oc_split(reg, nq, dc) ? 4u : 8u; }   // bytes per variable
+constexpr uint32_t oc_odd(bool reg, int nq, int dc) { return oc_split(reg, nq, dc) ? 4096u * (uint32_t)nq : 4u; }
+
 // One iteration: PAR = it & 1.  L of iteration i lives in component i & 1 of
 // each variable's pair, so this iteration reads component 1 - PAR (the
 // previous iteration's sums) and accumulates into component PAR; both are
@@ -130,7 +143,7 @@ __device__ __forceinline__ void oc_iteration(const OnchipArgs& A, float2* L, con
                                              float (&al)[NJ][NQ][DC], const float (&mu0)[NQ][DC], uint32_t tid8,
                                              uint32_t TB8, uint32_t p8, uint32_t* flag, const float* wit) {
     uint64_t viol = 0;
-    constexpr uint32_t kOld = 4u * (1 - PAR), kNew = 4u * PAR;
+    constexpr uint32_t kOdd = oc_odd(REG, NQ, DC), kOld = kOdd * (1 - PAR), kNew = kOdd * PAR;
     constexpr bool kMuInRegs = oc_mu_in_regs(REG, DC);
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
@@ -177,9 +190,11 @@ __device__ __forceinline__ void oc_iteration(const OnchipArgs& A, float2* L, con
                         if (first && kMuInRegs) {
                             acc[k] = mu0[q][k];
                         } else if (first) {
-                            // mu of variable v at byte 4 v of the frame (va = 8 v)
-                            const float m = *reinterpret_cast<const float*>(
-                                reinterpret_cast<const char*>(mu) + (va[k] >> 1));
+                            // mu of variable v at byte 4 v of the frame (va = 8 v,
+                            // or 4 bytes per cell of a full base's column k)
+                            const uint32_t at = oc_split(REG, NQ, DC) ? va[k] - (uint32_t)A.cb8[k] + (uint32_t)A.gb4[k]
+                                                                  : va[k] >> 1;
+                            const float m = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(mu) + at);
                             acc[k] = m * kLog2eF + 0.0f;
                         } else {
                             acc[k] = lds_at(L, va[k] + kNew);
@@ -212,12 +227,14 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
     // dynamic LDS: [n] posterior pairs (L of even iterations, L of odd
     // iterations), then three flag words
     extern __shared__ float2 Lpair[];
-    uint32_t* flag = reinterpret_cast<uint32_t*>(Lpair + n);
+    constexpr bool kSplit = oc_split(REG, NQ, DC);
+    constexpr uint32_t kUnit = oc_unit(REG, NQ, DC), kOdd = oc_odd(REG, NQ, DC);
+    uint32_t* flag = reinterpret_cast<uint32_t*>(Lpair + (kSplit ? DC * 1024 * NQ : n));
     const int tid = threadIdx.x;
     const int TB = blockDim.x;
     const size_t f0 = (size_t)blockIdx.x * n;
     const float* __restrict__ mu = A.llr + f0;
-    const uint32_t p8 = 8u * (uint32_t)p, TB8 = 8u * (uint32_t)TB;
+    const uint32_t p8 = kUnit * (uint32_t)p, TB8 = kUnit * (uint32_t)TB;
     float mu0[NQ][DC];
     // L of "iteration 0" is mu, so that iteration 1 reads beta = clip(mu - 0)
     if constexpr (oc_mu_in_regs(REG, DC)) {
@@ -226,19 +243,19 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
         // l of a full base row 0 is column l's)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+            const uint32_t s8 = kUnit * (uint32_t)tid + (uint32_t)q * TB8;
 #pragma unroll
             for (int l = 0; l < DC; ++l) {
                 mu0[q][l] = 0.0f;
                 if (s8 < p8)
                     mu0[q][l] = *reinterpret_cast<const float*>(
                                     reinterpret_cast<const char*>(mu) +
-                                    ((A.cb8[l] + oc_wrap8(s8 + A.rot8[l], p8)) >> 1)) * kLog2eF + 0.0f;
+                                    (A.gb4[l] + oc_wrap8(s8 + A.rot8[l], p8) / (kUnit / 4))) * kLog2eF + 0.0f;
             }
         }
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+            const uint32_t s8 = kUnit * (uint32_t)tid + (uint32_t)q * TB8;
 #pragma unroll
             for (int l = 0; l < DC; ++l)
                 if (s8 < p8) *lds_ptr(Lpair, A.cb8[l] + s8) = mu0[q][l];
@@ -250,7 +267,8 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
 #pragma unroll
                 for (int l = 0; l < DC; ++l) m[l] = mu[l * p + u];
 #pragma unroll
-                for (int l = 0; l < DC; ++l) Lpair[l * p + u].x = m[l] * kLog2eF + 0.0f;
+                for (int l = 0; l < DC; ++l)
+                    *lds_ptr(Lpair, (uint32_t)A.cb8[l] + kUnit * (uint32_t)u) = m[l] * kLog2eF + 0.0f;
             }
         } else {
             for (int v = tid; v < n; v += TB) Lpair[v].x = mu[v] * kLog2eF + 0.0f;
@@ -274,7 +292,7 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
         // the edges' offsets do not change between iterations, but holding
         // them would take as many registers as the alphas: the thread index
         // passes through an opaque copy so that they are recomputed
-        uint32_t tid8 = 8u * (uint32_t)tid;
+        uint32_t tid8 = kUnit * (uint32_t)tid;
         asm volatile("" : "+v"(tid8));
         const bool syn = SYN && it >= 2;
         if (tid == 0) flag[(it + 1) % 3] = 0u;
@@ -322,13 +340,13 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
             const int d = REG ? DC : A.deg[j];
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+                const uint32_t s8 = kUnit * (uint32_t)tid + (uint32_t)q * TB8;
                 if (s8 < p8) {
                     uint64_t par = 0;
 #pragma unroll
                     for (int k = 0; k < DC; ++k)
                         if (REG || k < d)
-                            par ^= __ballot(lds_at(Lpair, oc_pair(A, j * kOcSlots + k, s8, p8) + 4u * comp) < 0.0f);
+                            par ^= __ballot(lds_at(Lpair, oc_pair(A, j * kOcSlots + k, s8, p8) + kOdd * comp) < 0.0f);
                     viol |= par;
                 }
             }
@@ -342,25 +360,24 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
     if constexpr (oc_mu_in_regs(REG, DC)) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-            const uint32_t s8 = 8u * (uint32_t)tid + (uint32_t)q * TB8;
+            const uint32_t s8 = kUnit * (uint32_t)tid + (uint32_t)q * TB8;
             if (s8 >= p8) continue;
             uint32_t v[DC];
             float m[DC];
 #pragma unroll
             for (int l = 0; l < DC; ++l) {
-                v[l] = (A.cb8[l] + oc_wrap8(s8 + A.rot8[l], p8)) >> 3;
+                v[l] = ((uint32_t)A.gb4[l] + oc_wrap8(s8 + A.rot8[l], p8) / (kUnit / 4)) >> 2;
                 m[l] = mu[v[l]];
             }
 #pragma unroll
             for (int l = 0; l < DC; ++l) {
-                const float x = lds_at(Lpair, A.cb8[l] + s8 + 4u * (uint32_t)comp);
+                const float x = lds_at(Lpair, A.cb8[l] + s8 + kOdd * (uint32_t)comp);
                 A.post[f0 + v[l]] = unscale2(x, m[l]);
                 A.bits[f0 + v[l]] = (uint8_t)(x < 0.0f);
             }
         }
     } else {
-        auto put = [&](int v, float m) {
-            const float x = Lf[2 * v + comp];
+        auto put = [&](int v, float x, float m) {
             A.post[f0 + v] = unscale2(x, m);
             A.bits[f0 + v] = (uint8_t)(x < 0.0f);
         };
@@ -370,10 +387,12 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
 #pragma unroll
                 for (int l = 0; l < DC; ++l) m[l] = mu[l * p + u];
 #pragma unroll
-                for (int l = 0; l < DC; ++l) put(l * p + u, m[l]);
+                for (int l = 0; l < DC; ++l)
+                    put(l * p + u, lds_at(Lpair, (uint32_t)A.cb8[l] + kUnit * (uint32_t)u + kOdd * (uint32_t)comp),
+                        m[l]);
             }
         } else {
-            for (int v = tid; v < n; v += TB) put(v, mu[v]);
+            for (int v = tid; v < n; v += TB) put(v, Lf[2 * v + comp], mu[v]);
         }
     }
     if (tid == 0) {
@@ -444,8 +463,11 @@ bool choose(const ldpc_graph* g, int rule, Choice& c) {
         (void)hipGetLastError();
         return false;
     }
-    const size_t lds = (size_t)D.n * sizeof(float2) + 3 * sizeof(uint32_t);   // pairs, flags
-    if (lds > (size_t)limit) return false;
+    // pairs, or two runs of 1024 NQ cells per column; flags
+    auto bytes = [&](const Variant& v) {
+        const size_t cells = oc_split(v.reg, v.nq, v.dc) ? (size_t)v.dc * 1024 * v.nq : (size_t)D.n;
+        return cells * sizeof(float2) + 3 * sizeof(uint32_t);
+    };
     const Variant* best = nullptr;
     int best_tb = 0;
     for (const Variant& v : kVariants) {
@@ -453,7 +475,7 @@ bool choose(const ldpc_graph* g, int rule, Choice& c) {
         if (v.reg && !(reg && v.dc == D.dc_max)) continue;
         const int per = (D.p + v.nq - 1) / v.nq;
         const int tb = (per + 63) / 64 * 64;
-        if (tb > v.maxt) continue;
+        if (tb > v.maxt || bytes(v) > (size_t)limit) continue;
         // fewest rows per thread, then a regular variant, then the smallest row-weight capacity
         const bool better = !best || v.nq < best->nq ||
                             (v.nq == best->nq && (v.reg > best->reg || (v.reg == best->reg && v.dc < best->dc)));
@@ -465,7 +487,7 @@ bool choose(const ldpc_graph* g, int rule, Choice& c) {
     if (!best) return false;
     c.v = best;
     c.tb = best_tb;
-    c.lds = lds;
+    c.lds = bytes(*best);
     return true;
 }
 
@@ -508,14 +530,19 @@ int onchip_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iter
     int rot[kOcSlots] = {0};
     if (oc_mu_in_regs(c.v->reg, c.v->dc))
         for (int k = 0; k < D.rstart[1]; ++k) rot[D.ecol[k]] = D.eshift[k];
-    for (int l = 0; l < kOcSlots; ++l) A.rot8[l] = 8 * rot[l];
+    const bool split = oc_split(c.v->reg, c.v->nq, c.v->dc);
+    const int unit = (int)oc_unit(c.v->reg, c.v->nq, c.v->dc);
+    for (int l = 0; l < kOcSlots; ++l) {
+        A.rot8[l] = unit * rot[l];
+        A.gb4[l] = 4 * l * D.p;
+    }
     for (int j = 0; j < D.J; ++j) {
         A.deg[j] = D.rstart[j + 1] - D.rstart[j];
         A.rb0[j] = D.rstart[j];
         for (int k = 0; k < A.deg[j]; ++k) {
             const int b = D.rstart[j] + k;
-            A.cb8[j * kOcSlots + k] = 8 * D.ecol[b] * D.p;
-            A.sh8[j * kOcSlots + k] = 8 * ((D.eshift[b] - rot[D.ecol[b]] + D.p) % D.p);
+            A.cb8[j * kOcSlots + k] = 8 * D.ecol[b] * (split ? 1024 * c.v->nq : D.p);
+            A.sh8[j * kOcSlots + k] = unit * ((D.eshift[b] - rot[D.ecol[b]] + D.p) % D.p);
             if (D.cedge[D.cstart[D.ecol[b]]] == b)   // edge blocks of a column ascend by base row
                 A.first |= 1ull << (j * kOcSlots + k);
         }
