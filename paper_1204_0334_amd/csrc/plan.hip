@@ -1326,12 +1326,20 @@ int persist_items_per_ticket() {
     return v >= 1 && v <= 64 ? v : 2;
 }
 
+// Whether code c is decoded on several compute units: its words fit the region
+// that the plan was created with (under another LDPC_BLOCK_PATH, perhaps).
+bool spread_fits(const ldpc_plan* P, int c) {
+    const size_t need = spread_bytes(P->graphs[c], P->gammas[c]);
+    return need > 0 && need <= P->region_bytes[c];
+}
+
 // fill the host table for the current layouts and buffers
 std::vector<uint8_t> onchip_choice(const ldpc_plan* P) {
     std::vector<uint8_t> v(P->ncodes, 0);
     if (!P->persistent)
-        for (int c = 0; c < P->ncodes; ++c) v[c] = onchip_selected(P->graphs[c]) || small_selected(P->graphs[c], P->gammas[c]) ||
-                           spread_bytes(P->graphs[c], P->gammas[c]) ? 1 : 0;
+        for (int c = 0; c < P->ncodes; ++c)
+            v[c] = onchip_selected(P->graphs[c]) || small_selected(P->graphs[c], P->gammas[c]) || spread_fits(P, c)
+                       ? 1 : 0;
     return v;
 }
 
@@ -1359,7 +1367,7 @@ void deal_onchip(ldpc_plan* P) {
             phases = std::max(phases, 3.6 * (2 * P->max_iters + 5)) + 1e-5 * g->E * P->gammas[c] * iters;
             continue;
         }
-        cost[c] = spread_bytes(g, P->gammas[c]) ? 20.0 + 8.0 * iters
+        cost[c] = spread_fits(P, c) ? 20.0 + 8.0 * iters
                                                 : 12.0 + 0.2e-3 * g->E * iters * ((P->gammas[c] + 255) / 256);
         total += cost[c];
         order.push_back(c);

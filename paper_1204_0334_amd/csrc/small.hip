@@ -191,7 +191,7 @@ const SmallVariant kSmall[] = {small<4, 4>(),  small<4, 16>(),  small<6, 4>(),  
 constexpr int kSmallEdges = 8192;
 
 const SmallVariant* choose_small(const ldpc_graph* g, int gamma, size_t& lds) {
-    if (!g || g->kind != LDPC_GRAPH_QC || g->qc.E > kSmallEdges || onchip_fits(g)) return nullptr;
+    if (!g || g->kind != LDPC_GRAPH_QC || g->qc.E == 0 || g->qc.E > kSmallEdges || onchip_fits(g)) return nullptr;
     if (g->qc.dv_max > 4 && gamma > 256) return nullptr;
     const char* path = std::getenv("LDPC_BLOCK_PATH");
     if (path && std::strcmp(path, "packages") == 0) return nullptr;
