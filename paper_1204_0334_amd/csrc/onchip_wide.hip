@@ -14,8 +14,8 @@
 //   * Addresses without a wrap.  The rows of a wavefront are consecutive, so
 //     the variables an edge slot meets are consecutive in a base column up to
 //     one wrap.  Every column is stored with 64 further cells behind its p
-//     sums, so a wavefront's 64 variables are one run of cells from a base
-//     that the scalar unit computes: one vector operation per edge.  While
+//     sums, so a wavefront's 64 variables are one run of cells, whose first
+//     cell one lane holds for all: one vector operation per edge.  While
 //     sums are accumulated, a further cell takes the part of its variable's
 //     sum that arrives across the wrap; a last short step adds the two parts
 //     and writes the total to both.
@@ -27,7 +27,7 @@
 //
 // The decode is bound by the vector ALUs: about 25 plain instructions and 3
 // transcendentals per edge and iteration.  4 x 24 code, p = 1024, 1024
-// frames, 30 iterations: 2.53 ms (98,304 edges per frame: 1.19 10^12 edge
+// frames, 30 iterations: 2.45 ms (98,304 edges per frame: 1.23 10^12 edge
 // updates per second), 12.15 ms with the message-package decoder, which
 // streams every message through HBM twice an iteration.  Tried on the way
 // there: (u, w, s) triples instead of pairs, two rows per thread, 512 threads

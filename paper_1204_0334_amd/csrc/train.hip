@@ -28,11 +28,11 @@
 // (dloss/dL first, then base row by base row the two edges per row that a
 // gradient reaches).  The weight gradients are summed per wavefront in
 // registers and written once per base row and iteration.  What memory holds
-// is loaded a step ahead (without that: 1.30 ms for 1.08 below).
+// is loaded a step ahead (without that the backward pass took a fifth longer).
 //
-// 3 x 6, p = 3060, 1024 frames, 12 iterations: forward 0.87 ms, backward
-// 1.08 ms, the sums over wavefronts and frames 0.05 ms as traced; loss and
-// gradients together 1.75 ms untraced, 5.50 ms in the package form.  2.3 GB
+// 3 x 6, p = 3060, 1024 frames, 12 iterations: forward 0.76 ms, backward
+// 0.96 ms, the sums over wavefronts and frames 0.05 ms as traced; loss and
+// gradients together 1.72 ms untraced, 5.50 ms in the package form.  2.3 GB
 // pass each way, 0.45 ms at the rate of a large copy; the rest is the
 // workgroup's own arithmetic and LDS traffic between barriers, which one
 // workgroup per compute unit (147 KB of LDS) does not hide.
