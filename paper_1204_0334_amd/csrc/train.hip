@@ -27,12 +27,13 @@
 // iteration reads D from one array and forms the next one's in the other
 // (dloss/dL first, then base row by base row the two edges per row that a
 // gradient reaches).  The weight gradients are summed per wavefront in
-// registers and written once per base row and iteration.  What memory holds
+// registers, over many wavefronts in LDS, and written once per base row and
+// iteration.  What memory holds
 // is loaded a step ahead (without that the backward pass took a fifth longer).
 //
-// 3 x 6, p = 3060, 1024 frames, 12 iterations: forward 0.76 ms, backward
-// 0.96 ms, the sums over wavefronts and frames 0.05 ms as traced; loss and
-// gradients together 1.72 ms untraced, 5.50 ms in the package form.  2.3 GB
+// 3 x 6, p = 3060, 1024 frames, 12 iterations: forward 0.72 ms, backward
+// 0.90 ms as traced, the sums over frames below 0.01 ms; loss and gradients
+// together 1.62 ms untraced, 5.50 ms in the package form.  2.3 GB
 // pass each way, 0.45 ms at the rate of a large copy; the rest is the
 // workgroup's own arithmetic and LDS traffic between barriers, which one
 // workgroup per compute unit (147 KB of LDS) does not hide.
@@ -45,7 +46,7 @@
 
 namespace ldpc {
 
-constexpr int kTrRows = 4, kTrSlots = 24;
+constexpr int kTrRows = 4, kTrSlots = 24, kTrWaves = 16;
 
 // words kept per row: the minima, their edges and the signs (rows of weight
 // above 18: the signs in a word of their own)
@@ -58,9 +59,10 @@ struct TrainArgs {
     float* rows;           // [gamma][T][words][rows][p]: minimum, second minimum, edges and signs
     float* post;           // [gamma][T][n]: posteriors, by place
     float* lpart;          // [T][gamma]: loss sums
-    float* gpart;          // [T][gamma][waves][blocks][2]
+    float* gpart;          // [T][gamma][parts][blocks][2]
     float inv_count;
-    int32_t n, p, T, gamma, waves;
+    int32_t n, p, T, gamma;
+    int32_t parts;         // partial sums of a frame: one, or one per wavefront
     // Columns are kept rotated by base row 0's shifts (place l p + u holds
     // variable l p + (u + a_0l) mod p), so a row (0, s) meets the places l p +
     // s.  Edge slot k of base row j (index j * kTrSlots + k): 4 times its
@@ -406,7 +408,9 @@ __global__ void __launch_bounds__(MAXT) train_forward4_kernel(const TrainArgs A)
     }
 }
 
-template <int kNJ, int NQ, int DC, int MAXT>
+// ONE: the weight gradients of a frame in one sum (over its wavefronts, in LDS),
+// else one per wavefront.
+template <int kNJ, int NQ, int DC, int MAXT, bool ONE>
 __global__ void __launch_bounds__(MAXT) train_backward_kernel(const TrainArgs A) {
     extern __shared__ float lds[];   // two arrays of n: D of this iteration, of the one before
     constexpr int NV = (2 * DC + 3) / 4 * 4;   // (dw, db) of a base row's slots, filled up to fours
@@ -421,6 +425,8 @@ __global__ void __launch_bounds__(MAXT) train_backward_kernel(const TrainArgs A)
         return (uint32_t)k * p4 + min(t, t - p4);
     };
     uint32_t* shifts = reinterpret_cast<uint32_t*>(lds + 2 * n);
+    float* red = lds + 2 * n + kTrRows * kTrSlots;
+    int phase = 0;
     for (int i = tid; i < kNJ * DC; i += TB) shifts[i] = A.sh4[i / DC * kTrSlots + i % DC];
     auto var4_at = [&](uint32_t s4, int j, uint32_t k) -> uint32_t {
         if (j == 0) return k * p4 + s4;
@@ -556,27 +562,43 @@ __global__ void __launch_bounds__(MAXT) train_backward_kernel(const TrainArgs A)
                 }
             }
             wave_sums<NV>(sum);
-            float* part = A.gpart + (((size_t)(t - 1) * A.gamma + f) * A.waves + (tid >> 6)) * (kNJ * DC * 2) +
-                          j * DC * 2;
-            if ((tid & 63) < 4) {
+            float* part = A.gpart + ((size_t)(t - 1) * A.gamma + f) * A.parts * (kNJ * DC * 2) + j * DC * 2;
+            if constexpr (ONE) {
+                // the wavefronts' sums in LDS, two sets in turn: one is read
+                // while the next base row's are written
+                float* set = red + (phase & 1) * (kTrWaves * NV);
+                if ((tid & 63) < 4) {
 #pragma unroll
-                for (int i = 0; i < NV / 4; ++i)
-                    if (4 * i + (tid & 3) < 2 * DC) part[4 * i + (tid & 3)] = sum[i];
+                    for (int i = 0; i < NV / 4; ++i) set[(tid >> 6) * NV + 4 * i + (tid & 3)] = sum[i];
+                }
+                __syncthreads();
+                if (tid < 2 * DC) {
+                    float total = 0.0f;
+                    for (int i = 0; i < TB / 64; ++i) total += set[i * NV + tid];
+                    part[tid] = total;
+                }
+            } else {
+                part += (tid >> 6) * (kNJ * DC * 2);
+                if ((tid & 63) < 4) {
+#pragma unroll
+                    for (int i = 0; i < NV / 4; ++i)
+                        if (4 * i + (tid & 3) < 2 * DC) part[4 * i + (tid & 3)] = sum[i];
+                }
+                __syncthreads();
             }
-            __syncthreads();
+            ++phase;
         }
         cur = next;
     }
 }
 
-// grad[t][b] = sum of the wavefronts' partial sums over the frames, in a fixed
-// order; grid (blocks, T).
+// grad[t][b] = sum over the frames, in a fixed order; grid (blocks, T).
 __global__ void __launch_bounds__(256) train_grad_kernel(const TrainArgs A, int blocks, float* grad) {
     __shared__ float sw[256], sb[256];
     const int b = blockIdx.x, t = blockIdx.y;
-    const float2* part = reinterpret_cast<const float2*>(A.gpart) + (size_t)t * A.gamma * A.waves * blocks + b;
+    const float2* part = reinterpret_cast<const float2*>(A.gpart) + (size_t)t * A.gamma * A.parts * blocks + b;
     float aw = 0.0f, ab = 0.0f;
-    for (int i = threadIdx.x; i < A.gamma * A.waves; i += 256) {
+    for (int i = threadIdx.x; i < A.gamma * A.parts; i += 256) {
         const float2 v = part[(size_t)i * blocks];
         aw += v.x;
         ab += v.y;
@@ -618,18 +640,20 @@ namespace {
 
 struct TrainVariant {
     int nj, nq, dc, maxt;
-    const void *forward, *backward;
+    const void *forward, *backward[2];   // backward: one sum per wavefront (few of them), per frame
 };
 
 template <int NQ, int DC>
 constexpr TrainVariant train() {
     return TrainVariant{3, NQ, DC, 1024, reinterpret_cast<const void*>(&train_forward_kernel<NQ, DC>),
-                        reinterpret_cast<const void*>(&train_backward_kernel<3, NQ, DC, 1024>)};
+                        {reinterpret_cast<const void*>(&train_backward_kernel<3, NQ, DC, 1024, (NQ > 1)>),
+                         reinterpret_cast<const void*>(&train_backward_kernel<3, NQ, DC, 1024, true>)}};
 }
 template <int DC, int MAXT>
 constexpr TrainVariant train4() {
     return TrainVariant{4, 1, DC, MAXT, reinterpret_cast<const void*>(&train_forward4_kernel<DC, MAXT>),
-                        reinterpret_cast<const void*>(&train_backward_kernel<4, 1, DC, MAXT>)};
+                        {reinterpret_cast<const void*>(&train_backward_kernel<4, 1, DC, MAXT, (MAXT > 512)>),
+                         reinterpret_cast<const void*>(&train_backward_kernel<4, 1, DC, MAXT, true>)}};
 }
 
 // 54 edges per thread at most; of 4-row bases 96, with fewer threads and more
@@ -639,8 +663,11 @@ const TrainVariant kTrain[] = {train<1, 6>(), train<2, 6>(), train<3, 6>(), trai
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// two arrays by place, then the loss sums or the shifts
-size_t lds_bytes(const QCDesc& D) { return (2 * (size_t)D.n + kTrRows * kTrSlots) * sizeof(float); }
+// two arrays by place, then the loss sums, or the shifts and two sets of sums
+// per wavefront
+size_t lds_bytes(const QCDesc& D) {
+    return (2 * (size_t)D.n + kTrRows * kTrSlots + 2 * kTrWaves * 2 * kTrSlots) * sizeof(float);
+}
 
 const TrainVariant* covered(const ldpc_graph* g) {
     const QCDesc& D = g->qc;
@@ -665,6 +692,13 @@ struct TrainSpace {
 
 int threads(const TrainVariant& v, const QCDesc& D) { return ((D.p + v.nq - 1) / v.nq + 63) / 64 * 64; }
 
+// Partial sums of a frame's weight gradients.  One for each wavefront leaves
+// the sum over wavefronts out of the workgroup's chain of steps; one for the
+// frame saves their bytes, which count with many wavefronts.  3 x 6, p = 3060,
+// 1024 frames (16 wavefronts) 1715 and 1621 us for the step; 4 x 24, p = 194, 22
+// frames (4) 533 and 545.
+int parts(const TrainVariant& v, const QCDesc& D) { return threads(v, D) >= 512 ? 1 : threads(v, D) / 64; }
+
 TrainSpace train_space(const TrainVariant& v, const QCDesc& D, int gamma, int T) {
     TrainSpace S{};
     size_t off = 0;
@@ -672,7 +706,7 @@ TrainSpace train_space(const TrainVariant& v, const QCDesc& D, int gamma, int T)
     S.rows = take((size_t)gamma * T * tr_words(v.dc) * D.J * D.p);
     S.post = take((size_t)gamma * T * D.n);
     S.lpart = take((size_t)gamma * T);
-    S.gpart = take((size_t)gamma * T * (threads(v, D) / 64) * D.nb * 2);
+    S.gpart = take((size_t)gamma * T * parts(v, D) * D.nb * 2);
     S.total = off;
     return S;
 }
@@ -692,7 +726,7 @@ TrainArgs train_args(const TrainVariant& v, const ldpc_graph* g, int gamma, int 
     A.p = D.p;
     A.T = T;
     A.gamma = gamma;
-    A.waves = threads(v, D) / 64;
+    A.parts = parts(v, D);
     for (int j = 0; j < D.J; ++j)
         for (int k = 0; k < D.L; ++k)
             A.sh4[j * kTrSlots + k] = 4u * (uint32_t)((D.eshift[D.rstart[j] + k] - D.eshift[k] + D.p) % D.p);
@@ -737,7 +771,7 @@ bool train_onchip_backward(const ldpc_graph* g, int gamma, int T, const float* w
     A.dloss = dloss;
     {
         timing::Scope ts(15, st);
-        if (!launch(v->backward, g, *v, A, st)) return false;
+        if (!launch(v->backward[A.parts == 1 && threads(*v, g->qc) > 64 ? 1 : 0], g, *v, A, st)) return false;
     }
     timing::Scope ts(16, st);
     train_grad_kernel<<<dim3((unsigned)g->qc.nb, (unsigned)T), 256, 0, st>>>(A, g->qc.nb, grad);
