@@ -1260,6 +1260,11 @@ int default_layout(const ldpc_graph* g, int gamma) {
 // for each of a process's four hardware queues.
 constexpr int kSides = 3;
 
+// What decodes a code of a plan: the phase launches, a frame on several compute
+// units (spread.hip), on one (onchip.hip), or with its packages in LDS
+// (small.hip).
+enum CodeKernel : uint8_t { kPhases, kSpread, kOnchip, kSmall };
+
 struct ldpc_plan {
     int ncodes = 0, max_iters = 0, early = 0;
     std::vector<const ldpc_graph*> graphs;
@@ -1281,11 +1286,11 @@ struct ldpc_plan {
     int persist_grid = 0;                 // workgroups: what fits the device at once
     size_t state_off = 0;                 // PersistState in the workspace
     PersistArgs pa{};
-    // codes decoded by the on-chip block decoder (onchip.hip) instead of the
-    // phase launches: decided when the table is built (phase launches only,
-    // as ldpc_decode decides), launched on `sides` streams forked from the
-    // caller's (branch[c]: code c's)
-    std::vector<uint8_t> onchip, branch;
+    // the decoder of each code (CodeKernel), decided when the table is built as
+    // ldpc_decode decides (the phase launches in persistent mode); those of
+    // one launch per code run on `sides` streams forked from the caller's
+    // (branch[c]: code c's)
+    std::vector<uint8_t> kernel, branch;
     int sides = 0;
     hipStream_t side[kSides] = {};
     hipEvent_t fork_ev = nullptr, join_ev[kSides] = {};
@@ -1326,20 +1331,21 @@ int persist_items_per_ticket() {
     return v >= 1 && v <= 64 ? v : 2;
 }
 
-// Whether code c is decoded on several compute units: its words fit the region
-// that the plan was created with (under another LDPC_BLOCK_PATH, perhaps).
-bool spread_fits(const ldpc_plan* P, int c) {
-    const size_t need = spread_bytes(P->graphs[c], P->gammas[c]);
-    return need > 0 && need <= P->region_bytes[c];
-}
-
-// fill the host table for the current layouts and buffers
-std::vector<uint8_t> onchip_choice(const ldpc_plan* P) {
-    std::vector<uint8_t> v(P->ncodes, 0);
-    if (!P->persistent)
-        for (int c = 0; c < P->ncodes; ++c)
-            v[c] = onchip_selected(P->graphs[c]) || small_selected(P->graphs[c], P->gammas[c]) || spread_fits(P, c)
-                       ? 1 : 0;
+// The codes' decoders, in the order in which ldpc_decode takes them.  The words
+// of a frame on several units have to fit the region that the plan was created
+// with (under another LDPC_BLOCK_PATH, perhaps).
+std::vector<uint8_t> choose_kernels(const ldpc_plan* P) {
+    std::vector<uint8_t> v(P->ncodes, kPhases);
+    if (P->persistent) return v;
+    for (int c = 0; c < P->ncodes; ++c) {
+        const size_t words = spread_bytes(P->graphs[c], P->gammas[c]);
+        if (words > 0 && words <= P->region_bytes[c])
+            v[c] = kSpread;
+        else if (onchip_selected(P->graphs[c]))
+            v[c] = kOnchip;
+        else if (small_selected(P->graphs[c], P->gammas[c]))
+            v[c] = kSmall;
+    }
     return v;
 }
 
@@ -1363,12 +1369,12 @@ void deal_onchip(ldpc_plan* P) {
     double phases = 0.0;
     for (int c = 0; c < P->ncodes; ++c) {
         const ldpc_graph* g = P->graphs[c];
-        if (!P->onchip[c]) {
+        if (P->kernel[c] == kPhases) {
             phases = std::max(phases, 3.6 * (2 * P->max_iters + 5)) + 1e-5 * g->E * P->gammas[c] * iters;
             continue;
         }
-        cost[c] = spread_fits(P, c) ? 20.0 + 8.0 * iters
-                                                : 12.0 + 0.2e-3 * g->E * iters * ((P->gammas[c] + 255) / 256);
+        cost[c] = P->kernel[c] == kSpread ? 20.0 + 8.0 * iters
+                                          : 12.0 + 0.2e-3 * g->E * iters * ((P->gammas[c] + 255) / 256);
         total += cost[c];
         order.push_back(c);
     }
@@ -1385,7 +1391,7 @@ void deal_onchip(ldpc_plan* P) {
 
 void build_table(ldpc_plan* P, const PlanBuffers& B, char* ws) {
     P->table.assign(P->ncodes, PlanCode{});
-    P->onchip = onchip_choice(P);
+    P->kernel = choose_kernels(P);
     deal_onchip(P);
     int64_t cn = 0, vn = 0, syn = 0, st = 0, io = 0, red = 0;
     for (int c = 0; c < P->ncodes; ++c) {
@@ -1436,7 +1442,7 @@ void build_table(ldpc_plan* P, const PlanBuffers& B, char* ws) {
         T.io0 = io;
         T.red0 = red;
         T.red_chunks = (int)(((int64_t)T.cn_wpt * T.fpl + kPlanRedWords - 1) / kPlanRedWords);
-        if (P->onchip[c]) {
+        if (P->kernel[c] != kPhases) {
             // no work in the phase launches, not even in what fills up their
             // last block
             T.cn0 = T.vn0 = T.syn0 = T.st0 = T.io0 = T.red0 = INT64_MAX;
@@ -1494,7 +1500,7 @@ void build_table(ldpc_plan* P, const PlanBuffers& B, char* ws) {
 
 bool same_buffers(const ldpc_plan* P, const PlanBuffers& B, const void* ws) {
     if (!P->table_valid || P->table_ws != ws) return false;
-    if (P->onchip != onchip_choice(P)) return false;
+    if (P->kernel != choose_kernels(P)) return false;
     for (int c = 0; c < P->ncodes; ++c) {
         const PlanCode& T = P->table[c];
         if (T.llr != B.llr[c] || T.post != B.post[c] || T.bits_out != B.bits[c]) return false;
@@ -1554,16 +1560,17 @@ bool enqueue(ldpc_plan* P, char* ws, hipStream_t st) {
     for (int i = 0; i < P->sides; ++i) {
         (void)hipStreamWaitEvent(P->side[i], P->fork_ev, 0);
         for (int c = 0; c < nc; ++c) {
-            if (!P->onchip[c] || P->branch[c] != i) continue;
+            if (P->kernel[c] == kPhases || P->branch[c] != i) continue;
             const PlanCode& H = P->table[c];
-            int r = spread_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
-                                  H.converged, H.region, P->region_bytes[c], P->side[i], nullptr);
-            if (r == 0)
-                r = onchip_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
-                                  H.converged, P->side[i]);
-            if (r == 0)
-                r = small_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
-                                 H.converged, P->side[i]);
+            const int r =
+                P->kernel[c] == kSpread
+                    ? spread_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
+                                    H.converged, H.region, P->region_bytes[c], P->side[i], nullptr)
+                : P->kernel[c] == kOnchip
+                    ? onchip_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
+                                    H.converged, P->side[i])
+                    : small_decode(P->graphs[c], H.llr, H.gamma, P->max_iters, P->early, H.post, H.bits_out, H.iters,
+                                   H.converged, P->side[i]);
             ok = ok && r > 0;
         }
         (void)hipEventRecord(P->join_ev[i], P->side[i]);
@@ -1796,7 +1803,7 @@ ldpc_status ldpc_plan_autotune(ldpc_plan* P, const float* const* llr, float* con
     double best = 0.0;
     ldpc_status status = measure(best);
     for (int c = 0; c < P->ncodes && status == LDPC_OK; ++c) {
-        if (P->onchip[c]) continue;   // decoded on chip: its lane layout is not used
+        if (P->kernel[c] != kPhases) continue;   // its lane layout is not used
         const int start = P->layouts[c];
         int keep = start;
         for (int l = 0; l < kLayoutValues && status == LDPC_OK; ++l) {
