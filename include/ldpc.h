@@ -195,7 +195,10 @@ ldpc_status ldpc_decode(const ldpc_graph* g, const float* llr, int32_t gamma, in
  * rounding, not bit for bit.  Setting
  * the environment variable LDPC_BLOCK_PATH=packages makes ldpc_decode use
  * the launches of the package decoder for every code, =onchip keeps a frame
- * on one compute unit (read at each call).  The workspace
+ * on one compute unit (read at each call).  The compute units of a frame wait
+ * for each other a bounded number of times (LDPC_SPREAD_TRIES sets another);
+ * one of them decodes a frame alone, with the same results, where a wait runs
+ * out.  A call whose outputs overlap its LLRs keeps a frame on one unit.  The workspace
  * argument of ldpc_decode is validated the same way on both paths.
  * Errors: EINVAL (NULL, convolutional graph).
  */

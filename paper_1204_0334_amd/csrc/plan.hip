@@ -1334,12 +1334,13 @@ int persist_items_per_ticket() {
 // The codes' decoders, in the order in which ldpc_decode takes them.  The words
 // of a frame on several units have to fit the region that the plan was created
 // with (under another LDPC_BLOCK_PATH, perhaps).
-std::vector<uint8_t> choose_kernels(const ldpc_plan* P) {
+std::vector<uint8_t> choose_kernels(const ldpc_plan* P, const PlanBuffers& B) {
     std::vector<uint8_t> v(P->ncodes, kPhases);
     if (P->persistent) return v;
     for (int c = 0; c < P->ncodes; ++c) {
         const size_t words = spread_bytes(P->graphs[c], P->gammas[c]);
-        if (words > 0 && words <= P->region_bytes[c])
+        if (words > 0 && words <= P->region_bytes[c] &&
+            !spread_in_place(P->graphs[c], P->gammas[c], B.llr[c], B.post[c], B.bits[c]))
             v[c] = kSpread;
         else if (onchip_selected(P->graphs[c]))
             v[c] = kOnchip;
@@ -1391,7 +1392,7 @@ void deal_onchip(ldpc_plan* P) {
 
 void build_table(ldpc_plan* P, const PlanBuffers& B, char* ws) {
     P->table.assign(P->ncodes, PlanCode{});
-    P->kernel = choose_kernels(P);
+    P->kernel = choose_kernels(P, B);
     deal_onchip(P);
     int64_t cn = 0, vn = 0, syn = 0, st = 0, io = 0, red = 0;
     for (int c = 0; c < P->ncodes; ++c) {
@@ -1500,7 +1501,7 @@ void build_table(ldpc_plan* P, const PlanBuffers& B, char* ws) {
 
 bool same_buffers(const ldpc_plan* P, const PlanBuffers& B, const void* ws) {
     if (!P->table_valid || P->table_ws != ws) return false;
-    if (P->kernel != choose_kernels(P)) return false;
+    if (P->kernel != choose_kernels(P, B)) return false;
     for (int c = 0; c < P->ncodes; ++c) {
         const PlanCode& T = P->table[c];
         if (T.llr != B.llr[c] || T.post != B.post[c] || T.bits_out != B.bits[c]) return false;

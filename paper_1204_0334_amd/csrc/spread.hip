@@ -29,20 +29,26 @@
 // later, beside the alphas, when L of the iteration they judge is still at
 // hand.
 //
-// Every wait ends: workgroups take their places in the order in which they
-// start, so at most one frame of a launch has a member that has not started,
-// and at most C - 1 workgroups wait for it.  A device runs at most 32 queues
-// at a time and holds two of these workgroups per compute unit, so with C <=
-// kSpMembers = 16 at most 480 of its 512 places are taken by such workgroups
-// and the missing ones find room.  The number of tries is bounded all the
-// same; a thread that exhausts it marks its outputs as NaN.
+// Every wait ends, and no result depends on how one ends.  Workgroups take
+// their places in the order in which they start, so at most one frame of a
+// launch has a member that has not started, and at most C - 1 workgroups wait
+// for it; a device with a unit mask, or several such launches that fill an
+// XCD between them, can all the same leave it without room.  So a wavefront
+// tries kSpTries times (0.1 s) and then gives up: it publishes nothing more,
+// writes no output, and its workgroup leaves with a mark in the frame's word
+// `left`, in which all workgroups of a frame are counted as they leave.  What
+// the others got was right, or they run out of tries themselves.  The last
+// one to leave finds the mark and decodes the frame alone, in the same
+// arithmetic, without waiting for anybody (3 x 6, p = 3060: 95 us per
+// iteration).
 //
-// 3 x 6, p = 3060, 20 iterations: 1 frame 96 us for 168 on one unit, 16 frames
-// 139 for 169.  An iteration of one frame takes 4.5 us, of which 3.3 are the
-// exchange (with one wavefront per member the rows take 0.8).
+// 3 x 6, p = 3060, 20 iterations with early stopping: 1 frame 85 us for 168 on
+// one unit, 16 frames 124 for 169 (96 and 127 before all words of a try were
+// in flight together).  An iteration of one frame takes 3 us without early
+// stopping, 3.8 with, most of them the exchange.
 // Codes too long for one unit, 20 iterations, spread / message packages: 3 x 6,
-// p = 3600, 1 frame 84 / 434 us, 16 frames 126 / 425; 3 x 18, p = 3600, 8
-// frames 239 / 940; stopping after 4 iterations 91 / 473 and 114 / 640.
+// p = 3600, 1 frame 79 / 434 us; 3 x 18, p = 3600, 8 frames 212 / 940;
+// stopping after 4 iterations 91 / 473 and 114 / 640.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -69,7 +75,9 @@ struct SpreadArgs {
     uint64_t* box;         // [gamma][2][E]: alpha of edge (j DC + k) p + s, slot iteration & 1
     uint64_t* verdict;     // [gamma][2][kSpMembers]
     uint32_t* ticket;      // workgroups that have started
-    int32_t n, p, max_iters, members, nb;
+    uint32_t* left;        // [gamma] workgroups of the frame that have left, and from bit 16 those that gave up
+    int32_t n, p, gamma, max_iters, members, nb;
+    uint32_t tries;        // of a wavefront, before it gives up
     int32_t rb0[kSpRows];                      // first block of base row j
     uint32_t sh4[kSpRows * kSpSlots];          // 4 times the shift of edge slot k of base row j
     // 8 times the offset from row (j, s) to the row of base row (j + 1) % 3
@@ -89,21 +97,32 @@ __device__ __forceinline__ void sp_store(sp_word* base, uint32_t byte, uint32_t 
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The rule of base row j at iteration it, in place.
+template <int DC, int RULE>
+__device__ __forceinline__ void spread_rule(const SpreadArgs& A, int it, int j, float (&x)[DC]) {
+    if constexpr (RULE == 0)
+        check2e_row<DC, DC <= 9 ? 1 : 2>(x, DC);
+    else
+        nms2_row<DC>(x, DC, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
+}
+
 // DC: row weight; RULE 0: sum-product, 1: learned min-sum; EARLY: with early
 // stopping.  Two workgroups fit a compute unit (256 registers).  The words of
 // all three rows are in flight together, of heavy rows those of one row.
 template <int DC, int RULE, bool EARLY>
 __global__ void __launch_bounds__(kSpThreads) __attribute__((amdgpu_waves_per_eu(2)))
 spread_kernel(const SpreadArgs A) {
-    __shared__ uint32_t place, bad[2], go;
+    // failed: a wavefront of this workgroup has given up
+    __shared__ uint32_t place, bad[3], go, failed;
     const int tid = threadIdx.x, TB = blockDim.x, p = A.p;
     if (tid == 0) {
         place = __hip_atomic_fetch_add(A.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bad[0] = bad[1] = 0u;
+        bad[0] = bad[1] = bad[2] = failed = 0u;
     }
     __syncthreads();
     const uint32_t me = __builtin_amdgcn_readfirstlane(place);
     const uint32_t frame = me / (uint32_t)A.members, member = me - frame * (uint32_t)A.members;
+    if (frame >= (uint32_t)A.gamma) return;   // only where another launch uses the same workspace
     const size_t f0 = (size_t)frame * A.n;
     const float* __restrict__ llr = A.llr + f0;
     const uint32_t p4 = 4u * (uint32_t)p, p8 = 8u * (uint32_t)p;
@@ -113,14 +132,16 @@ spread_kernel(const SpreadArgs A) {
     const size_t E = (size_t)kSpRows * DC * p;
     sp_word* const box = (sp_word*)A.box + (size_t)frame * 2 * E;
     sp_word* const verdict = (sp_word*)A.verdict + (size_t)frame * 2 * kSpMembers;
-    uint32_t tries = 1u << 22;
+    uint32_t* const left = A.left + frame;
+    uint32_t tries = A.tries;
+    bool alive = true;   // this wavefront has not given up
 
-    auto channel = [&](int j, int k) -> uint32_t {   // byte of the LLR that slot k of row (j, s) meets
-        const uint32_t t = s4 + A.sh4[j * kSpSlots + k];
+    auto channel = [&](int j, int k, uint32_t r4) -> uint32_t {   // byte of the LLR that slot k of row (j, r) meets
+        const uint32_t t = r4 + A.sh4[j * kSpSlots + k];
         return (uint32_t)k * p4 + min(t, t - p4);
     };
-    auto raw = [&](int j, int k) -> float {
-        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(llr) + channel(j, k));
+    auto raw = [&](int j, int k, uint32_t r4) -> float {
+        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(llr) + channel(j, k, r4));
     };
     // of heavy rows the channel LLRs are read again where they are used
     constexpr bool kMuInRegs = DC <= 9;
@@ -129,7 +150,7 @@ spread_kernel(const SpreadArgs A) {
     for (int j = 0; j < kSpRows; ++j)
 #pragma unroll
         for (int k = 0; k < DC; ++k) {
-            if (kMuInRegs) mu[kMuInRegs ? j : 0][k] = active ? raw(j, k) : 0.0f;
+            if (kMuInRegs) mu[kMuInRegs ? j : 0][k] = active ? raw(j, k, s4) : 0.0f;
             al[j][k] = 0.0f;
         }
 #pragma unroll
@@ -141,23 +162,39 @@ spread_kernel(const SpreadArgs A) {
             for (int k = 0; k < DC; ++k) mu[kMuInRegs ? j : 0][k] = mu[kMuInRegs ? j : 0][k] * kLog2eF + 0.0f;
     }
 
-    // whether a member's rows are violated, from the words of iteration it
+    // repeats get() until no lane needs another try; false when this
+    // wavefront has no tries left, or another workgroup of the frame gave up
+    auto await = [&](auto&& get) -> bool {
+        while (__ballot(!get()) != 0ull) {
+            if (tries == 0u) return false;
+            --tries;
+            if ((tries & 255u) == 0u &&
+                __hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= 0x10000u)
+                return false;
+        }
+        return true;
+    };
+    auto give_up = [&]() {
+        alive = false;
+        if ((tid & 63) == 0) failed = 1u;
+    };
+    // the first wavefront: whether a member's rows are violated, from the
+    // words of iteration it
     auto judged = [&](uint32_t it) -> bool {
         bool v = false;
-        if (tid < A.members) {
-            uint64_t w = sp_load(verdict, 8u * ((it & 1u) * kSpMembers + (uint32_t)tid));
-            while ((uint32_t)(w >> 32) != it && tries > 0u) {
-                --tries;
-                w = sp_load(verdict, 8u * ((it & 1u) * kSpMembers + (uint32_t)tid));
-            }
-            v = (uint32_t)w != 0u;
-        }
+        if (!await([&]() -> bool {
+                if (tid >= A.members) return true;
+                const uint64_t w = sp_load(verdict, 8u * ((it & 1u) * kSpMembers + (uint32_t)tid));
+                v = (uint32_t)w != 0u;
+                return (uint32_t)(w >> 32) == it;
+            }))
+            give_up();
         return __ballot(v) != 0ull;
     };
 
     int stop = 0;
     for (int it = 1;; ++it) {
-        const bool fin = it > A.max_iters;
+        bool fin = it > A.max_iters;
         const uint32_t want = (uint32_t)(it - 1);
         sp_word* from = box + (want & 1u) * E;
         sp_word* to = box + ((uint32_t)it & 1u) * E;
@@ -166,10 +203,10 @@ spread_kernel(const SpreadArgs A) {
         constexpr int NW = DC <= 9 ? kSpRows : 1;
         uint64_t w1[NW][DC], w2[NW][DC];
         auto fetch = [&](int j0) -> bool {
+            if (!active) return true;
             // opaque: the words' offsets are worked out again at every try, not held
             uint32_t at = s8;
             asm volatile("" : "+v"(at));
-            bool ok = true;
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
                 const int j = j0 + i, j1 = (j + 1) % kSpRows, j2 = (j + 2) % kSpRows;
@@ -180,100 +217,185 @@ spread_kernel(const SpreadArgs A) {
                     w2[i][k] = sp_load(from, (uint32_t)(j2 * DC + k) * p8 + min(t2, t2 - p8));
                 }
             }
+            // no load waits for the test of an earlier one
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t off = 0;
 #pragma unroll
             for (int i = 0; i < NW; ++i)
 #pragma unroll
                 for (int k = 0; k < DC; ++k)
-                    ok = ok && (uint32_t)(w1[i][k] >> 32) == want && (uint32_t)(w2[i][k] >> 32) == want;
-            return ok;
+                    off |= ((uint32_t)(w1[i][k] >> 32) ^ want) | ((uint32_t)(w2[i][k] >> 32) ^ want);
+            return off == 0u;
         };
-        if (NW == kSpRows && active)
-            while (__ballot(!fetch(0)) != 0ull && tries > 0u) --tries;
+        if (NW == kSpRows && alive && !await([&]() { return fetch(0); })) give_up();
         if (EARLY && it >= 3) {
             if (tid < 64) {
-                const bool any = judged(want);
-                if (tid == 0) go = any ? 1u : 0u;
+                const bool any = alive && judged(want);
+                if (tid == 0) go = failed ? 2u : any ? 1u : 0u;
             }
             __syncthreads();
-            if (go == 0u) {   // the syndrome of iteration it - 2 is zero: Lkeep holds its sums
+            const uint32_t verdict_read = go;
+            if (verdict_read == 2u) {
+                alive = false;
+                break;
+            }
+            if (verdict_read == 0u) {   // the syndrome of iteration it - 2 is zero: Lkeep holds its sums
                 stop = it - 2;
                 break;
             }
         }
         uint64_t viol = 0;
-        if (active) {
 #pragma unroll
-            for (int j = 0; j < kSpRows; ++j) {
-                float (&m)[DC] = mu[kMuInRegs ? j : 0];
-                if (!kMuInRegs) {
-                    uint32_t at = s4;
-                    asm volatile("" : "+v"(at));
+        for (int j = 0; j < kSpRows; ++j) {
+            float (&m)[DC] = mu[kMuInRegs ? j : 0];
+            if (!kMuInRegs && active) {   // in flight with the words
+                uint32_t at = s4;
+                asm volatile("" : "+v"(at));
 #pragma unroll
-                    for (int k = 0; k < DC; ++k) {
-                        const uint32_t t = at + A.sh4[j * kSpSlots + k];
-                        m[k] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(llr) +
-                                                               ((uint32_t)k * p4 + min(t, t - p4))) * kLog2eF + 0.0f;
-                    }
-                }
-                if (NW == 1)
-                    while (__ballot(!fetch(j)) != 0ull && tries > 0u) --tries;
-                constexpr bool all = NW == kSpRows;
-                float x[DC];
-                uint32_t sx = 0;
+                for (int k = 0; k < DC; ++k) m[k] = raw(j, k, at);
+            }
+            if (NW == 1 && alive && !await([&]() { return fetch(j); })) give_up();
+            if (!active || !alive) continue;
+            if (!kMuInRegs) {
+#pragma unroll
+                for (int k = 0; k < DC; ++k) m[k] = m[k] * kLog2eF + 0.0f;
+            }
+            constexpr bool all = NW == kSpRows;
+            float x[DC];
+            uint32_t sx = 0;
+#pragma unroll
+            for (int k = 0; k < DC; ++k) {
+                const float u = __uint_as_float((uint32_t)w1[all ? j : 0][k]);
+                const float v = __uint_as_float((uint32_t)w2[all ? j : 0][k]);
+                const float a0 = j == 0 ? al[j][k] : j == 1 ? v : u;
+                const float a1 = j == 0 ? u : j == 1 ? al[j][k] : v;
+                const float a2 = j == 0 ? v : j == 1 ? u : al[j][k];
+                const float L = ((m[k] + a0) + a1) + a2;
+                if (j == 0) Lkeep[k] = L;
+                sx ^= __float_as_uint(L);   // the row's parity in bit 31 (a sum is never -0)
+                x[k] = clip2(L - al[j][k]);
+            }
+            viol |= __ballot((int32_t)sx < 0);
+            if (!fin) {
+                uint32_t at = s8;
+                asm volatile("" : "+v"(at));
+                spread_rule<DC, RULE>(A, it, j, x);
 #pragma unroll
                 for (int k = 0; k < DC; ++k) {
-                    const float u = __uint_as_float((uint32_t)w1[all ? j : 0][k]);
-                    const float v = __uint_as_float((uint32_t)w2[all ? j : 0][k]);
-                    const float a0 = j == 0 ? al[j][k] : j == 1 ? v : u;
-                    const float a1 = j == 0 ? u : j == 1 ? al[j][k] : v;
-                    const float a2 = j == 0 ? v : j == 1 ? u : al[j][k];
-                    const float L = ((m[k] + a0) + a1) + a2;
-                    if (j == 0) Lkeep[k] = L;
-                    sx ^= __float_as_uint(L);   // the row's parity in bit 31 (a sum is never -0)
-                    x[k] = clip2(L - al[j][k]);
-                }
-                viol |= __ballot((int32_t)sx < 0);
-                if (!fin) {
-                    uint32_t at = s8;
-                    asm volatile("" : "+v"(at));
-                    if constexpr (RULE == 0)
-                        check2e_row<DC, DC <= 9 ? 1 : 2>(x, DC);
-                    else
-                        nms2_row<DC>(x, DC, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
-#pragma unroll
-                    for (int k = 0; k < DC; ++k) {
-                        al[j][k] = x[k];
-                        sp_store(to, (uint32_t)(j * DC + k) * p8 + at, __float_as_uint(x[k]), (uint32_t)it);
-                    }
+                    al[j][k] = x[k];
+                    sp_store(to, (uint32_t)(j * DC + k) * p8 + at, __float_as_uint(x[k]), (uint32_t)it);
                 }
             }
         }
+        // without early stopping no other barrier comes: straight to the last
+        if (!EARLY && !alive) fin = true;
         if ((EARLY && it >= 2) || fin) {
             if (viol != 0ull && (tid & 63) == 0) bad[it & 1] = 1u;
             __syncthreads();
             if (tid == 0) {
-                sp_store(verdict, 8u * (((uint32_t)it & 1u) * kSpMembers + member), bad[it & 1], (uint32_t)it);
+                if (!failed)
+                    sp_store(verdict, 8u * (((uint32_t)it & 1u) * kSpMembers + member), bad[it & 1], (uint32_t)it);
                 bad[(it + 1) & 1] = 0u;
             }
         }
         if (fin) break;
     }
 
-    if (active) {
+    // the words are in memory before this workgroup is counted as gone
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    auto leave = [&]() -> uint32_t {
+        return __hip_atomic_fetch_add(left, failed ? 0x10001u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const bool judge = member == 0 && !stop;   // still reads the last iteration's verdicts
+    uint32_t before = 0;
+    if (tid == 0 && !judge) before = leave();
+    auto put = [&](int k, uint32_t r4, float L) {
+        const size_t v = f0 + (channel(0, k, r4) >> 2);
+        A.post[v] = unscale2(L, raw(0, k, r4));
+        A.bits[v] = (uint8_t)(L < 0.0f);
+    };
+    if (active && alive) {
 #pragma unroll
-        for (int k = 0; k < DC; ++k) {
-            const float x = tries > 0u ? Lkeep[k] : __builtin_nanf("");
-            const size_t v = f0 + (channel(0, k) >> 2);
-            A.post[v] = unscale2(x, raw(0, k));
-            A.bits[v] = (uint8_t)(x < 0.0f);
-        }
+        for (int k = 0; k < DC; ++k) put(k, s4, Lkeep[k]);
     }
     if (member == 0 && tid < 64) {
-        const bool any = stop ? false : judged((uint32_t)A.max_iters + 1u);
+        const bool any = judge && !failed && judged((uint32_t)A.max_iters + 1u);
         if (tid == 0) {
-            if (A.iters) A.iters[frame] = stop ? stop : A.max_iters;
-            if (A.conv) A.conv[frame] = any || tries == 0u ? 0 : 1;
+            if (!failed) {
+                if (A.iters) A.iters[frame] = stop ? stop : A.max_iters;
+                if (A.conv) A.conv[frame] = any ? 0 : 1;
+            }
+            if (judge) before = leave();
         }
+    }
+    if (tid == 0) go = (before & 0xffffu) + 1u == (uint32_t)A.members && (before >= 0x10000u || failed) ? 1u : 0u;
+    __syncthreads();
+    if (go == 0u) return;
+
+    // The last to leave a frame that a member gave up: all of its rows, one
+    // iteration after the other, in the same words.
+    if (tid < 3) bad[tid] = 0u;
+    __syncthreads();
+    for (int it = 1;; ++it) {
+        const bool fin = it > A.max_iters;
+        sp_word* from = box + ((uint32_t)(it - 1) & 1u) * E;
+        sp_word* to = box + ((uint32_t)it & 1u) * E;
+        // the sum of the variable of slot k of row (j, r) after iteration it - 1, and its edge's alpha
+        auto sum = [&](int j, int k, uint32_t r, float& own) -> float {
+            const int j1 = j == 2 ? 0 : j + 1, j2 = j == 0 ? 2 : j - 1;
+            const uint32_t t1 = 8u * r + A.to1[j * kSpSlots + k], t2 = 8u * r + A.to2[j * kSpSlots + k];
+            float u = 0.0f, v = 0.0f;
+            own = 0.0f;
+            if (it > 1) {
+                own = __uint_as_float((uint32_t)sp_load(from, (uint32_t)(j * DC + k) * p8 + 8u * r));
+                u = __uint_as_float((uint32_t)sp_load(from, (uint32_t)(j1 * DC + k) * p8 + min(t1, t1 - p8)));
+                v = __uint_as_float((uint32_t)sp_load(from, (uint32_t)(j2 * DC + k) * p8 + min(t2, t2 - p8)));
+            }
+            const float a0 = j == 0 ? own : j == 1 ? v : u;
+            const float a1 = j == 0 ? u : j == 1 ? own : v;
+            const float a2 = j == 0 ? v : j == 1 ? u : own;
+            const float m = raw(j, k, 4u * r) * kLog2eF + 0.0f;
+            return ((m + a0) + a1) + a2;
+        };
+        bool viol = false;
+#pragma unroll 1
+        for (uint32_t r = (uint32_t)tid; r < (uint32_t)p; r += (uint32_t)TB) {
+#pragma unroll 1
+            for (int j = 0; j < kSpRows; ++j) {
+                float x[DC];
+                uint32_t sx = 0;
+#pragma unroll
+                for (int k = 0; k < DC; ++k) {
+                    float own;
+                    const float L = sum(j, k, r, own);
+                    sx ^= __float_as_uint(L);
+                    x[k] = clip2(L - own);
+                }
+                viol = viol || (int32_t)sx < 0;
+                if (fin) continue;
+                spread_rule<DC, RULE>(A, it, j, x);
+#pragma unroll
+                for (int k = 0; k < DC; ++k)
+                    sp_store(to, (uint32_t)(j * DC + k) * p8 + 8u * r, __float_as_uint(x[k]), (uint32_t)it);
+            }
+        }
+        if (viol) bad[it % 3] = 1u;
+        if (tid == 0) bad[(it + 1) % 3] = 0u;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const bool any = bad[it % 3] != 0u;
+        if (!fin && !(EARLY && it >= 2 && !any)) continue;
+        for (uint32_t r = (uint32_t)tid; r < (uint32_t)p; r += (uint32_t)TB)
+            for (int k = 0; k < DC; ++k) {
+                float own;
+                put(k, 4u * r, sum(0, k, r, own));
+            }
+        if (tid == 0) {
+            if (A.iters) A.iters[frame] = it - 1;
+            if (A.conv) A.conv[frame] = any ? 0 : 1;
+        }
+        return;
     }
 }
 
@@ -311,6 +433,15 @@ const SpreadVariant kSpread[] = {spread<6, 0>(), spread<9, 0>(), spread<18, 0>()
 // have p < 64) are faster here at every length.
 constexpr int kSpLeastP = 1800, kSpLeastLongP = 1024;
 
+// Tries of a wavefront before it gives up, 1-2 us each.  LDPC_SPREAD_TRIES sets
+// another number (read at each call); it changes speed, never results.
+constexpr uint32_t kSpTries = 1u << 16;
+
+uint32_t spread_tries() {
+    const char* env = std::getenv("LDPC_SPREAD_TRIES");
+    return env ? (uint32_t)std::strtoul(env, nullptr, 10) : kSpTries;
+}
+
 struct SpreadChoice {
     const SpreadVariant* v;
     int members, tb;
@@ -345,7 +476,7 @@ bool choose_spread(const ldpc_graph* g, int rule, int gamma, SpreadChoice& c) {
         if (v.dc == D.L && v.rule == rule) c.v = &v;
     c.verdict = (size_t)gamma * 2 * D.E * sizeof(uint64_t);
     c.ticket = c.verdict + (size_t)gamma * 2 * kSpMembers * sizeof(uint64_t);
-    c.total = c.ticket + 16;
+    c.total = c.ticket + ((size_t)(1 + gamma) * sizeof(uint32_t) + 15) / 16 * 16;
     return c.v != nullptr;
 }
 
@@ -356,11 +487,19 @@ size_t spread_bytes(const ldpc_graph* g, int gamma) {
     return choose_spread(g, 0, gamma, c) ? c.total : 0;
 }
 
+bool spread_in_place(const ldpc_graph* g, int gamma, const float* llr, const float* post, const uint8_t* bits) {
+    const size_t count = (size_t)gamma * g->n;
+    const uintptr_t a = reinterpret_cast<uintptr_t>(llr), b = reinterpret_cast<uintptr_t>(post);
+    const uintptr_t c = reinterpret_cast<uintptr_t>(bits);
+    return (a < b + 4 * count && b < a + 4 * count) || (a < c + count && c < a + 4 * count);
+}
+
 int spread_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
                   uint8_t* bits, int32_t* iters, uint8_t* converged, void* ws, size_t ws_bytes, hipStream_t st,
                   const float* nms_w) {
     SpreadChoice c;
     if (!choose_spread(g, nms_w ? 1 : 0, gamma, c) || c.total > ws_bytes) return 0;
+    if (spread_in_place(g, gamma, llr, post, bits)) return 0;
     const QCDesc& D = g->qc;
     char* base = reinterpret_cast<char*>(ws);
     SpreadArgs A{};
@@ -373,8 +512,11 @@ int spread_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iter
     A.box = reinterpret_cast<uint64_t*>(base);
     A.verdict = reinterpret_cast<uint64_t*>(base + c.verdict);
     A.ticket = reinterpret_cast<uint32_t*>(base + c.ticket);
+    A.left = A.ticket + 1;
+    A.tries = spread_tries();
     A.n = D.n;
     A.p = D.p;
+    A.gamma = gamma;
     A.max_iters = max_iters;
     A.members = c.members;
     A.nb = D.nb;
