@@ -182,11 +182,13 @@ ldpc_status ldpc_decode(const ldpc_graph* g, const float* llr, int32_t gamma, in
  * edge messages in the workspace; for codes of up to 8192 edges, with columns
  * of weight above 4 for batches of up to 256 frames, one launch per decode
  * with a frame's packages in LDS, equal bit for bit).  Batches of up to 16
- * frames of full bases of 3 rows of weight 6, 9 or 18 with 1800 <= p <= 4096
- * are decoded with a frame on 16 compute units, messages in the workspace:
- * bit for bit as on one unit where the code has two sums per variable there;
- * longer codes, of which this function returns 0, in the on-chip decoder's
- * arithmetic.  Both decoders compute Algorithm 1; the package
+ * frames of full bases of 3 rows are decoded with a frame on 16 compute units,
+ * messages in the workspace, in one launch after one that clears them: rows of
+ * weight 6 or 9 with p >= 1800 that have two sums per variable on one unit (up
+ * to 3072 and 2048), bit for bit as there (1 is returned); codes that no unit
+ * takes, up to p = 4096 (rows of weight 6 or 9 from p = 3073, 18 from 1537),
+ * bit for bit as with the launches of the package decoder (0 is returned).  So
+ * a frame's results do not depend on its batch.  Both decoders compute Algorithm 1; the package
  * decoder's FP32 check rule combines (tanh, 1 - tanh) pairs, the on-chip
  * decoder's the two parities' probabilities up to a common factor (no
  * reciprocal per input), and the on-chip decoder forms each

@@ -155,8 +155,9 @@ __device__ __forceinline__ void check2e_row(float (&x)[DC], int d) {
 // offset) of slot k's block, the offset in natural units (scaled here).  The
 // second minimum is the median of a value and the two minima so far, and an
 // edge that holds the minimum is one whose magnitude equals it (with a tie
-// the two minima are equal), so no index is kept.  out may be in.
-template <int DC>
+// the two minima are equal), so no index is kept.  out may be in.  BASE2 =
+// false: all in natural units, and -0 among the betas, as the package decoder.
+template <int DC, bool BASE2 = true>
 __device__ __forceinline__ void nms2_row(const float (&in)[DC], int d, const float* __restrict__ w,
                                          float (&out)[DC]) {
     float min1 = __builtin_inff(), min2 = __builtin_inff();
@@ -167,7 +168,7 @@ __device__ __forceinline__ void nms2_row(const float (&in)[DC], int d, const flo
             const float m = fabsf(in[k]);
             min2 = __builtin_amdgcn_fmed3f(m, min1, min2);
             min1 = fminf(m, min1);
-            sgn = __builtin_amdgcn_alignbit(sgn, __float_as_uint(in[k]), 31);
+            sgn = __builtin_amdgcn_alignbit(sgn, __float_as_uint(BASE2 ? in[k] : in[k] + 0.0f), 31);
         } else {
             sgn <<= 1;
         }
@@ -177,7 +178,7 @@ __device__ __forceinline__ void nms2_row(const float (&in)[DC], int d, const flo
     for (int k = 0; k < DC; ++k) {
         if (k < d) {
             const float m = fabsf(in[k]) == min1 ? min2 : min1;
-            const float v = fmaxf(m - w[2 * k + 1] * kLog2eF, 0.0f);
+            const float v = fmaxf(m - (BASE2 ? w[2 * k + 1] * kLog2eF : w[2 * k + 1]), 0.0f);
             // rounded before it is added to a sum: the sums are the same whether a
             // message comes from a register or from another compute unit
             {

@@ -1,7 +1,8 @@
 // Block decoder with a frame on several compute units (spread.hip), for
 // batches that would leave most of the chip idle.  Called by ldpc_decode and
 // the plans before the one-unit decoder of onchip.hip, whose results it
-// returns bit for bit, and in place of the message packages for longer codes.
+// returns bit for bit, and in place of the message packages, whose results it
+// returns bit for bit, for longer codes.
 #pragma once
 
 #include <hip/hip_runtime_api.h>

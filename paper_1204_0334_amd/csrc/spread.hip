@@ -12,7 +12,8 @@
 // one-unit decoder's sums are formed, and beta = clip(L - own alpha): every
 // row forms its variables' sums itself, so there is one exchange per
 // iteration, no sum is shared, and the results are the one-unit decoder's bit
-// for bit.
+// for bit; of codes too long for one unit, in their arithmetic, the message
+// packages'.
 //
 // The exchange needs no barrier.  An alpha travels as one 64-bit word (value,
 // iteration) through device-coherent stores and loads, and a reader repeats
@@ -47,8 +48,10 @@
 // in flight together).  An iteration of one frame takes 3 us without early
 // stopping, 3.8 with, most of them the exchange.
 // Codes too long for one unit, 20 iterations, spread / message packages: 3 x 6,
-// p = 3600, 1 frame 79 / 434 us; 3 x 18, p = 3600, 8 frames 212 / 940;
-// stopping after 4 iterations 91 / 473 and 114 / 640.
+// p = 3600, 1 frame 101 / 434 us; 3 x 9, 16 frames 187; 3 x 18, 8 frames 236 /
+// 940.  In the one-unit decoder's arithmetic they took 79, 187 and 212, but
+// then a frame's results depended on the batch, and their error against 64
+// bits was up to 1.2 times the packages'.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -97,17 +100,81 @@ __device__ __forceinline__ void sp_store(sp_word* base, uint32_t byte, uint32_t 
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// RULE 0, 1: sum-product and learned min-sum as on one unit (onchip.hip), whose
+// results are equal bit for bit; 2, 3: the same as in the message packages
+// (natural units, a variable's beta the sum of the other alphas), with the
+// results of which those of codes that no unit takes are equal bit for bit.
+constexpr bool sp_packages(int rule) { return rule >= 2; }
+
+// Channel LLR as the sums take it.
+template <int RULE>
+__device__ __forceinline__ float spread_mu(float mu) {
+    return sp_packages(RULE) ? mu : mu * kLog2eF + 0.0f;
+}
+
+// Sum L of a variable, and the beta that it sends to its row of base row j;
+// a: its alphas by base row (all 0 before iteration 1: first).
+template <int RULE>
+__device__ __forceinline__ float spread_sum(float m, const float (&a)[kSpRows], int j, bool first, float& beta) {
+    if constexpr (sp_packages(RULE)) {
+        const float mu[1] = {m};
+        float al[kSpRows][1], b[kSpRows][1], L[1];
+#pragma unroll
+        for (int i = 0; i < kSpRows; ++i) al[i][0] = a[i];
+        sp_variable<kSpRows, 1>(mu, al, b, L);
+        // the first message is mu itself, which the rule clips
+        const float c = fminf(fabsf(m), kClip), from_mu = RULE == 2 ? m : m < 0.0f ? -c : c;
+        beta = first ? from_mu : j == 0 ? b[0][0] : j == 1 ? b[1][0] : b[2][0];
+        return L[0];
+    } else {
+        const float L = ((m + a[0]) + a[1]) + a[2];
+        beta = clip2(L - (j == 0 ? a[0] : j == 1 ? a[1] : a[2]));
+        return L;
+    }
+}
+
+// What a sum adds to its row's parity, in bit 31 (on one unit no sum is ever
+// -0: it starts from mu + 0).
+template <int RULE>
+__device__ __forceinline__ uint32_t spread_sign(float L) {
+    return sp_packages(RULE) ? (L < 0.0f ? 0x80000000u : 0u) : __float_as_uint(L);
+}
+
 // The rule of base row j at iteration it, in place.
 template <int DC, int RULE>
 __device__ __forceinline__ void spread_rule(const SpreadArgs& A, int it, int j, float (&x)[DC]) {
-    if constexpr (RULE == 0)
+    const float* w = RULE % 2 ? A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2 : nullptr;
+    if constexpr (RULE == 0) {
         check2e_row<DC, DC <= 9 ? 1 : 2>(x, DC);
-    else
-        nms2_row<DC>(x, DC, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
+    } else if constexpr (RULE == 1) {
+        nms2_row<DC>(x, DC, w, x);
+    } else if constexpr (RULE == 2) {
+        // sp_check, at the package kernels' row capacity (12 and 24 for rows of
+        // weight 9 and 18) as far as it can be seen: whether a slot follows
+        // the row's last decides how that one's output is rounded
+        constexpr int N = DC == 6 ? DC : DC + 1;
+        float t[N], q[N], mag[N];
+        uint32_t sgn = 0;
+#pragma unroll
+        for (int k = 0; k < DC; ++k) {
+            tq_of(x[k], t[k], q[k]);
+            sgn ^= __float_as_uint(x[k]) & 0x80000000u;
+        }
+        if constexpr (N > DC) {
+            t[DC] = 1.0f;
+            q[DC] = 0.0f;
+            asm volatile("" : "+v"(t[DC]), "+v"(q[DC]));
+        }
+        boxplus_fb<N>(t, q, mag);
+#pragma unroll
+        for (int k = 0; k < DC; ++k)
+            x[k] = __uint_as_float(__float_as_uint(mag[k]) | (sgn ^ (__float_as_uint(x[k]) & 0x80000000u)));
+    } else {
+        nms2_row<DC, false>(x, DC, w, x);
+    }
 }
 
-// DC: row weight; RULE 0: sum-product, 1: learned min-sum; EARLY: with early
-// stopping.  Two workgroups fit a compute unit (256 registers).  The words of
+// DC: row weight; RULE as above; EARLY: with early stopping.  Two workgroups fit a compute unit (256 registers).  The words of
 // all three rows are in flight together, of heavy rows those of one row.
 template <int DC, int RULE, bool EARLY>
 __global__ void __launch_bounds__(kSpThreads) __attribute__((amdgpu_waves_per_eu(2)))
@@ -159,7 +226,7 @@ spread_kernel(const SpreadArgs A) {
 #pragma unroll
         for (int j = 0; j < kSpRows; ++j)
 #pragma unroll
-            for (int k = 0; k < DC; ++k) mu[kMuInRegs ? j : 0][k] = mu[kMuInRegs ? j : 0][k] * kLog2eF + 0.0f;
+            for (int k = 0; k < DC; ++k) mu[kMuInRegs ? j : 0][k] = spread_mu<RULE>(mu[kMuInRegs ? j : 0][k]);
     }
 
     // repeats get() until no lane needs another try; false when this
@@ -258,7 +325,7 @@ spread_kernel(const SpreadArgs A) {
             if (!active || !alive) continue;
             if (!kMuInRegs) {
 #pragma unroll
-                for (int k = 0; k < DC; ++k) m[k] = m[k] * kLog2eF + 0.0f;
+                for (int k = 0; k < DC; ++k) m[k] = spread_mu<RULE>(m[k]);
             }
             constexpr bool all = NW == kSpRows;
             float x[DC];
@@ -267,13 +334,11 @@ spread_kernel(const SpreadArgs A) {
             for (int k = 0; k < DC; ++k) {
                 const float u = __uint_as_float((uint32_t)w1[all ? j : 0][k]);
                 const float v = __uint_as_float((uint32_t)w2[all ? j : 0][k]);
-                const float a0 = j == 0 ? al[j][k] : j == 1 ? v : u;
-                const float a1 = j == 0 ? u : j == 1 ? al[j][k] : v;
-                const float a2 = j == 0 ? v : j == 1 ? u : al[j][k];
-                const float L = ((m[k] + a0) + a1) + a2;
+                const float a[kSpRows] = {j == 0 ? al[j][k] : j == 1 ? v : u, j == 0 ? u : j == 1 ? al[j][k] : v,
+                                          j == 0 ? v : j == 1 ? u : al[j][k]};
+                const float L = spread_sum<RULE>(m[k], a, j, it == 1, x[k]);
                 if (j == 0) Lkeep[k] = L;
-                sx ^= __float_as_uint(L);   // the row's parity in bit 31 (a sum is never -0)
-                x[k] = clip2(L - al[j][k]);
+                sx ^= spread_sign<RULE>(L);
             }
             viol |= __ballot((int32_t)sx < 0);
             if (!fin) {
@@ -312,7 +377,7 @@ spread_kernel(const SpreadArgs A) {
     if (tid == 0 && !judge) before = leave();
     auto put = [&](int k, uint32_t r4, float L) {
         const size_t v = f0 + (channel(0, k, r4) >> 2);
-        A.post[v] = unscale2(L, raw(0, k, r4));
+        A.post[v] = sp_packages(RULE) ? clip30(L) : unscale2(L, raw(0, k, r4));
         A.bits[v] = (uint8_t)(L < 0.0f);
     };
     if (active && alive) {
@@ -341,22 +406,19 @@ spread_kernel(const SpreadArgs A) {
         const bool fin = it > A.max_iters;
         sp_word* from = box + ((uint32_t)(it - 1) & 1u) * E;
         sp_word* to = box + ((uint32_t)it & 1u) * E;
-        // the sum of the variable of slot k of row (j, r) after iteration it - 1, and its edge's alpha
-        auto sum = [&](int j, int k, uint32_t r, float& own) -> float {
+        // the sum of the variable of slot k of row (j, r) after iteration it - 1, and the beta it sends there
+        auto sum = [&](int j, int k, uint32_t r, float& beta) -> float {
             const int j1 = j == 2 ? 0 : j + 1, j2 = j == 0 ? 2 : j - 1;
             const uint32_t t1 = 8u * r + A.to1[j * kSpSlots + k], t2 = 8u * r + A.to2[j * kSpSlots + k];
-            float u = 0.0f, v = 0.0f;
-            own = 0.0f;
+            float own = 0.0f, u = 0.0f, v = 0.0f;
             if (it > 1) {
                 own = __uint_as_float((uint32_t)sp_load(from, (uint32_t)(j * DC + k) * p8 + 8u * r));
                 u = __uint_as_float((uint32_t)sp_load(from, (uint32_t)(j1 * DC + k) * p8 + min(t1, t1 - p8)));
                 v = __uint_as_float((uint32_t)sp_load(from, (uint32_t)(j2 * DC + k) * p8 + min(t2, t2 - p8)));
             }
-            const float a0 = j == 0 ? own : j == 1 ? v : u;
-            const float a1 = j == 0 ? u : j == 1 ? own : v;
-            const float a2 = j == 0 ? v : j == 1 ? u : own;
-            const float m = raw(j, k, 4u * r) * kLog2eF + 0.0f;
-            return ((m + a0) + a1) + a2;
+            const float a[kSpRows] = {j == 0 ? own : j == 1 ? v : u, j == 0 ? u : j == 1 ? own : v,
+                                      j == 0 ? v : j == 1 ? u : own};
+            return spread_sum<RULE>(spread_mu<RULE>(raw(j, k, 4u * r)), a, j, it == 1, beta);
         };
         bool viol = false;
 #pragma unroll 1
@@ -367,10 +429,7 @@ spread_kernel(const SpreadArgs A) {
                 uint32_t sx = 0;
 #pragma unroll
                 for (int k = 0; k < DC; ++k) {
-                    float own;
-                    const float L = sum(j, k, r, own);
-                    sx ^= __float_as_uint(L);
-                    x[k] = clip2(L - own);
+                    sx ^= spread_sign<RULE>(sum(j, k, r, x[k]));
                 }
                 viol = viol || (int32_t)sx < 0;
                 if (fin) continue;
@@ -388,8 +447,8 @@ spread_kernel(const SpreadArgs A) {
         if (!fin && !(EARLY && it >= 2 && !any)) continue;
         for (uint32_t r = (uint32_t)tid; r < (uint32_t)p; r += (uint32_t)TB)
             for (int k = 0; k < DC; ++k) {
-                float own;
-                put(k, 4u * r, sum(0, k, r, own));
+                float beta;
+                put(k, 4u * r, sum(0, k, r, beta));
             }
         if (tid == 0) {
             if (A.iters) A.iters[frame] = it - 1;
@@ -422,8 +481,9 @@ constexpr SpreadVariant spread() {
                          reinterpret_cast<const void*>(&spread_kernel<DC, RULE, true>)};
 }
 
-const SpreadVariant kSpread[] = {spread<6, 0>(), spread<9, 0>(), spread<18, 0>(),
-                                 spread<6, 1>(), spread<9, 1>(), spread<18, 1>()};
+const SpreadVariant kSpread[] = {spread<6, 0>(), spread<9, 0>(), spread<6, 1>(), spread<9, 1>(),
+                                 spread<6, 2>(), spread<9, 2>(), spread<18, 2>(),
+                                 spread<6, 3>(), spread<9, 3>(), spread<18, 3>()};
 
 // Below this an iteration on one compute unit takes no longer than the
 // exchange.  20 iterations, one unit / spread: 3 x 6, p = 1000 61 / 87 us for
@@ -450,7 +510,8 @@ struct SpreadChoice {
 
 // Codes that the one-unit decoder keeps two sums per variable for (its order
 // of additions is the one followed here) and codes that no one-unit kernel
-// takes; batches that leave kSpMembers compute units to a frame: with 25
+// takes (in the packages' arithmetic, so that a frame's results do not depend on
+// the batch); batches that leave kSpMembers compute units to a frame: with 25
 // frames on 10 units each the exchange's traffic makes it slower (p = 2000 133
 // us for 115).
 bool choose_spread(const ldpc_graph* g, int rule, int gamma, SpreadChoice& c) {
@@ -458,7 +519,8 @@ bool choose_spread(const ldpc_graph* g, int rule, int gamma, SpreadChoice& c) {
     if (g->kind != LDPC_GRAPH_QC || D.J != kSpRows || gamma < 1) return false;
     const char* path = std::getenv("LDPC_BLOCK_PATH");
     if (path && (std::strcmp(path, "onchip") == 0 || std::strcmp(path, "packages") == 0)) return false;
-    if (onchip_fits(g) ? !onchip_pairs(g) || D.p < kSpLeastP : D.p < kSpLeastLongP) return false;
+    const bool unit = onchip_fits(g);
+    if (unit ? !onchip_pairs(g) || D.p < kSpLeastP : D.p < kSpLeastLongP) return false;
     for (int j = 0; j < D.J; ++j)
         if (D.rstart[j + 1] - D.rstart[j] != D.L) return false;   // a zero block
     int dev = 0, cus = 0;
@@ -473,7 +535,7 @@ bool choose_spread(const ldpc_graph* g, int rule, int gamma, SpreadChoice& c) {
     c.members = (D.p + c.tb - 1) / c.tb;
     c.v = nullptr;
     for (const SpreadVariant& v : kSpread)
-        if (v.dc == D.L && v.rule == rule) c.v = &v;
+        if (v.dc == D.L && v.rule == rule + (unit ? 0 : 2)) c.v = &v;
     c.verdict = (size_t)gamma * 2 * D.E * sizeof(uint64_t);
     c.ticket = c.verdict + (size_t)gamma * 2 * kSpMembers * sizeof(uint64_t);
     c.total = c.ticket + ((size_t)(1 + gamma) * sizeof(uint32_t) + 15) / 16 * 16;
