@@ -33,6 +33,11 @@ __device__ __forceinline__ float unscale2(float L, float mu) {
     return clip30(fabsf(L) < 64.0f ? __builtin_copysignf(x, L) : L);
 }
 
+// Posterior in natural units from the base-2 sum S of the alphas alone and the
+// channel LLR mu.  Where S can be had this is the better form: L's rounding,
+// that of the sum with mu, does not come in.
+__device__ __forceinline__ float posterior2(float S, float mu) { return fmaf(S, kLn2F, mu); }
+
 // Eq. 3 for one row in base-2 units, in place: x[k] = beta of slot k on
 // entry, alpha of slot k on return (k < d; the other slots are left with
 // values nobody reads).  In terms of e = 2^-|beta|, the ratio of the two
