@@ -27,7 +27,8 @@
 // literal tanh product saturates at 1.
 //
 // Variable-node update (Eq. 4, 5).  beta_k = clip(mu + sum_{k' != k} alpha_k')
-// by prefix/suffix sums (never L - alpha_k), L = mu + sum alpha; hard decision
+// by prefix/suffix sums (not L - alpha_k, except where the sweeps of sweep.hip,
+// which do so, take a convolutional code too), L = mu + sum alpha; hard decision
 // c = (L < 0) (Eq. 6) packed by wave ballots into 64-bit words.
 //
 // Early stopping (an addition to the paper, which always runs I_max
@@ -1083,6 +1084,7 @@ struct ConvParams {
     float* msg;       // [tiles][R * eps][Gt]
     float* mu;        // [tiles][R * c][Gt]
     int tiles, rows, gamma;
+    int one_sum;      // VN: betas as the sweeps form them
 };
 
 template <int DCMAX, int FPL>
@@ -1121,13 +1123,50 @@ __global__ void __launch_bounds__(kBlock) conv_cn_kernel(const ConvDesc D, const
         if (R.valid(D, S, k) && R.writable(S, k)) store_frames<FPL>(mt + (size_t)R.pkg(D, S, U, k) * Gt, io[k]);
 }
 
-// One variable column: the posterior from the channel LLR and the alphas of
-// layers lo..hi in ascending order, betas (the posterior less the own alpha,
-// clipped) on every existing edge.
+// Sum of a variable's alphas, for its posterior, and in their place its betas.
+// A beta is the sum of mu and the alphas before the own, added in ascending
+// order, plus the sum of those behind, added in descending order.
+template <int DV>
+__device__ __forceinline__ float conv_betas(float mu, float (&a)[DV]) {
+    float suf[DV];
+    suf[DV - 1] = 0.0f;
+#pragma unroll
+    for (int k = DV - 2; k >= 0; --k) suf[k] = suf[k + 1] + a[k + 1];
+    const float sum = a[0] + suf[0];
+    float pre = fmaf(mu, kLog2eF, a[0]);
+    a[0] = clip2(fmaf(mu, kLog2eF, suf[0]));
+#pragma unroll
+    for (int k = 1; k < DV; ++k) {
+        const float b = pre + suf[k];
+        pre += a[k];
+        a[k] = clip2(b);
+    }
+    return sum;
+}
+
+// The same as the sweeps of sweep.hip have it, which keep one sum L per
+// variable: a beta is L less the own alpha, that of the last edge (`last`) L as
+// it was before that edge's alpha came.
+template <int DV>
+__device__ __forceinline__ float conv_betas_of_sum(float mu, float (&a)[DV], int last) {
+    float L = fmaf(mu, kLog2eF, a[0]), before = mu * kLog2eF + 0.0f, sum = 0.0f + a[0];
+#pragma unroll
+    for (int k = 1; k < DV; ++k) {
+        before = k == last ? L : before;
+        L += a[k];
+        sum += a[k];
+    }
+#pragma unroll
+    for (int k = 0; k < DV; ++k) a[k] = clip2(k == last ? before : L - a[k]);
+    return sum;
+}
+
+// One variable column from the channel LLR and the alphas of layers lo..hi:
+// betas on every existing edge, and the sum of the alphas.
 template <int DVMAX, int FPL>
 __device__ __forceinline__ void conv_vn_column(const ConvDesc& D, const ConvSlots& S, const ConvUnits& U,
                                                const ConvParams& P, const ConvCol& C, int tile, int lane,
-                                               float (&L)[FPL]) {
+                                               float (&sum)[FPL]) {
     constexpr int Gt = 64 * FPL;
     const size_t lane_off = (size_t)lane * FPL;
     float* mt = P.msg + (size_t)tile * U.ring * U.eps * Gt + lane_off;
@@ -1145,11 +1184,12 @@ __device__ __forceinline__ void conv_vn_column(const ConvDesc& D, const ConvSlot
     }
 #pragma unroll
     for (int f = 0; f < FPL; ++f) {
-        L[f] = mu[f];
+        float x[DVMAX];
 #pragma unroll
-        for (int k = 0; k < DVMAX; ++k) L[f] += a[k][f];
+        for (int k = 0; k < DVMAX; ++k) x[k] = a[k][f];
+        sum[f] = P.one_sum ? conv_betas_of_sum(mu[f], x, (D.ms + 1) * D.Jb - 1) : conv_betas(mu[f], x);
 #pragma unroll
-        for (int k = 0; k < DVMAX; ++k) a[k][f] = clip2(L[f] - a[k][f]);
+        for (int k = 0; k < DVMAX; ++k) a[k][f] = x[k];
     }
 #pragma unroll
     for (int k = 0; k < DVMAX; ++k)
@@ -1219,10 +1259,10 @@ __global__ void __launch_bounds__(kOutBlock) conv_vn_out_kernel(const ConvDesc D
     const int64_t oc = (int64_t)U.pos[U.out_unit] * D.c + c0 + var;
     const int nvalid = min(P.gamma - tile * Gt, Gt);
     for (int fr = threadIdx.x / kOutVars; fr < nvalid; fr += kOutBlock / kOutVars) {
-        const float L = Ls[var][fr];
         const size_t o = (size_t)(tile * Gt + fr) * ld + oc;
-        post[o] = unscale2(L, llr[o]);
-        bits_out[o] = (uint8_t)(L < 0.0f);
+        const float x = posterior2(Ls[var][fr], llr[o]);
+        post[o] = clip30(x);
+        bits_out[o] = (uint8_t)(x < 0.0f);
     }
 }
 
@@ -1259,9 +1299,9 @@ __global__ void __launch_bounds__(kIngestBlock) conv_ingest_kernel(const ConvDes
         const int t = t0 + pu;
         const int q = rem / D.p, uu = rem - q * D.p;
         const int slot = t % U.ring;
-        const float mu = tileS[tx][r] * kLog2eF + 0.0f;   // base-2 units; never -0
+        const float mu = tileS[tx][r] + 0.0f;   // never -0
         P.mu[((size_t)tile * U.ring * D.c + (size_t)slot * D.c + rem) * Gt + fl] = mu;
-        const float b = clip2(mu);
+        const float b = clip2(mu * kLog2eF + 0.0f);
         const int jc = t % D.T;
         for (int k = 0; k < nslots; ++k) {
             const int dd = S.vn_dd[k], rr = S.vn_rr[k];
@@ -1369,9 +1409,9 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                 const int t = in_lo + pu;
                 const int q = rem / D.p, uu = rem - q * D.p;
                 const int slot = t % R;
-                const float m = x[(int64_t)t * D.c + rem] * kLog2eF + 0.0f;   // base-2 units; never -0
+                const float m = x[(int64_t)t * D.c + rem] + 0.0f;   // never -0
                 mu[slot * D.c + rem] = m;
-                const float b = clip2(m);
+                const float b = clip2(m * kLog2eF + 0.0f);
                 const int jc = t % D.T;
                 for (int k = 0; k < nvs; ++k) {
                     const int dd = S.vn_dd[k], rr = S.vn_rr[k];
@@ -1457,6 +1497,12 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
             for (int e = 0; e < DCMAX; ++e)
                 if (idx[e] >= 0 && u >= cdd[e]) msg[idx[e]] = in[e];   // position s + u - dd is not frozen
         };
+        // posterior and decision of variable o of the output from the sum of its alphas
+        auto decide = [&](float sum, size_t o) {
+            const float x = posterior2(sum, llr[o]);
+            post[o] = clip30(x);
+            bits_out[o] = (uint8_t)(x < 0.0f);
+        };
         // variable column (unit u = position s + u, circulant column q,
         // offset uu; rem = q * p + uu); the table holds the edge's ring
         // offset minus its shift, so the package is base + uu (+ p on wrap)
@@ -1485,16 +1531,10 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                 if (full) {
 #pragma unroll
                     for (int e = 0; e < DVMAX; ++e) a[e] = msg[idx[e]];
-                    float L = m;
+                    const float sum = conv_betas(m, a);
 #pragma unroll
-                    for (int e = 0; e < DVMAX; ++e) L += a[e];
-#pragma unroll
-                    for (int e = 0; e < DVMAX; ++e) msg[idx[e]] = clip2(L - a[e]);
-                    if (out && u == 0) {
-                        const size_t o = frame_off + (size_t)s * D.c + rem;
-                        post[o] = unscale2(L, llr[o]);
-                        bits_out[o] = (uint8_t)(L < 0.0f);
-                    }
+                    for (int e = 0; e < DVMAX; ++e) msg[idx[e]] = a[e];
+                    if (out && u == 0) decide(sum, frame_off + (size_t)s * D.c + rem);
                     return;
                 }
             }
@@ -1506,17 +1546,11 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                 // only messages from window layers (s + u + dd <= lay_hi) are summed
                 a[e] = (o != kNoEdge && u + vdd[e] <= span) ? msg[i] : 0.0f;
             }
-            float L = m;
-#pragma unroll
-            for (int e = 0; e < DVMAX; ++e) L += a[e];
+            const float sum = conv_betas(m, a);
 #pragma unroll
             for (int e = 0; e < DVMAX; ++e)
-                if (idx[e] >= 0) msg[idx[e]] = clip2(L - a[e]);
-            if (out && u == 0) {
-                const size_t o = frame_off + (size_t)s * D.c + rem;
-                post[o] = unscale2(L, llr[o]);
-                bits_out[o] = (uint8_t)(L < 0.0f);
-            }
+                if (idx[e] >= 0) msg[idx[e]] = a[e];
+            if (out && u == 0) decide(sum, frame_off + (size_t)s * D.c + rem);
         };
         // fixed columns (at most kWinPre per thread): each edge's package for
         // this slide, worked out once for the K iterations: >= 0 summed
@@ -1573,19 +1607,13 @@ __global__ void __launch_bounds__(kWinBlock) window_lds_kernel(const ConvDesc D,
                         float a[DVMAX];
 #pragma unroll
                         for (int e = 0; e < DVMAX; ++e) a[e] = vix[j][e] >= 0 ? msg[vix[j][e]] : 0.0f;
-                        float L = m;
-#pragma unroll
-                        for (int e = 0; e < DVMAX; ++e) L += a[e];
+                        const float sum = conv_betas(m, a);
 #pragma unroll
                         for (int e = 0; e < DVMAX; ++e) {
                             const int v = vix[j][e];
-                            if (v != -1) msg[v >= 0 ? v : -2 - v] = clip2(L - a[e]);
+                            if (v != -1) msg[v >= 0 ? v : -2 - v] = a[e];
                         }
-                        if (k == K && cu0 + j * cstep == 0) {
-                            const size_t o = frame_off + (size_t)s * D.c + crem0;
-                            post[o] = unscale2(L, llr[o]);
-                            bits_out[o] = (uint8_t)(L < 0.0f);
-                        }
+                        if (k == K && cu0 + j * cstep == 0) decide(sum, frame_off + (size_t)s * D.c + crem0);
                     }
                 }
             }
@@ -2653,6 +2681,7 @@ ldpc_status ldpc_decode_pipeline(const ldpc_graph* g, const float* llr, int32_t 
                        hipGetLastError() == hipSuccess ? LDPC_OK : LDPC_EHIP;
     }
     ConvRun r = make_conv_run(g, llr, gamma, post, bits, reinterpret_cast<char*>(workspace), lay, tl, st);
+    r.P.one_sum = sweep_takes(g);
     (void)hipGetLastError();
     switch (tl.fpl) {
         case 4: run_pipeline<4>(r, iters); break;

@@ -28,6 +28,10 @@ struct SweepPlan {
 // one circulant row per layer: T = 3 with 2 columns per position, T = 4 with 6).
 bool sweep_plan(const ldpc_graph* g, int gamma, int iters, SweepPlan& plan);
 
+// Whether they cover g at some batch.  The ring forms messages and sums of such a
+// code as the sweeps do, so that results do not depend on which of them runs.
+bool sweep_takes(const ldpc_graph* g);
+
 // Enqueues the decode; false when a launch failed.
 bool sweep_decode(const ldpc_graph* g, const SweepPlan& plan, const float* llr, int gamma, int iters, float* post,
                   uint8_t* bits, void* workspace, hipStream_t st);

@@ -5,29 +5,33 @@
 // window_lds_kernel of decode.hip, which takes the other codes, keeps every
 // edge message of the window in LDS and passes over them twice per iteration
 // (check rows, then variables).  Here a thread owns a check row of up to NW
-// layers of the window and keeps their check-to-variable messages alpha in
-// registers; LDS holds the posterior sums L of the window's W positions, those
-// of the previous iteration and those being formed.  A variable-to-check
-// message is clip(L - alpha).  Per iteration: every row is updated from the
-// previous sums and starts its own position's new sums (mu + alpha, mu in
-// registers); after a barrier the layers add their messages to the positions
-// one back, after another to those two back, so that the sums are formed in
-// order of the layers (each is met once per step) as in the other forms, with
-// which the results agree bit for bit; a third barrier ends the iteration.
+// layers of the window and keeps their messages in registers; LDS holds two
+// sums per variable, so that a beta is the sum of the other alphas, as in the
+// other forms, with which the results agree bit for bit.  A position t is met
+// by layers t, t + 1 and t + 2.  Per iteration, after the rows' update:
 //
-// A position that leaves the window is frozen: where a later layer meets it,
-// the row's register holds the message beta it last sent in place of alpha
-// (+infinity, the identity of the row's products, where the chain has no such
-// position).
+//   * layer t writes the prefix mu + a_t, layer t + 2 the suffix a_t+2;
+//   * after a barrier layer t + 1 reads both, which sum to its beta, and adds
+//     a_t+1 to both;
+//   * after another the prefix is the beta of layer t + 2, mu and the suffix
+//     that of layer t; they are read as the next update begins, and a third
+//     barrier ends the reading.
+//
+// The posterior of a position that leaves is mu + ln 2 (a_t + suffix).  From
+// then on it is frozen: where a later layer meets it, the row's register holds
+// the beta it last sent (+infinity, the identity of the row's products, where
+// the chain has no such position).
 //
 // The layers are dealt to G groups of threads by their number modulo G, so a
 // layer stays with its thread while the window slides; in a group's registers
 // layers move down by one when its oldest leaves.
 //
 // Bound by the vector ALUs and the latency of a row's chain between two
-// barriers.  p = 512, 128 positions, 512 streams, W = 6, 10 iterations: 7.75
-// ms (1.55 10^12 edge updates per second); 13.0 ms with the messages in LDS
-// and the same check rule, 14.8 ms before that.
+// barriers.  p = 512, 128 positions, 512 streams, W = 6, 10 iterations: 7.30
+// ms (1.64 10^12 edge updates per second); 13.0 ms with the messages in LDS
+// and the same check rule, 14.8 ms before that.  With one sum L per variable
+// and beta = clip(L - alpha) it took 7.75 ms, at 1.07-1.10 times the error of
+// these sums against 64 bits before the change of check rule; now 0.86-0.95.
 #include <hip/hip_runtime.h>
 
 #include "check2.h"
@@ -57,18 +61,22 @@ __device__ __forceinline__ float* wd_at(float* base, uint32_t byte) {
 template <int NW, int MAXT, int WPE>
 __global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
     constexpr int T = kWdPeriod, LB = kWdCols, DC = kWdSlots, MS = T - 1;
-    extern __shared__ float sums[];   // [2][W][LB][p]
+    static_assert(MS == 2, "three layers meet a position");
+    extern __shared__ float sums[];   // prefixes [W][LB][p], suffixes [W][LB][p]
     const int p = A.p, P = A.positions, W = A.W;
-    const uint32_t p4 = 4u * (uint32_t)p, c4 = LB * p4, other = (uint32_t)W * c4;
+    const uint32_t p4 = 4u * (uint32_t)p, c4 = LB * p4, behind = (uint32_t)W * c4;   // the suffixes
     const int g = __builtin_amdgcn_readfirstlane((int)threadIdx.x / A.per);
     const uint32_t s4 = 4u * (threadIdx.x - (uint32_t)(g * A.per));
     const bool own = s4 < p4;
     const size_t frame = (size_t)blockIdx.x * P * LB * p;
     const float* __restrict__ mu = A.llr + frame;
 
-    float al[NW][DC];            // alpha, or the beta of a frozen (+inf: missing) position
+    // Edge slots of the oldest position (2 layers back), the one after, the
+    // layer's own.  al: alphas, then betas, of a row's edges; the last beta for
+    // a frozen position, +inf where there is none.
+    float al[NW][DC];
     uint32_t offs[NW][DC / 2];   // offsets of the edges' variables in their positions, two to a register
-    float m0[NW][LB];            // channel LLRs that the newest position's sums start from
+    float m0[NW][LB];            // channel LLRs of the layer's own position
     auto off = [&](int j, int k) -> uint32_t { return k % 2 ? offs[j][k / 2] >> 16 : offs[j][k / 2] & 0xffffu; };
     auto open_layer = [&](int j, int tau) {
         const int cls = tau % T;
@@ -86,7 +94,29 @@ __global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
         if (tau < P) {
 #pragma unroll
             for (int q = 0; q < LB; ++q)
-                m0[j][q] = mu[(size_t)tau * (LB * p) + (off(j, MS * LB + q) >> 2)] * kLog2eF + 0.0f;
+                m0[j][q] = (mu + (size_t)tau * (LB * p))[off(j, MS * LB + q) >> 2] + 0.0f;
+        }
+    };
+    for (int i = threadIdx.x; i < min(W, P) * LB * p; i += blockDim.x) {
+        sums[i] = mu[i] * kLog2eF + 0.0f;
+        sums[W * LB * p + i] = 0.0f;
+    }
+    __syncthreads();
+
+    int sW = 0;          // s mod W
+    int w0 = g;          // the group's oldest layer is s + w0
+    // ring offset of position s + w, -MS <= w < W
+    auto slot = [&](int w) -> uint32_t {
+        int r = sW + w;
+        r = r < 0 ? r + W : r;
+        return (uint32_t)(r >= W ? r - W : r) * c4;
+    };
+    // layer s + w of a row comes into the window: its first beta for the
+    // position before its own
+    auto enter = [&](int j, int s, int w) {
+        if ((uint32_t)(s + w - 1) < (uint32_t)P) {
+#pragma unroll
+            for (int q = 0; q < LB; ++q) al[j][LB + q] = clip2(*wd_at(sums, slot(w - 1) + off(j, LB + q)));
         }
     };
 #pragma unroll
@@ -97,117 +127,102 @@ __global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
         for (int k = 0; k < DC / 2; ++k) offs[j][k] = 0u;
 #pragma unroll
         for (int q = 0; q < LB; ++q) m0[j][q] = 0.0f;
-        if (own) open_layer(j, g + j * A.groups);
+        if (own) {
+            const int w = g + j * A.groups;
+            open_layer(j, w);
+            if (w < W) enter(j, 0, w);
+        }
     }
-    for (int i = threadIdx.x; i < min(W, P) * LB * p; i += blockDim.x) sums[i] = mu[i] * kLog2eF + 0.0f;
-    __syncthreads();
-
-    uint32_t cur = 0;    // LDS offset of the current sums
-    int sW = 0;          // s mod W
-    int w0 = g;          // the group's oldest layer is s + w0
     for (int s = 0; s < P; ++s) {
-        // ring offset of position s + w, -MS <= w < W
-        auto slot = [&](int w) -> uint32_t {
-            int r = sW + w;
-            r = r < 0 ? r + W : r;
-            return (uint32_t)(r >= W ? r - W : r) * c4;
-        };
         auto live = [&](int w) { return w < W && s + w < A.layers; };                // layer s + w is in the window
         auto active = [&](int w, int dd) { return w >= dd && s + w - dd < P; };      // and meets position s + w - dd
         for (int it = 0; it < A.K; ++it) {
-            const uint32_t old = cur, fresh = other - cur;
             if (own) {
 #pragma unroll
                 for (int j = 0; j < NW; ++j) {
                     const int w = w0 + j * A.groups;
                     if (!live(w)) continue;
-                    float x[DC];
-                    if (w >= MS && s + w < P) {
+                    if (active(w, 2)) {
 #pragma unroll
-                        for (int dd = MS; dd >= 0; --dd) {
-                            const uint32_t base = old + slot(w - dd);
+                        for (int q = 0; q < LB; ++q) al[j][q] = clip2(*wd_at(sums, slot(w - 2) + off(j, q)));
+                    }
+                    if (active(w, 0)) {
 #pragma unroll
-                            for (int q = 0; q < LB; ++q) {
-                                const int k = (MS - dd) * LB + q;
-                                x[k] = *wd_at(sums, base + off(j, k));
-                            }
+                        for (int q = 0; q < LB; ++q) {
+                            const int k = 2 * LB + q;
+                            al[j][k] = clip2(fmaf(m0[j][q], kLog2eF, *wd_at(sums, behind + slot(w) + off(j, k))));
                         }
-#pragma unroll
-                        for (int k = 0; k < DC; ++k) al[j][k] = clip2(x[k] - al[j][k]);
+                    }
+                    if (w >= MS && s + w < P) {
                         check2e_row<DC, 1>(al[j], DC);
                     } else {
+                        float x[DC];
 #pragma unroll
-                        for (int dd = MS; dd >= 0; --dd) {
-#pragma unroll
-                            for (int q = 0; q < LB; ++q) {
-                                const int k = (MS - dd) * LB + q;
-                                x[k] = active(w, dd) ? clip2(*wd_at(sums, old + slot(w - dd) + off(j, k)) - al[j][k])
-                                                     : al[j][k];
-                            }
-                        }
+                        for (int k = 0; k < DC; ++k) x[k] = al[j][k];
                         check2e_row<DC, 1>(x, DC);
 #pragma unroll
                         for (int k = 0; k < DC; ++k)
                             if (active(w, MS - k / LB)) al[j][k] = x[k];
                     }
-                    if (s + w < P) {
-                        const uint32_t base = fresh + slot(w);
-#pragma unroll
-                        for (int q = 0; q < LB; ++q)
-                            *wd_at(sums, base + off(j, MS * LB + q)) = m0[j][q] + al[j][MS * LB + q];
-                    }
                 }
             }
             __syncthreads();
-#pragma unroll
-            for (int dd = 1; dd <= MS; ++dd) {
-                if (own) {
-                    float v[NW][LB];
-#pragma unroll
-                    for (int j = 0; j < NW; ++j) {
-                        const int w = w0 + j * A.groups;
-                        if (!live(w) || !active(w, dd)) continue;
-#pragma unroll
-                        for (int q = 0; q < LB; ++q)
-                            v[j][q] = *wd_at(sums, fresh + slot(w - dd) + off(j, (MS - dd) * LB + q));
-                    }
-#pragma unroll
-                    for (int j = 0; j < NW; ++j) {
-                        const int w = w0 + j * A.groups;
-                        if (!live(w) || !active(w, dd)) continue;
-#pragma unroll
-                        for (int q = 0; q < LB; ++q) {
-                            const int k = (MS - dd) * LB + q;
-                            *wd_at(sums, fresh + slot(w - dd) + off(j, k)) = v[j][q] + al[j][k];
-                        }
-                    }
-                }
-                __syncthreads();
-            }
-            cur = fresh;
-        }
-        // position s is decided and freezes: the layers that meet it from now on keep the beta it last sent
-        {
-            const uint32_t base = cur + slot(0);
-            const size_t v0 = (size_t)s * (LB * p);
-            for (int i = threadIdx.x; i < LB * p; i += blockDim.x) {
-                const float L = *wd_at(sums, base + 4u * (uint32_t)i);
-                A.post[frame + v0 + i] = unscale2(L, mu[v0 + i]);
-                A.bits[frame + v0 + i] = (uint8_t)(L < 0.0f);
-            }
             if (own) {
 #pragma unroll
                 for (int j = 0; j < NW; ++j) {
                     const int w = w0 + j * A.groups;
                     if (!live(w)) continue;
 #pragma unroll
-                    for (int dd = 1; dd <= MS; ++dd) {
-                        if (w != dd) continue;
+                    for (int q = 0; q < LB; ++q) {
+                        const int k = 2 * LB + q;
+                        if (active(w, 0)) *wd_at(sums, slot(w) + off(j, k)) = fmaf(m0[j][q], kLog2eF, al[j][k]);
+                        if (active(w, 2)) *wd_at(sums, behind + slot(w - 2) + off(j, q)) = al[j][q];
+                    }
+                }
+            }
+            __syncthreads();
+            if (own) {
 #pragma unroll
-                        for (int q = 0; q < LB; ++q) {
-                            const int k = (MS - dd) * LB + q;
-                            al[j][k] = clip2(*wd_at(sums, base + off(j, k)) - al[j][k]);
-                        }
+                for (int j = 0; j < NW; ++j) {
+                    const int w = w0 + j * A.groups;
+                    if (!live(w) || !active(w, 1)) continue;
+                    float u[LB], v[LB];
+#pragma unroll
+                    for (int q = 0; q < LB; ++q) {
+                        const uint32_t at = slot(w - 1) + off(j, LB + q);
+                        u[q] = *wd_at(sums, at);
+                        v[q] = live(w + 1) ? *wd_at(sums, behind + at) : 0.0f;
+                    }
+#pragma unroll
+                    for (int q = 0; q < LB; ++q) {
+                        const uint32_t at = slot(w - 1) + off(j, LB + q);
+                        const float x = al[j][LB + q];
+                        *wd_at(sums, at) = u[q] + x;
+                        *wd_at(sums, behind + at) = v[q] + x;
+                        al[j][LB + q] = clip2(u[q] + v[q]);
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        // Position s is decided, by its own layer's rows, and freezes: the
+        // layers that meet it from now on keep the beta they last sent.
+        if (own) {
+#pragma unroll
+            for (int j = 0; j < NW; ++j) {
+                const int w = w0 + j * A.groups;
+                if (!live(w)) continue;
+#pragma unroll
+                for (int q = 0; q < LB; ++q) {
+                    if (w == 0) {
+                        const int k = 2 * LB + q;
+                        const float S = al[j][k] + *wd_at(sums, behind + slot(0) + off(j, k));
+                        const float x = posterior2(S, m0[j][q]);
+                        const size_t at = frame + (size_t)s * (LB * p);   // the same for all threads
+                        (A.post + at)[off(j, k) >> 2] = clip30(x);
+                        (A.bits + at)[off(j, k) >> 2] = (uint8_t)(x < 0.0f);
+                    } else if (w == MS) {
+                        al[j][q] = clip2(*wd_at(sums, slot(0) + off(j, q)));
                     }
                 }
             }
@@ -215,10 +230,12 @@ __global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
         __syncthreads();
         // position s + W enters with its channel LLRs; layer s leaves, layer s + W enters
         if (s + W < P) {
-            const uint32_t base = cur + slot(0);
+            const uint32_t base = slot(0);
             const size_t v0 = (size_t)(s + W) * (LB * p);
-            for (int i = threadIdx.x; i < LB * p; i += blockDim.x)
+            for (int i = threadIdx.x; i < LB * p; i += blockDim.x) {
                 *wd_at(sums, base + 4u * (uint32_t)i) = mu[v0 + i] * kLog2eF + 0.0f;
+                *wd_at(sums, behind + base + 4u * (uint32_t)i) = 0.0f;
+            }
         }
         if (w0 == 0) {
             w0 = A.groups - 1;
@@ -234,6 +251,11 @@ __global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
             if (own) open_layer(NW - 1, s + NW * A.groups);
         } else {
             --w0;
+        }
+        if (own) {
+#pragma unroll
+            for (int j = 0; j < NW; ++j)
+                if (w0 + j * A.groups == W - 1) enter(j, s, W);
         }
         sW = sW + 1 == W ? 0 : sW + 1;
         __syncthreads();
@@ -252,8 +274,9 @@ int window_decode(const ldpc_graph* g, const float* llr, int gamma, int W, int K
     const int per = (g->p + 63) / 64 * 64;
     // Layers per thread: the fewest that 1024 threads can hold the window with
     // (rows of one thread are updated one after the other).  W = 6, 10
-    // iterations: p = 52, 128 streams, 1, 2, 3 or 6 layers: 153, 231, 315, 592
-    // us; p = 512, 256 streams, 3 or 6: 4.52 and 5.80 ms.
+    // iterations: p = 52, 20 positions, 128 streams, 1, 2, 3 or 6 layers: 152,
+    // 237, 336, 597 us; p = 512, 128 positions, 256 streams, 3 or 6: 4.36 and
+    // 5.60 ms.
     int nw = 0;
     for (int n : {6, 3, 2, 1})
         if ((W + n - 1) / n * per <= 1024) nw = n;
@@ -283,8 +306,8 @@ int window_decode(const ldpc_graph* g, const float* llr, int gamma, int W, int K
             A.sh4[m * kWdSlots + k] =
                 4u * (uint32_t)g->sf[(m * kWdPeriod + (g->ms - k / kWdCols)) * kWdCols + k % kWdCols];
     // With more streams than compute units, 64 registers, so that two
-    // workgroups of 1024 threads share one (p = 512, 512 streams: 7.75 ms
-    // against 9.05; 256 streams: 4.60 against 4.52).
+    // workgroups of 1024 threads share one (p = 512, 512 streams: 7.29 ms
+    // against 8.70; 256 streams: 4.46 against 4.35).
     const bool two = gamma > 256;
     const void* fn = nw == 1 ? reinterpret_cast<const void*>(&window_kernel<1, 1024, 8>)
                      : nw == 2 ? (two ? reinterpret_cast<const void*>(&window_kernel<2, 1024, 8>)
