@@ -12,7 +12,8 @@
 //     keeps the check-to-variable messages alpha of those rows' edges in
 //     registers for the whole decode;
 //   * LDS holds, for every variable, the posterior sum L = mu + sum alpha
-//     (Eq. 5) of two consecutive iterations;
+//     (Eq. 5) of two consecutive iterations; it starts with mu, scaled, and
+//     the first alpha in one fused multiply-add;
 //   * the variable-to-check message of an edge is recovered as
 //     beta = clip(L_v - alpha_e) (Eq. 4 written as "all but the own edge")
 //     from the previous iteration's sum and the edge's own alpha, so no beta
@@ -112,10 +113,10 @@ __device__ __forceinline__ float* lds_ptr(float2* L, uint32_t byte) {
 }
 
 // Messages and sums are carried in base-2 units (check2.h): the channel
-// LLRs are scaled by log2(e) once when read and the posteriors unscaled when
+// LLRs are scaled by log2(e) as a sum starts and the posteriors unscaled when
 // written.
 
-// Regular bases with rows of weight <= 6 keep the scaled channel LLRs of the
+// Regular bases with rows of weight <= 6 keep the channel LLRs of the
 // thread's base-row-0 edges in registers (the 3 x 9 rows would spill them);
 // the others read them from the frame's LLRs in L2 when a sum starts.
 constexpr bool oc_mu_in_regs(bool reg, int dc) { return reg && dc <= 6; }
@@ -136,7 +137,7 @@ constexpr uint32_t oc_odd(bool reg, int nq, int dc) { return oc_split(reg, nq, d
 // immediate offsets of one address.  The signs read are the previous
 // iteration's decisions: with SYN and flag != NULL, a wave with a violated
 // row sets *flag (SYN = false compiles the test out, for decodes without
-// early stopping).  mu0: with oc_mu_in_regs, the scaled channel LLRs of the thread's
+// early stopping).  mu0: with oc_mu_in_regs, the channel LLRs of the thread's
 // base-row-0 edges (their variables' sums start there).
 template <int NJ, int NQ, int DC, bool REG, int RULE, int PAR, bool SYN>
 __device__ __forceinline__ void oc_iteration(const OnchipArgs& A, float2* L, const float* __restrict__ mu,
@@ -195,7 +196,7 @@ __device__ __forceinline__ void oc_iteration(const OnchipArgs& A, float2* L, con
                             const uint32_t at = oc_split(REG, NQ, DC) ? va[k] - (uint32_t)A.cb8[k] + (uint32_t)A.gb4[k]
                                                                   : va[k] >> 1;
                             const float m = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(mu) + at);
-                            acc[k] = m * kLog2eF + 0.0f;
+                            acc[k] = m + 0.0f;   // no -0
                         } else {
                             acc[k] = lds_at(L, va[k] + kNew);
                         }
@@ -205,7 +206,8 @@ __device__ __forceinline__ void oc_iteration(const OnchipArgs& A, float2* L, con
                 for (int k = 0; k < DC; ++k) {
                     if (REG || k < d) {
                         al[j][q][k] = in[k];
-                        *lds_ptr(L, va[k] + kNew) = acc[k] + in[k];
+                        const bool first = REG ? (j == 0) : ((A.first >> (j * kOcSlots + k)) & 1ull);
+                        *lds_ptr(L, va[k] + kNew) = fmaf(acc[k], first ? kLog2eF : 1.0f, in[k]);
                     }
                 }
             }
@@ -250,7 +252,7 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
                 if (s8 < p8)
                     mu0[q][l] = *reinterpret_cast<const float*>(
                                     reinterpret_cast<const char*>(mu) +
-                                    (A.gb4[l] + oc_wrap8(s8 + A.rot8[l], p8) / (kUnit / 4))) * kLog2eF + 0.0f;
+                                    (A.gb4[l] + oc_wrap8(s8 + A.rot8[l], p8) / (kUnit / 4))) + 0.0f;   // no -0
             }
         }
 #pragma unroll
@@ -258,7 +260,7 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
             const uint32_t s8 = kUnit * (uint32_t)tid + (uint32_t)q * TB8;
 #pragma unroll
             for (int l = 0; l < DC; ++l)
-                if (s8 < p8) *lds_ptr(Lpair, A.cb8[l] + s8) = mu0[q][l];
+                if (s8 < p8) *lds_ptr(Lpair, A.cb8[l] + s8) = mu0[q][l] * kLog2eF + 0.0f;
         }
     } else {
         if constexpr (REG) {   // a full base has DC columns: their loads go out together
@@ -362,37 +364,27 @@ __global__ void __launch_bounds__(MAXT) onchip_block_kernel(const int n, const i
         for (int q = 0; q < NQ; ++q) {
             const uint32_t s8 = kUnit * (uint32_t)tid + (uint32_t)q * TB8;
             if (s8 >= p8) continue;
-            uint32_t v[DC];
-            float m[DC];
 #pragma unroll
             for (int l = 0; l < DC; ++l) {
-                v[l] = ((uint32_t)A.gb4[l] + oc_wrap8(s8 + A.rot8[l], p8) / (kUnit / 4)) >> 2;
-                m[l] = mu[v[l]];
-            }
-#pragma unroll
-            for (int l = 0; l < DC; ++l) {
+                const uint32_t v = ((uint32_t)A.gb4[l] + oc_wrap8(s8 + A.rot8[l], p8) / (kUnit / 4)) >> 2;
                 const float x = lds_at(Lpair, A.cb8[l] + s8 + kOdd * (uint32_t)comp);
-                A.post[f0 + v[l]] = unscale2(x, m[l]);
-                A.bits[f0 + v[l]] = (uint8_t)(x < 0.0f);
+                A.post[f0 + v] = unscale2(x);
+                A.bits[f0 + v] = (uint8_t)(x < 0.0f);
             }
         }
     } else {
-        auto put = [&](int v, float x, float m) {
-            A.post[f0 + v] = unscale2(x, m);
+        auto put = [&](int v, float x) {
+            A.post[f0 + v] = unscale2(x);
             A.bits[f0 + v] = (uint8_t)(x < 0.0f);
         };
         if constexpr (REG) {
             for (int u = tid; u < p; u += TB) {
-                float m[DC];
-#pragma unroll
-                for (int l = 0; l < DC; ++l) m[l] = mu[l * p + u];
 #pragma unroll
                 for (int l = 0; l < DC; ++l)
-                    put(l * p + u, lds_at(Lpair, (uint32_t)A.cb8[l] + kUnit * (uint32_t)u + kOdd * (uint32_t)comp),
-                        m[l]);
+                    put(l * p + u, lds_at(Lpair, (uint32_t)A.cb8[l] + kUnit * (uint32_t)u + kOdd * (uint32_t)comp));
             }
         } else {
-            for (int v = tid; v < n; v += TB) put(v, Lf[2 * v + comp], mu[v]);
+            for (int v = tid; v < n; v += TB) put(v, Lf[2 * v + comp]);
         }
     }
     if (tid == 0) {

@@ -106,10 +106,10 @@ __device__ __forceinline__ void sp_store(sp_word* base, uint32_t byte, uint32_t 
 // results of which those of codes that no unit takes are equal bit for bit.
 constexpr bool sp_packages(int rule) { return rule >= 2; }
 
-// Channel LLR as the sums take it.
+// Channel LLR as the sums take it (on one unit no sum is ever -0).
 template <int RULE>
 __device__ __forceinline__ float spread_mu(float mu) {
-    return sp_packages(RULE) ? mu : mu * kLog2eF + 0.0f;
+    return sp_packages(RULE) ? mu : mu + 0.0f;
 }
 
 // Sum L of a variable, and the beta that it sends to its row of base row j;
@@ -127,7 +127,7 @@ __device__ __forceinline__ float spread_sum(float m, const float (&a)[kSpRows], 
         beta = first ? from_mu : j == 0 ? b[0][0] : j == 1 ? b[1][0] : b[2][0];
         return L[0];
     } else {
-        const float L = ((m + a[0]) + a[1]) + a[2];
+        const float L = (fmaf(m, kLog2eF, a[0]) + a[1]) + a[2];
         beta = clip2(L - (j == 0 ? a[0] : j == 1 ? a[1] : a[2]));
         return L;
     }
@@ -377,7 +377,7 @@ spread_kernel(const SpreadArgs A) {
     if (tid == 0 && !judge) before = leave();
     auto put = [&](int k, uint32_t r4, float L) {
         const size_t v = f0 + (channel(0, k, r4) >> 2);
-        A.post[v] = sp_packages(RULE) ? clip30(L) : unscale2(L, raw(0, k, r4));
+        A.post[v] = sp_packages(RULE) ? clip30(L) : unscale2(L);
         A.bits[v] = (uint8_t)(L < 0.0f);
     };
     if (active && alive) {
