@@ -248,8 +248,10 @@ ldpc_status ldpc_decode_noalloc(const ldpc_graph* g, const float* llr, int32_t g
  *   iters    iterations, 1..LDPC_MAX_ITERS (the weight rows used)
  * Other arguments as for ldpc_decode (workspace from
  * ldpc_workspace_size(g, gamma, iters, 0)).  Like ldpc_decode it decodes a
- * code that fits one compute unit on chip (ldpc_decode_path; the rule above
- * in base-2 units there, within FP32 rounding of the package decoder's).
+ * code that fits one compute unit on chip (ldpc_decode_path): with two sums per
+ * variable in base-2 units, within FP32 rounding of the package decoder's
+ * results; with one (rows of weight 18 and 24, and 9 above p = 2048) bit for
+ * bit as the package decoder.
  * Errors: those of ldpc_decode, and EINVAL for NULL weights.
  */
 ldpc_status ldpc_nms_decode(const ldpc_graph* g, const float* llr, int32_t gamma, int32_t iters,

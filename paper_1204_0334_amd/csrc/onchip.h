@@ -36,4 +36,9 @@ bool onchip_wide_fits(const ldpc_graph* g);
 int onchip_wide_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
                        uint8_t* bits, int32_t* iters, uint8_t* converged, hipStream_t st, const float* nms_w);
 
+// Learned min-sum of the same codes (onchip_nms.hip), bit for bit as the message
+// packages.
+int onchip_nms_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
+                      uint8_t* bits, int32_t* iters, uint8_t* converged, hipStream_t st, const float* nms_w);
+
 }  // namespace ldpc

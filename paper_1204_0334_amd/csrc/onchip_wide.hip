@@ -1,7 +1,7 @@
 // Block decoder with a whole frame on one compute unit (gfx950), for codes
 // whose posterior sums are too large, or whose check rows are too heavy, for
 // the kernel of onchip.hip: the rate-5/6 4 x 24 codes up to n = 24,576, for
-// instance.  As there, one workgroup decodes one frame, thread i keeps the
+// instance (their learned min-sum: onchip_nms.hip).  As there, one workgroup decodes one frame, thread i keeps the
 // check-to-variable messages of check rows (j, i + q*TB) of every base row in
 // registers for the whole decode, and beta = clip(L - alpha) is formed from
 // the posterior sums in LDS.  What differs:
@@ -74,9 +74,7 @@ struct WideArgs {
     uint8_t* bits;                    // [gamma][n]
     int32_t* iters;                   // [gamma] or NULL
     uint8_t* conv;                    // [gamma] or NULL
-    const float* nms_w;               // learned min-sum (RULE 1): [iters][blocks][2]
-    int32_t n, p, L, max_iters, nb;
-    int32_t rb0[kOwRows];             // first block of base row j
+    int32_t n, p, L, max_iters;
 };
 
 __device__ __forceinline__ float* ow_cell(float* L, uint32_t byte) {
@@ -84,10 +82,10 @@ __device__ __forceinline__ float* ow_cell(float* L, uint32_t byte) {
 }
 
 // One frame per workgroup.  NJ base rows, NQ rows per thread and base row, DC
-// slots per row (the base is full: DC columns, DC blocks in every row); RULE 0:
-// sum-product, 1: learned min-sum; NB: blocks of check2e_row; MAXT: threads
+// slots per row (the base is full: DC columns, DC blocks in every row); NB:
+// blocks of check2e_row; MAXT: threads
 // the register budget is for; EARLY: with early stopping.
-template <int NJ, int NQ, int DC, int RULE, int NB, int MAXT, bool EARLY>
+template <int NJ, int NQ, int DC, int NB, int MAXT, bool EARLY>
 __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
     // dynamic LDS: L columns of p + kOwPad sums, then two flag words
     extern __shared__ float cells[];
@@ -165,10 +163,7 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
                             const float L = *ow_cell(cells, first_cell(j, q, k) + lane4);
                             x[k] = clip2(L - x[k]);
                         }
-                        if constexpr (RULE == 0)
-                            check2e_row<DC, NB>(x, DC);
-                        else
-                            nms2_row<DC>(x, DC, A.nms_w + ((size_t)(it - 1) * A.nb + A.rb0[j]) * 2, x);
+                        check2e_row<DC, NB>(x, DC);
                     }
                 }
             }
@@ -306,25 +301,20 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
 namespace {
 
 struct WideVariant {
-    int nj, nq, dc, rule, maxt;
+    int nj, nq, dc, maxt;
     const void* fn;         // without early stopping
     const void* fn_early;   // with early stopping
 };
 
-template <int NJ, int NQ, int DC, int RULE, int NB, int MAXT>
+template <int NJ, int NQ, int DC, int NB, int MAXT>
 constexpr WideVariant wide() {
-    return WideVariant{NJ, NQ, DC, RULE, MAXT,
-                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, RULE, NB, MAXT, false>),
-                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, RULE, NB, MAXT, true>)};
+    return WideVariant{NJ, NQ, DC, MAXT,
+                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, NB, MAXT, false>),
+                       reinterpret_cast<const void*>(&onchip_wide_kernel<NJ, NQ, DC, NB, MAXT, true>)};
 }
 
 const WideVariant kWide[] = {
-    wide<4, 1, 24, 0, 3, 1024>(),
-    wide<3, 1, 18, 0, 2, 1024>(), wide<3, 2, 18, 0, 2, 768>(),
-    wide<3, 3, 9, 0, 1, 1024>(),
-    wide<4, 1, 24, 1, 2, 1024>(),
-    wide<3, 1, 18, 1, 2, 1024>(), wide<3, 2, 18, 1, 2, 768>(),
-    wide<3, 3, 9, 1, 1, 1024>(),
+    wide<4, 1, 24, 3, 1024>(), wide<3, 1, 18, 2, 1024>(), wide<3, 2, 18, 2, 768>(), wide<3, 3, 9, 1, 1024>(),
 };
 
 // Which codes: regular bases with a base row that fills a wavefront at least
@@ -338,7 +328,7 @@ struct WideChoice {
     size_t lds;
 };
 
-bool choose_wide(const ldpc_graph* g, int rule, WideChoice& c) {
+bool choose_wide(const ldpc_graph* g, WideChoice& c) {
     if (!g || g->kind != LDPC_GRAPH_QC) return false;
     const QCDesc& D = g->qc;
     if (D.J > kOwRows || D.dc_max > kOwSlots || D.p < kOwMinP) return false;
@@ -353,7 +343,7 @@ bool choose_wide(const ldpc_graph* g, int rule, WideChoice& c) {
     const size_t lds = ((size_t)D.L * (D.p + kOwPad) + 2) * sizeof(float);
     if (lds > (size_t)limit) return false;
     for (const WideVariant& v : kWide) {
-        if (v.rule != rule || v.nj != D.J || v.dc != D.dc_max) continue;
+        if (v.nj != D.J || v.dc != D.dc_max) continue;
         const int per = (D.p + v.nq - 1) / v.nq;
         const int tb = (per + 63) / 64 * 64;
         if (tb > v.maxt) continue;
@@ -369,13 +359,14 @@ bool choose_wide(const ldpc_graph* g, int rule, WideChoice& c) {
 
 bool onchip_wide_fits(const ldpc_graph* g) {
     WideChoice c;
-    return choose_wide(g, 0, c);
+    return choose_wide(g, c);
 }
 
 int onchip_wide_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters, int early, float* post,
                        uint8_t* bits, int32_t* iters, uint8_t* converged, hipStream_t st, const float* nms_w) {
+    if (nms_w) return onchip_nms_decode(g, llr, gamma, max_iters, early, post, bits, iters, converged, st, nms_w);
     WideChoice c;
-    if (!choose_wide(g, nms_w ? 1 : 0, c)) return 0;
+    if (!choose_wide(g, c)) return 0;
     const QCDesc& D = g->qc;
     WideArgs A{};
     A.llr = llr;
@@ -383,14 +374,11 @@ int onchip_wide_decode(const ldpc_graph* g, const float* llr, int gamma, int max
     A.bits = bits;
     A.iters = iters;
     A.conv = converged;
-    A.nms_w = nms_w;
     A.n = D.n;
     A.p = D.p;
     A.L = D.L;
     A.max_iters = max_iters;
-    A.nb = D.nb;
     for (int j = 0; j < D.J; ++j) {
-        A.rb0[j] = D.rstart[j];
         for (int k = 0; k < D.dc_max; ++k) {
             const int b = D.rstart[j] + k, l = D.ecol[b];
             WideEdge& e = A.e[j * kOwSlots + k];
