@@ -454,7 +454,9 @@ ldpc_status ldpc_plan_check(ldpc_plan* plan, void* workspace, void* stream);
  * Execution: each stream is decoded from start to end by one workgroup (one
  * launch) when its window is covered: messages in registers and the window's
  * sums in LDS for codes of a full base with one circulant row per layer and
- * two columns per position (T = ms + 1 = 3, p <= 512, W = 5 or 6), else a
+ * two columns per position (T = ms + 1 = 3), p <= 512, whose layers fit 1024
+ * threads, six layers to a thread (ceil(W / 6) p <= 1024, p rounded up to 64),
+ * and whose 16 W p bytes of sums fit the LDS, else a
  * ring of messages and channel LLRs (the W + ms positions a window holds) in
  * LDS where it fits; otherwise every phase is a launch over all streams, with the
  * ring in the workspace.  Both give the same results bit for bit; the

@@ -2336,8 +2336,6 @@ static int launch_window_lds(const ldpc_graph* g, const float* llr, int gamma, i
         return 0;
     }
     if (bytes + LDPC_MAX_BLOCKS * sizeof(int) > (size_t)limit) return 0;
-    // codes it covers keep their messages in registers, others in the ring
-    if (const int r = window_decode(g, llr, gamma, W, K, post, bits, st); r != 0) return r;
     // row and column indices of a window stay below 2^22 (div_small)
     const int wl = std::min(W, g->positions + g->ms);
     if ((int64_t)wl * std::max(g->Jb, g->Lb) * g->p >= ((int64_t)1 << 22)) return 0;
@@ -2362,6 +2360,8 @@ static int window_lds(const ldpc_graph* g, const float* llr, int gamma, int W, i
                        hipStream_t st) {
     const char* env = std::getenv("LDPC_WINDOW_PATH");
     if (env && std::strcmp(env, "launch") == 0) return 0;
+    // codes it covers keep their messages in registers, others in a ring
+    if (const int r = window_decode(g, llr, gamma, W, K, post, bits, st); r != 0) return r;
     const int R = window_ring(g, W);
     const size_t eps = (size_t)(g->ms + 1) * g->Jb * g->Lb * g->p;
     const size_t c = (size_t)g->Lb * g->p;

@@ -1,6 +1,6 @@
 // Sliding-window decoder with messages in registers (window.hip).  Called by
-// ldpc_decode_window for the codes it covers, where the ring in LDS
-// (window_lds_kernel of decode.hip) would fit too.
+// ldpc_decode_window for the codes it covers; window_lds_kernel of decode.hip,
+// whose ring of messages needs more LDS, or the launches take the others.
 #pragma once
 
 #include <hip/hip_runtime_api.h>

@@ -266,9 +266,13 @@ __global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
 // host side
 // ---------------------------------------------------------------------------
 
+// Circulants that the rule below was measured for; two groups of layers at
+// least then share a workgroup.
+constexpr int kWdMostP = 512;
+
 int window_decode(const ldpc_graph* g, const float* llr, int gamma, int W, int K, float* post, uint8_t* bits,
                   hipStream_t st) {
-    if (g->Jb != 1 || g->T != kWdPeriod || g->ms + 1 != g->T || g->Lb != kWdCols) return 0;
+    if (g->Jb != 1 || g->T != kWdPeriod || g->ms + 1 != g->T || g->Lb != kWdCols || g->p > kWdMostP) return 0;
     for (int v : g->sf)
         if (v < 0) return 0;
     const int per = (g->p + 63) / 64 * 64;
