@@ -180,7 +180,7 @@ ldpc_status ldpc_decode(const ldpc_graph* g, const float* llr, int32_t gamma, in
  * (p <= 1536) or 4 rows of weight 24 (p <= 1024)), 0
  * when it runs the message-package decoder (one launch per half-iteration,
  * edge messages in the workspace; for codes of up to 8192 edges, with columns
- * of weight above 4 for batches of up to 256 frames, one launch per decode
+ * of weight above 4 for batches of no more frames than compute units, one launch per decode
  * with a frame's packages in LDS, equal bit for bit).  Batches of up to 16
  * frames of full bases of 3 rows are decoded with a frame on 16 compute units,
  * messages in the workspace, in one launch after one that clears them: rows of
@@ -487,8 +487,8 @@ ldpc_status ldpc_decode_window(const ldpc_graph* conv, const float* llr, int32_t
  * the LDS allows, at most 512 or 1024) are decoded with a stream on one
  * compute unit, several processors per sweep of the chain, the messages
  * between sweeps in the workspace: ldpc_workspace_size is then the larger of
- * that and the ring.  Where those messages of 256 streams (or all, if fewer)
- * would take more than 4 GiB, for other codes, with
+ * that and the ring.  Where those messages of as many streams as the
+ * device has compute units (or all, if fewer) would take more than 4 GiB, for other codes, with
  * LDPC_PIPELINE_PATH=launch, and when the workspace passed holds only the
  * ring, every slot is two launches over all streams.  Both give the same
  * results bit for bit.

@@ -53,6 +53,9 @@ struct Scope {
 bool set_enabled(bool on);
 }  // namespace timing
 
+// Compute units of the current device (256, an MI355X's, when there is none).
+int compute_units();
+
 }  // namespace ldpc
 
 struct ldpc_graph {

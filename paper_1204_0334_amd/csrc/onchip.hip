@@ -485,6 +485,16 @@ bool choose(const ldpc_graph* g, int rule, Choice& c) {
 
 }  // namespace
 
+int compute_units() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+        (void)hipGetLastError();
+        return 256;
+    }
+    return cus;
+}
+
 bool onchip_fits(const ldpc_graph* g) {
     Choice c;
     return choose(g, 0, c) || onchip_wide_fits(g);

@@ -1351,8 +1351,8 @@ std::vector<uint8_t> choose_kernels(const ldpc_plan* P, const PlanBuffers& B) {
 }
 
 // Deals the on-chip codes to streams, longest first to the least loaded.  A
-// code takes about 12 us and 0.2 ns per edge, iteration and round of 256
-// frames (about six iterations with early stopping), spread over several
+// code takes about 12 us and 0.2 ns per edge, iteration and round of one frame
+// per compute unit (about six iterations with early stopping), spread over several
 // units 20 us and 8 per iteration; another stream is used for every 60 us,
 // since it costs an event wait at either end.  Five codes of 27 <= p <= 2700,
 // 32 to 1024 frames, with early stopping: 236 us one after the other, 133 us
@@ -1366,7 +1366,7 @@ void deal_onchip(ldpc_plan* P) {
     std::vector<int> order;
     std::vector<double> cost(P->ncodes, 0.0);
     double total = 0.0;
-    const int iters = P->early ? std::min(P->max_iters, 6) : P->max_iters;
+    const int iters = P->early ? std::min(P->max_iters, 6) : P->max_iters, cus = compute_units();
     double phases = 0.0;
     for (int c = 0; c < P->ncodes; ++c) {
         const ldpc_graph* g = P->graphs[c];
@@ -1375,7 +1375,7 @@ void deal_onchip(ldpc_plan* P) {
             continue;
         }
         cost[c] = P->kernel[c] == kSpread ? 20.0 + 8.0 * iters
-                                          : 12.0 + 0.2e-3 * g->E * iters * ((P->gammas[c] + 255) / 256);
+                                          : 12.0 + 0.2e-3 * g->E * iters * ((P->gammas[c] + cus - 1) / cus);
         total += cost[c];
         order.push_back(c);
     }

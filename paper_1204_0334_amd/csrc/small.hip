@@ -192,7 +192,7 @@ constexpr int kSmallEdges = 8192;
 
 const SmallVariant* choose_small(const ldpc_graph* g, int gamma, size_t& lds) {
     if (!g || g->kind != LDPC_GRAPH_QC || g->qc.E == 0 || g->qc.E > kSmallEdges || onchip_fits(g)) return nullptr;
-    if (g->qc.dv_max > 4 && gamma > 256) return nullptr;
+    if (g->qc.dv_max > 4 && gamma > compute_units()) return nullptr;
     const char* path = std::getenv("LDPC_BLOCK_PATH");
     if (path && std::strcmp(path, "packages") == 0) return nullptr;
     int dev = 0, limit = 0;
@@ -228,7 +228,7 @@ int small_decode(const ldpc_graph* g, const float* llr, int gamma, int max_iters
     }
     // a thread for each row; while every frame has a compute unit to itself, for
     // each second variable too
-    const int work = gamma <= 256 ? std::max(D.m, D.n / 2) : D.m;
+    const int work = gamma <= compute_units() ? std::max(D.m, D.n / 2) : D.m;
     const int tb = std::min(512, std::max(64, (work + 63) / 64 * 64));
     timing::Scope ts(23, st);
     void* args[] = {const_cast<QCDesc*>(&D), &A};

@@ -11,11 +11,10 @@
 namespace ldpc {
 
 // The messages and sums between sweeps of a batch of streams stay within
-// kSweepMostBytes; a batch of fewer than kSweepLeastBatch streams (of more)
-// would leave compute units idle, and longer chains go to the ring, whose
-// memory does not grow with them.
+// kSweepMostBytes; a batch of fewer streams than compute units (of more) would
+// leave some idle, and longer chains go to the ring, whose memory does not grow
+// with them.
 constexpr size_t kSweepMostBytes = (size_t)4 << 30;
-constexpr int kSweepLeastBatch = 256;
 
 struct SweepPlan {
     int sweeps, batch;                   // launches per batch, streams per batch

@@ -460,7 +460,8 @@ bool sweep_plan(const ldpc_graph* g, int gamma, int iters, SweepPlan& plan) {
     // 20 processors: 3.53 ms against 3.79; 256 streams, one to a unit: 2.50
     // against 1.90), two of fewer are not (4 x 24, p = 422: 6.12 ms for K = 1
     // against 4.59 for K = 2).
-    if (gamma > kSweepLeastBatch) {
+    const int cus = compute_units();
+    if (gamma > cus) {
         int twice = 0;
         for (const SweepVariant& v : kSweeps)
             if (variant_for(g, v.K, plan.lds_limit / 2)) twice = std::max(twice, v.K);
@@ -472,7 +473,7 @@ bool sweep_plan(const ldpc_graph* g, int gamma, int iters, SweepPlan& plan) {
     plan.sum_floats = plan.sweeps > 1 ? (size_t)g->positions * c : 0;
     const size_t per = (plan.alpha_floats + plan.sum_floats) * sizeof(float);
     const size_t fit = per ? kSweepMostBytes / per : (size_t)gamma;
-    if (fit < (size_t)std::min(gamma, kSweepLeastBatch)) return false;
+    if (fit < (size_t)std::min(gamma, cus)) return false;
     const int batches = (int)(((size_t)gamma + fit - 1) / fit);
     plan.batch = (gamma + batches - 1) / batches;
     plan.bytes = align256((size_t)plan.batch * plan.alpha_floats * sizeof(float)) +

@@ -312,7 +312,7 @@ int window_decode(const ldpc_graph* g, const float* llr, int gamma, int W, int K
     // With more streams than compute units, 64 registers, so that two
     // workgroups of 1024 threads share one (p = 512, 512 streams: 7.29 ms
     // against 8.70; 256 streams: 4.46 against 4.35).
-    const bool two = gamma > 256;
+    const bool two = gamma > compute_units();
     const void* fn = nw == 1 ? reinterpret_cast<const void*>(&window_kernel<1, 1024, 8>)
                      : nw == 2 ? (two ? reinterpret_cast<const void*>(&window_kernel<2, 1024, 8>)
                                       : reinterpret_cast<const void*>(&window_kernel<2, 1024, 4>))
