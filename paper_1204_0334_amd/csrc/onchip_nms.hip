@@ -200,6 +200,7 @@ __global__ void __launch_bounds__(MAXT) onchip_nms_kernel(const NmsArgs A) {
         for (int q = 0; q < NQ; ++q) viol |= __ballot(odd[q] != 0u);
 #pragma unroll
         for (int j = 0; j < NJ - 1; ++j) {
+            if (viol != 0ull) continue;   // the wavefront has its answer
 #pragma unroll
             for (int q = 0; q < NQ; ++q) odd[q] = 0u;
             each(j, true, false, [&](int q, int, uint32_t, uint32_t, float v, float) { odd[q] ^= (uint32_t)(v < 0.0f); },

@@ -26,20 +26,24 @@
 //     against 64 bits was up to 1.24 times the package decoder's, now
 //     0.93-1.01 times.  So the alphas must still be there when a frame stops:
 //     the syndrome is tested in a pass of its own over the signs of the sums,
-//     before the next update (which a decoded frame then saves).  4 x 24, p =
-//     422, 1024 frames, early stopping 177 -> 184 us; p = 81, 300 frames 37 ->
-//     42; without early stopping 2 %.
+//     before the next update (which a decoded frame then saves); a wavefront
+//     leaves the pass at its first base row that is violated, the first of
+//     all while a frame is far from decoded.  4 x 24, early stopping, sums in
+//     LDS and no such pass / this: p = 422, 1024 frames 155 / 155 us where
+//     they decode, 1149 / 1196 (1409 over all rows) where none does in 30
+//     iterations; p = 81, 300 frames 37 / 41; without early stopping 2 %.
 //   * Row updates in place and in blocks: a row's inputs replace its old
 //     messages, and the sweeps of Eq. 3 keep suffix pairs of one block of
 //     slots at a time (check2e_row), so that the 96 messages of four rows of
 //     weight 24 and their update fit the 128 registers a thread has with four
 //     wavefronts on a SIMD.
 //
-// The decode is bound by the vector ALUs: about 25 plain instructions and 3
-// transcendentals per edge and iteration.  4 x 24 code, p = 1024, 1024
-// frames, 30 iterations: 2.50 ms (98,304 edges per frame: 1.21 10^12 edge
-// updates per second), 12.15 ms with the message-package decoder, which
-// streams every message through HBM twice an iteration.  Tried on the way
+// The decode is bound by the vector ALUs: about 22 plain instructions and 3
+// transcendentals per edge and iteration (counted; the ALUs are busy 85 % of
+// the time).  4 x 24 code, p = 1024, 1024 frames, 30 iterations: 2.50 ms
+// (98,304 edges per frame: 1.21 10^12 edge updates per second), 12.15 ms with
+// the message-package decoder, which streams every message through HBM twice
+// an iteration.  Tried on the way
 // there: (u, w, s) triples instead of pairs, two rows per thread, 512 threads
 // and run bases formed by the scalar unit 3.9 ms.
 #include <hip/hip_runtime.h>
@@ -243,13 +247,14 @@ __global__ void __launch_bounds__(MAXT) onchip_wide_kernel(const WideArgs A) {
         for (int j = 0; j < NJ; ++j) {
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
+                if (viol != 0ull) continue;   // the wavefront has its answer
+                uint32_t sx = 0;
                 if (tid4 + 4u * (uint32_t)(q * TB) < p4) {
-                    uint32_t sx = 0;
 #pragma unroll
                     for (int k = 0; k < DC; ++k)
                         sx ^= __float_as_uint(*ow_cell(cells, first_cell(j, q, k) + lane4));
-                    viol |= __ballot((int32_t)sx < 0);
                 }
+                viol = __ballot((int32_t)sx < 0);
             }
         }
         if (viol != 0ull && (tid & 63) == 0) flag[it & 1] = 1u;
