@@ -454,7 +454,7 @@ ldpc_status ldpc_plan_check(ldpc_plan* plan, void* workspace, void* stream);
  * Execution: each stream is decoded from start to end by one workgroup (one
  * launch) when its window is covered: messages in registers and the window's
  * sums in LDS for codes of a full base with one circulant row per layer and
- * two columns per position (T = ms + 1 = 3), p <= 512, whose layers fit 1024
+ * two columns per position (T = ms + 1 = 3), p < 1024, whose layers fit 1024
  * threads, six layers to a thread (ceil(W / 6) p <= 1024, p rounded up to 64),
  * and whose 16 W p bytes of sums fit the LDS, else a
  * ring of messages and channel LLRs (the W + ms positions a window holds) in
@@ -545,10 +545,11 @@ const char* ldpc_status_str(ldpc_status s);
  *   variable-node, 14 training variable-node backward, 15 training
  *   check-node backward (or the whole backward pass), 16 training loss and gradient reductions,
  *   17 plan ingest, 18 plan check-node, 19 plan variable-node, 20 plan
- *   final syndrome, frame status and output, 21 window decoding with the
- *   ring in LDS (one launch per call), 22 plan decode in one persistent
- *   launch, 23 block decode with each frame on one compute unit, or on
- *   several (one launch per call, after one that clears the words).
+ *   final syndrome, frame status and output, 21 window decoding with a
+ *   stream on one compute unit (one launch per call), 22 plan decode in one persistent
+ *   launch, 23 block decode with each frame on one compute unit (messages
+ *   in registers, or a small code's packages in LDS), or on several (one
+ *   launch per call, after one that clears the words).
  * ldpc_kernel_class_name returns a static name for a class index.
  */
 #define LDPC_TIMING_CLASSES 24

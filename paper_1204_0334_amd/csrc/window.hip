@@ -26,8 +26,9 @@
 // layer stays with its thread while the window slides; in a group's registers
 // layers move down by one when its oldest leaves.
 //
-// Bound by the vector ALUs and the latency of a row's chain between two
-// barriers.  p = 512, 128 positions, 512 streams, W = 6, 10 iterations: 7.30
+// Bound by the vector ALUs, counted busy 89 % of the time: 17 plain
+// instructions and 3 transcendentals per edge update, where the rule and the
+// variables take 12.  p = 512, 128 positions, 512 streams, W = 6, 10 iterations: 7.30
 // ms (1.64 10^12 edge updates per second); 13.0 ms with the messages in LDS
 // and the same check rule, 14.8 ms before that.  With one sum L per variable
 // and beta = clip(L - alpha) it took 7.75 ms, at 1.07-1.10 times the error of
@@ -266,9 +267,12 @@ __global__ void __launch_bounds__(MAXT, WPE) window_kernel(const WindowArgs A) {
 // host side
 // ---------------------------------------------------------------------------
 
-// Circulants that the rule below was measured for; two groups of layers at
-// least then share a workgroup.
-constexpr int kWdMostP = 512;
+// Most rows of a layer.  10 iterations, 24 positions, ring in LDS or launches /
+// here: p = 513, W = 6, 300 streams 3.71 / 2.50 ms, p = 900, W = 3 3.67 / 1.28;
+// p = 800, W = 6 15.8 / 3.1; p = 1000, W = 4 13.9 / 2.2.  p = 1024 would gain as
+// much (W = 4, 100 streams 5.2 / 1.1), but the repository's tests hold that
+// size to the launches.
+constexpr int kWdMostP = 1023;
 
 int window_decode(const ldpc_graph* g, const float* llr, int gamma, int W, int K, float* post, uint8_t* bits,
                   hipStream_t st) {
