@@ -19,8 +19,9 @@
 // three words; only the suffixes of the base rows in between lie in registers.
 // mu is read from the caller's frame, which stays in L2.
 //
-// Bound by the vector ALUs: about 26 instructions per edge and iteration, 7 for
-// addresses and 7 to 10 for alphas.  13 iterations, packages / one sum L / here:
+// Bound by the vector ALUs: 35 instructions per edge and iteration (4 x 24, p =
+// 1024, counted; the ALUs are busy 82 % of the time), since an edge's address and
+// its alpha are worked out again at every use.  13 iterations, packages / one sum L / here:
 // 4 x 24, p = 1024, 500 frames 2.00 / 0.446 / 0.629 ms; 3 x 18, p = 1500, 400
 // frames 1.59 / 0.376 / 0.419; 3 x 9, p = 2500, 300 frames 0.993 / 0.308 / 0.310.
 #include <hip/hip_runtime.h>

@@ -36,11 +36,14 @@
 // separate sums of the other alphas, which this form had before the sweeps;
 // with L - alpha for every edge and posteriors from L it was 1.05-1.09.
 //
-// A sweep moves 8 bytes per edge and 8 per variable through memory for K
-// iterations.  What bounds it is the vector ALUs and, with two wavefronts on a
-// SIMD, the latency of a row's chain from its sums to its new messages; so
-// light rows issue all processors' reads first, and memory is read a slot
-// ahead.  3 x 6 code, p = 512, 128 positions, 512 streams, 20 processors:
+// A sweep moves 8 bytes per edge and 8 per variable, and mu for each of its
+// processors, through memory for K iterations.  For 3 x 6 that is the bound:
+// p = 512, 512 streams, K = 3, counted 1.87 GB in and 1.09 GB out per sweep in
+// the middle, at 5.5 TB/s (a plain copy reaches 5.05), the vector ALUs busy
+// 74 % of the time.  4 x 24, p = 422, 256 streams, K = 2: 1.20 and 0.87 GB at
+// 4.0 TB/s, the ALUs busy 52 %: two wavefronts on a SIMD, whose rows' chains
+// from sums to new messages nothing hides.  So light rows issue all
+// processors' reads first, and memory is read a slot ahead.  3 x 6 code, p = 512, 128 positions, 512 streams, 20 processors:
 // 3.52 ms, 14.6 ms with two launches per slot; 4 x 24 code, p = 422, 64
 // positions, 256 streams: 5.19 ms, 26.4 ms.  Before reads were issued early
 // and the exchange shared the slot's barrier: 4.18 and 5.63 ms.

@@ -11,8 +11,8 @@
 namespace ldpc {
 
 // Workspace of a step of `gamma` frames and T iterations, 0 when the code is
-// not covered: full bases of 3 rows of weight 6, 9 or 18, two arrays of n
-// floats in LDS.
+// not covered: full bases of 3 rows of weight 6, 9 or 18, or of 4 rows of
+// weight 24 with p <= 768, two arrays of n floats in LDS.
 size_t train_onchip_bytes(const ldpc_graph* g, int gamma, int T);
 
 // Enqueue the forward and the backward pass (arguments as the entry points);
