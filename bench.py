@@ -36,6 +36,7 @@ METRIC = "coded Mbit/s at 20 BP iters (n=18360, Γ=1024) + %HBM peak; FER learne
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_qc36_p3060.json")
 TRAFFIC_FILE_4096 = os.path.join(ROOT, "profiles", "traffic_qc36_p3060_g4096.json")
 TRAFFIC_FILE_PIPELINE = os.path.join(ROOT, "profiles", "traffic_cc36_p512_pipeline.json")
+TRAFFIC_FILE_SWEEP = os.path.join(ROOT, "profiles", "traffic_sweep_pipelines.json")
 TRAFFIC_FILE_ONCHIP = os.path.join(ROOT, "profiles", "traffic_onchip_qc36_p3060.json")
 TRAFFIC_FILE_ONCHIP_4096 = os.path.join(ROOT, "profiles", "traffic_onchip_qc36_p3060_g4096.json")
 # counter summaries per batch size of the n = 18360 workload (none for others)
@@ -43,11 +44,14 @@ TRAFFIC_BY_GAMMA = {1024: TRAFFIC_FILE, 4096: TRAFFIC_FILE_4096}
 TRAFFIC_ONCHIP_BY_GAMMA = {1024: TRAFFIC_FILE_ONCHIP, 4096: TRAFFIC_FILE_ONCHIP_4096}
 # sources a counter record stays valid for: the package kernels (and the
 # convolutional-code kernels) live in decode.hip, the on-chip decoder in
-# onchip.hip, the one-unit training passes in train.hip
+# onchip.hip, the one-unit training passes in train.hip, the pipelined decoder
+# with a stream on one compute unit in sweep.hip
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1204_0334_amd", "csrc", f)
                   for f in ("decode.hip", "check2.h", "device.h", "internal.h")]
 TRAIN_SOURCES = [os.path.join(ROOT, "paper_1204_0334_amd", "csrc", f)
                  for f in ("train.hip", "device.h", "internal.h")]
+SWEEP_SOURCES = [os.path.join(ROOT, "paper_1204_0334_amd", "csrc", f)
+                 for f in ("sweep.hip", "sweep.h", "check2.h", "device.h", "internal.h")]
 ONCHIP_SOURCES = [os.path.join(ROOT, "paper_1204_0334_amd", "csrc", f)
                   for f in ("onchip.hip", "check2.h", "device.h", "internal.h")]
 
@@ -268,19 +272,26 @@ def bench_window(args, pipeline: bool = False):
                     "frac": round(achieved / ALU_PEAK_TOPS, 4), "traffic": None, "kernel": "window_lds",
                     "avg_launch_us": round(avg_s * 1e6, 2), "algorithmic_ops_per_launch": ops,
                     "note": "FP32 vector issue slots (transcendentals count 4) against the FP32 vector "
-                            "issue rate (256 CUs x 128 lanes x 2.4 GHz); messages stay in LDS"}
+                            "issue rate (256 CUs x 128 lanes x 2.4 GHz); messages stay in registers or LDS"}
     elif pipeline and not per_kernel["pipeline_variable_node"][0]:
         # each stream on one compute unit, several processors per sweep: the
-        # bound is the ALUs
+        # bound is what crosses memory between sweeps (average of a decode's
+        # launches); the issue rate is given beside it
         launches, ms = per_kernel["pipeline_check_node"]
         decode_s = ms / args.steps * 1e-3
         ops = pipeline_algorithmic_ops(g.info, I, gamma)
-        achieved = ops / decode_s / 1e12
-        roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": round(ALU_PEAK_TOPS, 2), "unit": "Top/s",
-                    "frac": round(achieved / ALU_PEAK_TOPS, 4), "traffic": None, "kernel": "sweep_kernel",
-                    "avg_launch_us": round(ms / launches * 1e3, 2), "algorithmic_ops_per_decode": ops,
-                    "note": "FP32 vector issue slots (transcendentals count 4) against the FP32 vector "
-                            "issue rate (256 CUs x 128 lanes x 2.4 GHz); messages cross memory once per sweep"}
+        issue = ops / decode_s / 1e12
+        traffic = measured_traffic("cc36_p512_pipeline", TRAFFIC_FILE_SWEEP, SWEEP_SOURCES)
+        achieved = None if traffic is None else traffic / (ms / launches * 1e-3) / 1e9
+        roofline = {"bound": "hbm", "achieved": None if achieved is None else round(achieved, 1),
+                    "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": None if achieved is None else round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
+                    "kernel": "sweep_kernel", "avg_launch_us": round(ms / launches * 1e3, 2),
+                    "algorithmic_ops_per_decode": ops, "issue_tops": round(issue, 2),
+                    "issue_frac": round(issue / ALU_PEAK_TOPS, 4),
+                    "note": "achieved = counted bytes per launch / launch time (null when the counters predate the "
+                            "kernels); issue = FP32 vector issue slots (transcendentals count 4) against the FP32 "
+                            "vector issue rate (256 CUs x 128 lanes x 2.4 GHz)"}
     elif pipeline:
         # the ring of 68 frames x 512 streams (about 74 MB) stays in the
         # L2 / Infinity Cache, so algorithmic bytes overstate what crosses the
