@@ -27,7 +27,7 @@
 //
 // Early stopping: a member publishes whether one of its rows is violated, in
 // a word of the same form, and every member reads all of them an iteration
-// later, beside the alphas, when L of the iteration they judge is still at
+// later, beside the alphas, when L of the iteration they speak of is still at
 // hand.
 //
 // Every wait ends, and no result depends on how one ends.  Workgroups take
@@ -247,7 +247,7 @@ spread_kernel(const SpreadArgs A) {
     };
     // the first wavefront: whether a member's rows are violated, from the
     // words of iteration it
-    auto judged = [&](uint32_t it) -> bool {
+    auto any_violated = [&](uint32_t it) -> bool {
         bool v = false;
         if (!await([&]() -> bool {
                 if (tid >= A.members) return true;
@@ -297,7 +297,7 @@ spread_kernel(const SpreadArgs A) {
         if (NW == kSpRows && alive && !await([&]() { return fetch(0); })) give_up();
         if (EARLY && it >= 3) {
             if (tid < 64) {
-                const bool any = alive && judged(want);
+                const bool any = alive && any_violated(want);
                 if (tid == 0) go = failed ? 2u : any ? 1u : 0u;
             }
             __syncthreads();
@@ -372,9 +372,9 @@ spread_kernel(const SpreadArgs A) {
     auto leave = [&]() -> uint32_t {
         return __hip_atomic_fetch_add(left, failed ? 0x10001u : 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    const bool judge = member == 0 && !stop;   // still reads the last iteration's verdicts
+    const bool verdict_due = member == 0 && !stop;   // still reads the last iteration's verdicts
     uint32_t before = 0;
-    if (tid == 0 && !judge) before = leave();
+    if (tid == 0 && !verdict_due) before = leave();
     auto put = [&](int k, uint32_t r4, float L) {
         const size_t v = f0 + (channel(0, k, r4) >> 2);
         A.post[v] = sp_packages(RULE) ? clip30(L) : unscale2(L);
@@ -385,13 +385,13 @@ spread_kernel(const SpreadArgs A) {
         for (int k = 0; k < DC; ++k) put(k, s4, Lkeep[k]);
     }
     if (member == 0 && tid < 64) {
-        const bool any = judge && !failed && judged((uint32_t)A.max_iters + 1u);
+        const bool any = verdict_due && !failed && any_violated((uint32_t)A.max_iters + 1u);
         if (tid == 0) {
             if (!failed) {
                 if (A.iters) A.iters[frame] = stop ? stop : A.max_iters;
                 if (A.conv) A.conv[frame] = any ? 0 : 1;
             }
-            if (judge) before = leave();
+            if (verdict_due) before = leave();
         }
     }
     if (tid == 0) go = (before & 0xffffu) + 1u == (uint32_t)A.members && (before >= 0x10000u || failed) ? 1u : 0u;
